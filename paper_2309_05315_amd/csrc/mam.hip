@@ -25,6 +25,7 @@
 #include "mam.h"
 #include "mam_aux_kernels.hpp"
 #include "mam_dispatch.hpp"
+#include "mam_sparse.hpp"
 #include "mam_support.hpp"
 
 namespace {
@@ -105,6 +106,9 @@ struct Prob {
   size_t o_pm = 0, o_pm_prev = 0, o_p = 0, o_p_prev = 0, o_d2 = 0, o_t = 0, o_lam = 0, o_check = 0;
   size_t o_coloff = 0, o_Sd = 0, o_aw = 0;
   size_t o_acc = 0, o_fx = 0;  // short columns: fixed-point row sums of pi_hat; scales 2^E_m, then 2^-E_m
+  // sparse iterations (mam_sparse.hpp)
+  size_t o_nbv = 0, o_eb = 0, o_bb = 0, o_dblk = 0, o_drift = 0, o_G = 0, o_par = 0, o_d2w = 0, o_cmin = 0, o_cnt = 0,
+         o_prow = 0, o_pval = 0, o_vg = 0;
   int nb = 0;
   int group = 0;
   int mbase = 0;
@@ -186,6 +190,23 @@ struct LongPlan {
   size_t o_ldiag = 0, o_wdiag = 0;
 };
 
+// Sparse iterations of short-column plans: between the first and the last
+// iteration of a call the plans are kept as their patches (mam_sparse.hpp).
+struct SparsePlan {
+  bool on = false;    // the kernels take this plan's shapes
+  bool off = false;   // left out by the caller of the layout (no room for it)
+  bool use = false;   // decided by mam_init
+  int cols = 16;      // columns per wave
+  int mmax = 0;
+  bool finite = false;  // some problem has a finite gamma
+  int64_t plan_bytes = 0;
+  std::vector<mam::SpTile> tiles;
+  std::vector<mam::SpRows> rows;
+  std::vector<mam::SpCost> costs;
+  std::vector<mam::CandTask> cand;
+  size_t o_probs = 0, o_tiles = 0, o_rows = 0, o_costs = 0, o_cand = 0, o_stat = 0;
+};
+
 struct Plan {
   int dtype = MAM_F64;
   bool batch = false;
@@ -210,6 +231,8 @@ struct Plan {
   Adjoint adj;
   Bundles bund;
   LongPlan lg;
+  SparsePlan sp;
+  hipGraphExec_t sgexec = nullptr;  // graph_iters sparse iterations
   bool diag_valid = false;
   // graph of a fixed number of iterations
   int64_t graph_iters = 0;
@@ -231,7 +254,7 @@ struct Plan {
   const int32_t* gate = nullptr;
   int32_t* host_flag = nullptr;
   hipGraphExec_t uexec = nullptr;
-  int utest = -1;
+  int utest = -1, umode = -1;
   int64_t uevery = 0;
   std::vector<hipEvent_t> uev;
 
@@ -244,6 +267,7 @@ struct Plan {
     if (gfork) hipEventDestroy(gfork);
     for (hipStream_t s : gstream) hipStreamDestroy(s);
     if (gexec) hipGraphExecDestroy(gexec);
+    if (sgexec) hipGraphExecDestroy(sgexec);
     if (capture_stream) hipStreamDestroy(capture_stream);
   }
 };
@@ -442,6 +466,67 @@ int group_block(const Group& g) { return g.ng == 1 ? mam::kOneGroupBlock : g.kc;
 // so rebuilding after the index is known never grows it.
 void build_long_schedule(Plan* pl);
 
+// Tables of the sparse iterations.  They depend on the problem sizes alone.
+//
+// Columns per wave: the lanes of a wave settle one column each, and the
+// columns they leave open are taken four at a time, so a wave of few columns
+// has a short worst case (four: one round) and one of many needs fewer waves.
+//
+// Small plans stay dense: a sparse iteration costs 12-14 us on them whatever
+// their size, a dense one 11 us plus its plan traffic.  Measured, microseconds
+// per iteration over 200 iterations, dense against patches: 2.1 MB of plans
+// 11.6 / 13.5, 4.2 MB 16.8 / 16.4, 5.3 MB 18.4 / 13.3, 34 MB 26 / 12.4.
+//
+// Limits: the close kernel holds 64 rows of every measure in LDS
+// (kSparseMaxM measures), tiles hold 32-bit column numbers, and
+// MAM_FLAG_COLD asks for cold threshold searches, which the dense kernels do.
+void add_tiles(std::vector<mam::SpTile>& out, const Prob& p, int pi, int64_t m, int cols, bool first) {
+  for (int64_t j = p.col_off[m]; j < p.col_off[m + 1]; j += cols) {
+    const int n = (int)std::min<int64_t>(cols, p.col_off[m + 1] - j);
+    out.push_back({pi, (int32_t)m, (int32_t)j, n | (first && j == p.col_off[m] ? 1 << 16 : 0)});
+  }
+}
+
+constexpr int64_t kSparseMinBytes = (int64_t)5 << 20;
+
+void build_sparse_tables(Plan* pl) {
+  SparsePlan& sp = pl->sp;
+  sp.tiles.clear();
+  sp.rows.clear();
+  sp.costs.clear();
+  sp.cand.clear();
+  int64_t T = 0;
+  sp.mmax = 0;
+  sp.finite = false;
+  sp.plan_bytes = 0;
+  for (const Prob& p : pl->P) sp.plan_bytes += p.ld * p.T * (int64_t)elem_bytes(pl->dtype);
+  sp.on = !sp.off && sp.plan_bytes >= kSparseMinBytes;
+  for (const Prob& p : pl->P) {
+    T += p.T;
+    sp.finite = sp.finite || !std::isinf(p.gamma);
+    sp.mmax = std::max<int>(sp.mmax, (int)p.M);
+    if (p.R > kShortMaxR || p.M > mam::kSparseMaxM || (p.flags & MAM_FLAG_COLD) || p.T >= ((int64_t)1 << 30) ||
+        p.cost_ncols >= ((int64_t)1 << 30))
+      sp.on = false;
+  }
+  if (!sp.on) return;
+  sp.cols = T <= (1 << 14) ? 4 : (T <= (1 << 15) ? 8 : (T <= (1 << 18) ? 16 : 32));
+  const int64_t ns = std::max<int64_t>(2, 64 / (int64_t)pl->P.size());
+  for (size_t pi = 0; pi < pl->P.size(); ++pi) {
+    const Prob& p = pl->P[pi];
+    for (int64_t m = 0; m < p.M; ++m) add_tiles(sp.tiles, p, (int)pi, m, sp.cols, m == 0);
+    const int nblk = (int)((p.R + mam::kBlkRows - 1) / mam::kBlkRows);
+    for (int b = 0; b < nblk; ++b) sp.rows.push_back({(int32_t)pi, b});
+    for (int64_t c = 0; c < p.cost_ncols; c += 16)
+      sp.costs.push_back({(int32_t)pi, (int32_t)c, (int32_t)std::min<int64_t>(16, p.cost_ncols - c), 0});
+    for (int64_t k = 0; k < std::min(ns, p.T); ++k) {
+      const int64_t j = (2 * k + 1) * p.T / (2 * std::min(ns, p.T));
+      const int64_t m = std::upper_bound(p.col_off.begin(), p.col_off.end(), j) - p.col_off.begin() - 1;
+      sp.cand.push_back({(int32_t)pi, (int32_t)m, j});
+    }
+  }
+}
+
 // Team sweeps.  A group's workgroups form teams of 'team' workgroups; each
 // team takes an equal contiguous share of the group's column order and
 // deals it out in blocks of NG*kc columns, round robin over its workgroups,
@@ -564,6 +649,7 @@ void build_schedule(Plan* pl) {
   if (!pl->ws) {
     pl->nseg_cap = std::max<size_t>(cap_segs, pl->seg_p.size());
     pl->partial_cap = 0;
+    build_sparse_tables(pl);
   }
   pl->tables_uploaded = false;
 }
@@ -737,14 +823,42 @@ void build_layout(Plan* pl) {
       lg.o_spar = take(4);
     }
   }
+  SparsePlan& sp = pl->sp;
+  const bool spon = !pl->lg.on && sp.on;
+  if (spon) {
+    sp.o_probs = take(pl->P.size() * std::max(sizeof(mam::SpProb<float>), sizeof(mam::SpProb<double>)));
+    sp.o_tiles = take(sp.tiles.size() * sizeof(mam::SpTile));
+    sp.o_rows = take(sp.rows.size() * sizeof(mam::SpRows));
+    sp.o_costs = take(sp.costs.size() * sizeof(mam::SpCost));
+    sp.o_cand = take(sp.cand.size() * sizeof(mam::CandTask));
+    sp.o_stat = take(8);
+  }
   for (Prob& p : pl->P) {
     const size_t R = (size_t)p.R, M = (size_t)p.M;
+    if (spon) {
+      const size_t eb = elem_bytes(pl->dtype), T = (size_t)p.T, C = (size_t)p.cost_ncols;
+      const size_t nblk = (R + mam::kBlkRows - 1) / mam::kBlkRows, Rp = nblk * mam::kBlkRows;
+      p.o_nbv = take(M * Rp * eb);
+      p.o_eb = take(M * Rp * 8);
+      const size_t nblkp = (nblk + 3) / 4 * 4;
+      p.o_bb = take(M * Rp * 8);
+      p.o_dblk = take(M * nblkp * 8);
+      p.o_drift = take(2 * M * nblkp * 8);
+      p.o_G = take(M * 8);
+      p.o_par = take(2 * 4);
+      p.o_d2w = take(nblk * 8);
+      p.o_cmin = take(C * nblkp * eb);
+      p.o_cnt = take(T * 4);
+      p.o_prow = take(T * mam::kPatch * 4);
+      p.o_pval = take(T * mam::kPatch * eb);
+      p.o_vg = take(T * 8);
+    }
     p.o_pm = take(M * R * 8);
     p.o_pm_prev = take(M * R * 8);
     p.o_p = take(R * 8);
     p.o_p_prev = take(R * 8);
     p.o_d2 = take((size_t)p.nb * 8);
-    p.o_t = take(8);
+    p.o_t = take(2 * 8);
     p.o_lam = take((size_t)p.T * 8);
     p.o_check = take((M + 2) * 8);
     p.o_coloff = take((M + 1) * 8);
@@ -874,6 +988,10 @@ void drop_graphs(Plan* pl) {
     hipGraphExecDestroy(pl->gexec);
     pl->gexec = nullptr;
   }
+  if (pl->sgexec) {
+    hipGraphExecDestroy(pl->sgexec);
+    pl->sgexec = nullptr;
+  }
   if (pl->uexec) {
     hipGraphExecDestroy(pl->uexec);
     pl->uexec = nullptr;
@@ -961,6 +1079,72 @@ void fill_probdev(Plan* pl, std::vector<mam::ProbDev<T>>& out) {
 }
 
 
+int log2_of(int x) {
+  int k = 0;
+  while ((1 << k) < x) ++k;
+  return k;
+}
+
+template <typename T>
+void fill_spprob(Plan* pl, std::vector<mam::SpProb<T>>& out) {
+  out.resize(pl->P.size());
+  for (size_t i = 0; i < pl->P.size(); ++i) {
+    const Prob& p = pl->P[i];
+    const Group& g = pl->G[p.group];
+    mam::SpProb<T>& d = out[i];
+    d = {};
+    d.theta = static_cast<T*>(p.theta);
+    d.cost = static_cast<const T*>(p.cost);
+    d.q = static_cast<const T*>(p.q);
+    d.cidx = p.cidx;
+    d.acc = at<unsigned long long>(pl, p.o_acc);
+    d.fx = at<double>(pl, p.o_fx);
+    d.ld = p.ld;
+    d.cost_ld = p.cost_ld;
+    d.tcols = p.T;
+    d.R = (int32_t)p.R;
+    d.nblk = (int32_t)((p.R + mam::kBlkRows - 1) / mam::kBlkRows);
+    d.nblkp = (d.nblk + 3) / 4 * 4;
+    d.Rp = d.nblk * mam::kBlkRows;
+    d.cost_mode = p.cost_mode;
+    d.relaxed = (p.flags & MAM_FLAG_RELAXED) ? 1 : 0;
+    d.balanced = std::isinf(p.gamma) ? 1 : 0;
+    d.ntl = log2_of(g.nt);
+    d.vecl = log2_of(g.vec);
+    d.vpt = g.vpt;
+    d.M = (int32_t)p.M;
+    const int vn = vec_width(pl->dtype);
+    d.vec_cost = reinterpret_cast<uintptr_t>(p.cost) % 16 == 0 && p.cost_ld % vn == 0;
+    d.vec_theta = reinterpret_cast<uintptr_t>(p.theta) % 16 == 0 && p.ld % vn == 0;
+    d.rho = p.rho;
+    d.inv_rho = 1.0 / p.rho;
+    d.gamma = p.gamma;
+    d.pm = at<double>(pl, p.o_pm);
+    d.pm_prev = at<double>(pl, p.o_pm_prev);
+    d.p = at<double>(pl, p.o_p);
+    d.p_prev = at<double>(pl, p.o_p_prev);
+    d.aw = at<double>(pl, p.o_aw);
+    d.Sd = at<double>(pl, p.o_Sd);
+    d.d2w = at<double>(pl, p.o_d2w);
+    d.d2part = at<double>(pl, p.o_d2);
+    d.lam = at<double>(pl, p.o_lam);
+    d.t_out = at<double>(pl, p.o_t);
+    d.col_off = at<int64_t>(pl, p.o_coloff);
+    d.nbv = at<T>(pl, p.o_nbv);
+    d.eb = at<double>(pl, p.o_eb);
+    d.dblk = at<double>(pl, p.o_dblk);
+    d.cmin = at<T>(pl, p.o_cmin);
+    d.bb = at<double>(pl, p.o_bb);
+    d.drift = at<double>(pl, p.o_drift);
+    d.G = at<double>(pl, p.o_G);
+    d.par = at<int32_t>(pl, p.o_par);
+    d.cnt = at<int32_t>(pl, p.o_cnt);
+    d.prow = at<int32_t>(pl, p.o_prow);
+    d.pval = at<T>(pl, p.o_pval);
+    d.vg = at<double>(pl, p.o_vg);
+  }
+}
+
 // Host staging for the table uploads; the copies complete before it is
 // released (the upload synchronizes the stream).
 mam_status upload_tables(Plan* pl, hipStream_t st) {
@@ -1010,6 +1194,22 @@ mam_status upload_tables(Plan* pl, hipStream_t st) {
     TRY(put(lg.o_it_poff, lg.it_poff.data(), lg.it_poff.size() * 8));
     TRY(put(lg.o_wg_it, lg.wg_it.data(), lg.wg_it.size() * 4));
   }
+  std::vector<mam::SpProb<float>> spf;
+  std::vector<mam::SpProb<double>> spd;
+  if (!pl->lg.on && pl->sp.on) {
+    const SparsePlan& sp = pl->sp;
+    if (pl->dtype == MAM_F32) {
+      fill_spprob<float>(pl, spf);
+      TRY(put(sp.o_probs, spf.data(), spf.size() * sizeof(spf[0])));
+    } else {
+      fill_spprob<double>(pl, spd);
+      TRY(put(sp.o_probs, spd.data(), spd.size() * sizeof(spd[0])));
+    }
+    TRY(put(sp.o_tiles, sp.tiles.data(), sp.tiles.size() * sizeof(mam::SpTile)));
+    TRY(put(sp.o_rows, sp.rows.data(), sp.rows.size() * sizeof(mam::SpRows)));
+    TRY(put(sp.o_costs, sp.costs.data(), sp.costs.size() * sizeof(mam::SpCost)));
+    TRY(put(sp.o_cand, sp.cand.data(), sp.cand.size() * sizeof(mam::CandTask)));
+  }
   std::vector<mam::ProbDev<float>> pdf;
   std::vector<mam::ProbDev<double>> pdd;
   if (pl->dtype == MAM_F32) {
@@ -1040,8 +1240,9 @@ mam_status group_streams(Plan* pl) {
   return MAM_OK;
 }
 
+// sparse: the SPARSE instances (patches stored instead of plans).
 template <typename T>
-mam_status launch_columns(Plan* pl, hipStream_t st, int diag, uint8_t* rec, int64_t rec_ld) {
+mam_status launch_columns(Plan* pl, hipStream_t st, int diag, uint8_t* rec, int64_t rec_ld, bool sparse = false) {
   const Layout& L = pl->lay;
   const bool fork = pl->G.size() > 1 && pl->capturing;
   if (fork) {
@@ -1054,6 +1255,7 @@ mam_status launch_columns(Plan* pl, hipStream_t st, int diag, uint8_t* rec, int6
     if (fork) HIP_TRY(hipStreamWaitEvent(gs, pl->gfork, 0));
     mam::ColArgs<T> a;
     a.probs = at<mam::ProbDev<T>>(pl, L.probdev);
+    a.sp = sparse ? at<mam::SpProb<T>>(pl, pl->sp.o_probs) : nullptr;
     a.seg_p = at<int32_t>(pl, L.seg_p);
     a.seg_m = at<int32_t>(pl, L.seg_m);
     a.seg_j0 = at<int64_t>(pl, L.seg_j0);
@@ -1070,7 +1272,8 @@ mam_status launch_columns(Plan* pl, hipStream_t st, int diag, uint8_t* rec, int6
     const int kc = g.vec == 1 ? 1 : g.kc;
     if (g.nt < 64 && (diag || rec))
       return fail(MAM_EUNSUPPORTED, "diagnostics and the reverse mode need 64 or more threads per column");
-    mam::ColFn<T> fn = mam::pick_column<T>(g.nt, g.vpt, g.vec, kc, diag, g.stream);
+    mam::ColFn<T> fn = sparse ? mam::pick_column_sparse<T>(g.nt, g.vpt, g.vec)
+                              : mam::pick_column<T>(g.nt, g.vpt, g.vec, kc, diag, g.stream);
     if (!fn) return fail(MAM_EUNSUPPORTED, "no column kernel for nt=%d vpt=%d vec=%d kc=%d", g.nt, g.vpt, g.vec, kc);
     const int wgsize = g.nt <= 64 ? 256 : g.nt;
     const size_t shmem = (size_t)g.vpt * g.nt * 8 * (1 + g.ng);
@@ -1393,6 +1596,35 @@ mam_status resident_workgroups(Plan* pl, bool* changed) {
   return MAM_OK;
 }
 
+// Whether calls keep their plans as patches, from a sample of the columns:
+// the rows that a threshold w_max - q_s without corrections would leave
+// possibly active.  Small active sets are what the patches are for; where
+// most columns overflow their kPatch entries, the dense kernels are faster.
+// Measured on 32x32 and 64x64 grids, 8 measures, FP32, microseconds per
+// iteration over 20 iterations, dense against patches: rho = 4 (25-33
+// candidates) 40 against 35 and 230 against 173; rho = 16 (84-130) 41 against
+// 90 and 233 against 712, with the sets shrinking too slowly to make it good
+// (even after 100 iterations on the smaller grid).
+constexpr double kSparseMaxCandidates = 48.0;
+
+template <typename T>
+mam_status sparse_decide(Plan* pl, hipStream_t st) {
+  SparsePlan& sp = pl->sp;
+  sp.use = false;
+  if (pl->lg.on || !sp.on) return MAM_OK;
+  double* const stat = at<double>(pl, sp.o_stat);
+  hipLaunchKernelGGL(mam::zero_kernel, dim3(1), dim3(64), 0, st, stat, 1);
+  LAUNCH_CHECK("zero_kernel");
+  hipLaunchKernelGGL(mam::candidates_kernel<T>, dim3((unsigned)sp.cand.size()), dim3(256), 0, st,
+                     at<mam::ProbDev<T>>(pl, pl->lay.probdev), at<mam::CandTask>(pl, sp.o_cand), stat);
+  LAUNCH_CHECK("candidates_kernel");
+  double sum = 0.0;
+  HIP_TRY(hipMemcpyAsync(&sum, stat, 8, hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  sp.use = sum <= kSparseMaxCandidates * (double)sp.cand.size();
+  return MAM_OK;
+}
+
 mam_status plan_init(Plan* pl, const void* const* theta0, hipStream_t st) {
   if (!pl->ws) return fail(MAM_ESTATE, "no workspace");
   for (size_t i = 0; i < pl->P.size(); ++i)
@@ -1420,6 +1652,7 @@ mam_status plan_init(Plan* pl, const void* const* theta0, hipStream_t st) {
   drop_graphs(pl);
   TRY(upload_tables(pl, st));
   TRY(pl->dtype == MAM_F32 ? launch_checks<float>(pl, st) : launch_checks<double>(pl, st));
+  TRY(pl->dtype == MAM_F32 ? sparse_decide<float>(pl, st) : sparse_decide<double>(pl, st));
   std::vector<double> fx;
   for (size_t i = 0; i < pl->P.size(); ++i) {
     Prob& p = pl->P[i];
@@ -1486,15 +1719,156 @@ mam_status one_iteration(Plan* pl, hipStream_t st, int diag, uint8_t* rec = null
   return launch_marginals(pl, st, save_prev < 0 ? diag : save_prev);
 }
 
+// ---------------------------------------------------------------------------
+// sparse iterations: a call of several iterations reads the bound plans in
+// its first and writes them back when it returns (mam_sparse.hpp)
+// ---------------------------------------------------------------------------
+template <typename T>
+mam_status launch_sparse_columns(Plan* pl, const mam::SpTile* tiles, size_t ntiles, uint8_t* rec, int64_t rec_ld,
+                                 hipStream_t st) {
+  const mam::SparseFns<T> fn = mam::pick_sparse<T>();
+  mam::SpArgs<T> a;
+  a.probs = at<mam::SpProb<T>>(pl, pl->sp.o_probs);
+  a.tiles = tiles;
+  a.ntiles = (int32_t)ntiles;
+  a.stop = pl->gate;
+  a.rec = rec;
+  a.rec_ld = rec_ld;
+  hipLaunchKernelGGL(rec ? fn.column_rec : fn.column, dim3((unsigned)((ntiles + 3) / 4)), dim3(256), 0, st, a);
+  LAUNCH_CHECK("sparse_column_kernel");
+  return MAM_OK;
+}
+
+// Steps 3 and 1: 64 rows of every measure per workgroup, up to 16 waves.
+template <typename T>
+mam_status launch_sparse_close(Plan* pl, int save_prev, const uint8_t* upd, int mode, hipStream_t st) {
+  const SparsePlan& sp = pl->sp;
+  const mam::SparseFns<T> fn = mam::pick_sparse<T>();
+  const int waves = std::min(16, sp.mmax);
+  const size_t shmem = (size_t)sp.mmax * 64 * (16 + sizeof(T));
+  if (shmem > 65536)
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(fn.close), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)shmem));
+  hipLaunchKernelGGL(fn.close, dim3((unsigned)sp.rows.size()), dim3(64 * waves), shmem, st,
+                     at<mam::SpProb<T>>(pl, sp.o_probs), at<mam::SpRows>(pl, sp.o_rows), save_prev, upd, mode,
+                     pl->gate);
+  LAUNCH_CHECK("sparse_close_kernel");
+  if (sp.finite) {
+    hipLaunchKernelGGL(fn.next, dim3((unsigned)sp.rows.size()), dim3(64 * waves), 0, st,
+                       at<mam::SpProb<T>>(pl, sp.o_probs), at<mam::SpRows>(pl, sp.o_rows), upd, mode, pl->gate);
+    LAUNCH_CHECK("sparse_next_kernel");
+  }
+  return MAM_OK;
+}
+
+template <typename T>
+mam_status launch_sparse_d2(Plan* pl, hipStream_t st) {
+  if (!pl->sp.finite) return MAM_OK;
+  hipLaunchKernelGGL(mam::pick_sparse<T>().d2, dim3((unsigned)pl->P.size()), dim3(256), 0, st,
+                     at<mam::SpProb<T>>(pl, pl->sp.o_probs), pl->gate);
+  LAUNCH_CHECK("sparse_d2_kernel");
+  return MAM_OK;
+}
+
+template <typename T>
+mam_status launch_sparse_write(Plan* pl, const mam::SpTile* tiles, size_t ntiles, hipStream_t st) {
+  hipLaunchKernelGGL(mam::pick_sparse<T>().write, dim3((unsigned)ntiles), dim3(256), 0, st,
+                     at<mam::SpProb<T>>(pl, pl->sp.o_probs), tiles, pl->gate);
+  LAUNCH_CHECK("sparse_write_kernel");
+  return MAM_OK;
+}
+
+// Whether a run of 'iters' iterations keeps its plans as patches.  Its first
+// iterations cost more (the cost's block minima, a first look at every
+// column, the write-back): runs break even at 6-8 iterations on plans of
+// 10-80 MB and between 3 and 4 on 1.6 GB.
+bool sparse_use(const Plan* pl, int64_t iters) {
+  return !pl->lg.on && pl->sp.on && pl->sp.use && iters >= (pl->sp.plan_bytes >= ((int64_t)256 << 20) ? 4 : 8);
+}
+
+// Start of a call: the cost's block minima (the cost may have been rebuilt
+// in place since the last call).  Plans with sub-wave groups have no SPARSE
+// first iteration: their columns all start as stored dense.
+template <typename T>
+mam_status sparse_begin_t(Plan* pl, bool* first, hipStream_t st) {
+  const SparsePlan& sp = pl->sp;
+  const mam::SparseFns<T> fn = mam::pick_sparse<T>();
+  const mam::SpProb<T>* probs = at<mam::SpProb<T>>(pl, sp.o_probs);
+  hipLaunchKernelGGL(fn.cost_min, dim3((unsigned)sp.costs.size()), dim3(256), 0, st, probs,
+                     at<mam::SpCost>(pl, sp.o_costs), pl->gate);
+  LAUNCH_CHECK("cost_min_kernel");
+  *first = true;
+  for (const Group& g : pl->G) *first = *first && g.nt >= 64;
+  if (!*first) {
+    TRY(launch_sparse_close<T>(pl, 0, nullptr, mam::kSpNone, st));
+    hipLaunchKernelGGL(fn.all_dense, dim3((unsigned)((sp.tiles.size() + 3) / 4)), dim3(256), 0, st, probs,
+                       at<mam::SpTile>(pl, sp.o_tiles), (int)sp.tiles.size());
+    LAUNCH_CHECK("sparse_dense_kernel");
+  }
+  return MAM_OK;
+}
+
+mam_status sparse_begin(Plan* pl, bool* first, hipStream_t st) {
+  return pl->dtype == MAM_F32 ? sparse_begin_t<float>(pl, first, st) : sparse_begin_t<double>(pl, first, st);
+}
+
+// One iteration; first: it reads the bound plans (SPARSE column kernel).
+template <typename T>
+mam_status sparse_iteration_t(Plan* pl, bool first, hipStream_t st, uint8_t* rec, int64_t rec_ld, int save_prev) {
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  if (rec && pl->G[0].nt < 64)
+    return fail(MAM_EUNSUPPORTED, "diagnostics and the reverse mode need 64 or more threads per column");
+  if (rec && !first) {
+    // the recorded words start at zero; the kernel sets the active bits
+    const int64_t n = pl->P[0].T * rec_ld / 8;
+    hipLaunchKernelGGL(mam::fill_value_kernel, dim3((unsigned)std::min<int64_t>(4096, (n + 255) / 256)), dim3(256), 0,
+                       st, reinterpret_cast<double*>(rec), n, 0.0);
+    LAUNCH_CHECK("fill_value_kernel");
+  }
+  if (pl->timing) {
+    e0 = next_event(pl);
+    e1 = next_event(pl);
+    if (!e0 || !e1) return fail(MAM_EHIP, "hipEventCreate failed");
+    HIP_TRY(hipEventRecord(e0, st));
+  }
+  if (first) TRY(launch_columns<T>(pl, st, 0, rec, rec_ld, true));
+  else
+    TRY(launch_sparse_columns<T>(pl, at<mam::SpTile>(pl, pl->sp.o_tiles), pl->sp.tiles.size(), rec, rec_ld, st));
+  if (pl->timing) HIP_TRY(hipEventRecord(e1, st));
+  return launch_sparse_close<T>(pl, save_prev, nullptr, first ? mam::kSpFirst : mam::kSpNext, st);
+}
+
+mam_status sparse_iteration(Plan* pl, bool first, hipStream_t st, uint8_t* rec = nullptr, int64_t rec_ld = 0,
+                            int save_prev = 0) {
+  return pl->dtype == MAM_F32 ? sparse_iteration_t<float>(pl, first, st, rec, rec_ld, save_prev)
+                              : sparse_iteration_t<double>(pl, first, st, rec, rec_ld, save_prev);
+}
+
+// The plans (and the dense kernels' d^2 partials) written back; the patches
+// stay valid, so further sparse iterations may follow.
+template <typename T>
+mam_status sparse_end_t(Plan* pl, hipStream_t st) {
+  TRY(launch_sparse_d2<T>(pl, st));
+  return launch_sparse_write<T>(pl, at<mam::SpTile>(pl, pl->sp.o_tiles), pl->sp.tiles.size(), st);
+}
+
+mam_status sparse_end(Plan* pl, hipStream_t st) {
+  return pl->dtype == MAM_F32 ? sparse_end_t<float>(pl, st) : sparse_end_t<double>(pl, st);
+}
+
 // Capture graph_iters iterations once on a stream of the library's own (a
 // caller's legacy default stream cannot be captured); replays run on the
 // caller's stream.
-mam_status capture_graph(Plan* pl) {
+template <typename Body>
+mam_status capture(Plan* pl, hipGraphExec_t* out, Body&& body) {
   if (!pl->capture_stream) HIP_TRY(hipStreamCreateWithFlags(&pl->capture_stream, hipStreamNonBlocking));
+  if (*out) {
+    hipGraphExecDestroy(*out);
+    *out = nullptr;
+  }
   HIP_TRY(hipStreamBeginCapture(pl->capture_stream, hipStreamCaptureModeThreadLocal));
-  mam_status s = MAM_OK;
   pl->capturing = true;
-  for (int64_t k = 0; k < pl->graph_iters && s == MAM_OK; ++k) s = one_iteration(pl, pl->capture_stream, 0);
+  const mam_status s = body(pl->capture_stream);
   pl->capturing = false;
   hipGraph_t graph = nullptr;
   const hipError_t e = hipStreamEndCapture(pl->capture_stream, &graph);
@@ -1503,35 +1877,52 @@ mam_status capture_graph(Plan* pl) {
     return s;
   }
   if (e != hipSuccess) return fail(MAM_EHIP, "graph capture failed: %s", hipGetErrorString(e));
-  const hipError_t e2 = hipGraphInstantiate(&pl->gexec, graph, nullptr, nullptr, 0);
+  const hipError_t e2 = hipGraphInstantiate(out, graph, nullptr, nullptr, 0);
   hipGraphDestroy(graph);
   if (e2 != hipSuccess) {
-    pl->gexec = nullptr;
+    *out = nullptr;
     return fail(MAM_EHIP, "graph instantiation failed: %s", hipGetErrorString(e2));
   }
+  return MAM_OK;
+}
+
+// graph_iters dense or sparse iterations as one graph.
+mam_status capture_graph(Plan* pl, bool sparse) {
+  return capture(pl, sparse ? &pl->sgexec : &pl->gexec, [&](hipStream_t st) -> mam_status {
+    for (int64_t k = 0; k < pl->graph_iters; ++k) TRY(sparse ? sparse_iteration(pl, false, st) : one_iteration(pl, st, 0));
+    return MAM_OK;
+  });
+}
+
+// Iterations k .. end - 1 of a call, whole graphs of them first.
+mam_status run_iterations(Plan* pl, int64_t k, int64_t end, bool sparse, hipStream_t st) {
+  if (pl->graph_iters > 0 && !pl->timing && end - k >= pl->graph_iters) {
+    hipGraphExec_t* const g = sparse ? &pl->sgexec : &pl->gexec;
+    if (!*g) TRY(capture_graph(pl, sparse));
+    for (; end - k >= pl->graph_iters; k += pl->graph_iters) HIP_TRY(hipGraphLaunch(*g, st));
+  }
+  for (; k < end; ++k) TRY(sparse ? sparse_iteration(pl, false, st) : one_iteration(pl, st, 0));
   return MAM_OK;
 }
 
 mam_status plan_iterate(Plan* pl, int64_t iters, hipStream_t st) {
   if (iters < 0) return fail(MAM_EINVAL, "iters must be >= 0");
   if (!pl->inited) return fail(MAM_ESTATE, "mam_init has not run");
-  const bool want_diag = !pl->batch && (pl->P[0].flags & MAM_FLAG_DIAG);
-  int64_t k = 0;
-  if (pl->graph_iters > 0 && !pl->timing) {
-    // keep the last iteration outside the graph when it computes diagnostics
-    const int64_t plain = want_diag ? 1 : 0;
-    if (iters - plain >= pl->graph_iters) {
-      if (!pl->gexec) TRY(capture_graph(pl));
-      while (iters - k - plain >= pl->graph_iters) {
-        HIP_TRY(hipGraphLaunch(pl->gexec, st));
-        k += pl->graph_iters;
-      }
-    }
+  // the last iteration computes the diagnostics, outside any graph
+  const bool diag = !pl->batch && (pl->P[0].flags & MAM_FLAG_DIAG) && iters > 0;
+  const int64_t plain = iters - (diag ? 1 : 0);
+  if (sparse_use(pl, plain)) {
+    bool first = false;
+    TRY(sparse_begin(pl, &first, st));
+    if (first) TRY(sparse_iteration(pl, true, st));
+    TRY(run_iterations(pl, first ? 1 : 0, plain, true, st));
+    TRY(sparse_end(pl, st));
+  } else {
+    TRY(run_iterations(pl, 0, plain, false, st));
   }
-  for (; k < iters; ++k) {
-    const int diag = want_diag && k == iters - 1;
-    TRY(one_iteration(pl, st, diag));
-    if (diag) pl->diag_valid = true;
+  if (diag) {
+    TRY(one_iteration(pl, st, 1));
+    pl->diag_valid = true;
   }
   pl->iters_done += iters;
   return sparse_writeback(pl, st);
@@ -1542,6 +1933,10 @@ mam_status plan_graph(Plan* pl, int64_t iters) {
   if (pl->gexec) {
     hipGraphExecDestroy(pl->gexec);
     pl->gexec = nullptr;
+  }
+  if (pl->sgexec) {
+    hipGraphExecDestroy(pl->sgexec);
+    pl->sgexec = nullptr;
   }
   pl->graph_iters = iters;
   return MAM_OK;
@@ -1558,10 +1953,33 @@ static_assert(MAM_STOP_DTHETA == mam::STOP_DTHETA && MAM_STOP_DP == mam::STOP_DP
 // One check period: every-1 plain iterations, then the check iteration
 // (diagnostics of the column kernel for the theta test, previous marginals
 // kept for the others) and the test itself, all gated by the stop flag.
-mam_status until_period(Plan* pl, hipStream_t st, int test, int64_t every) {
+// How the iterations of a run are taken: dense; sparse (the plans stay
+// patches over all periods: the tests on the marginals never read them); or
+// sparse inside a period, whose check iteration is dense (the theta test
+// compares dense plans).
+enum UntilMode { kUntilDense, kUntilSparse, kUntilPeriod };
+
+mam_status until_period(Plan* pl, hipStream_t st, int test, int64_t every, UntilMode mode, bool start) {
   const Layout& L = pl->lay;
-  for (int64_t k = 0; k + 1 < every; ++k) TRY(one_iteration(pl, st, 0));
-  TRY(one_iteration(pl, st, test == MAM_STOP_DTHETA ? 1 : 0, nullptr, 0, 1));
+  bool first = start;  // kUntilSparse: the run's first iteration reads the bound plans
+  if (mode == kUntilSparse) {
+    for (int64_t k = 0; k < every; ++k) {
+      TRY(sparse_iteration(pl, first, st, nullptr, 0, k + 1 == every ? 1 : 0));
+      first = false;
+    }
+  } else {
+    if (mode == kUntilPeriod) {
+      TRY(sparse_begin(pl, &first, st));
+      for (int64_t k = 0; k + 1 < every; ++k) {
+        TRY(sparse_iteration(pl, first, st));
+        first = false;
+      }
+      TRY(sparse_end(pl, st));
+    } else {
+      for (int64_t k = 0; k + 1 < every; ++k) TRY(one_iteration(pl, st, 0));
+    }
+    TRY(one_iteration(pl, st, test == MAM_STOP_DTHETA ? 1 : 0, nullptr, 0, 1));
+  }
   mam::StopState* ss = at<mam::StopState>(pl, L.stop);
   const Prob& pr = pl->P[0];
   if (test != MAM_STOP_DTHETA) {
@@ -1580,31 +1998,11 @@ mam_status until_period(Plan* pl, hipStream_t st, int test, int64_t every) {
   return MAM_OK;
 }
 
-mam_status capture_until(Plan* pl, int test, int64_t every) {
-  if (!pl->capture_stream) HIP_TRY(hipStreamCreateWithFlags(&pl->capture_stream, hipStreamNonBlocking));
-  if (pl->uexec) {
-    hipGraphExecDestroy(pl->uexec);
-    pl->uexec = nullptr;
-  }
-  HIP_TRY(hipStreamBeginCapture(pl->capture_stream, hipStreamCaptureModeThreadLocal));
-  pl->capturing = true;
-  const mam_status s = until_period(pl, pl->capture_stream, test, every);
-  pl->capturing = false;
-  hipGraph_t graph = nullptr;
-  const hipError_t e = hipStreamEndCapture(pl->capture_stream, &graph);
-  if (s != MAM_OK) {
-    if (graph) hipGraphDestroy(graph);
-    return s;
-  }
-  if (e != hipSuccess) return fail(MAM_EHIP, "graph capture failed: %s", hipGetErrorString(e));
-  const hipError_t e2 = hipGraphInstantiate(&pl->uexec, graph, nullptr, nullptr, 0);
-  hipGraphDestroy(graph);
-  if (e2 != hipSuccess) {
-    pl->uexec = nullptr;
-    return fail(MAM_EHIP, "graph instantiation failed: %s", hipGetErrorString(e2));
-  }
+mam_status capture_until(Plan* pl, int test, int64_t every, UntilMode mode) {
+  TRY(capture(pl, &pl->uexec, [&](hipStream_t st) { return until_period(pl, st, test, every, mode, false); }));
   pl->utest = test;
   pl->uevery = every;
+  pl->umode = mode;
   return MAM_OK;
 }
 
@@ -1626,8 +2024,19 @@ mam_status until_run(Plan* pl, int64_t max_iters, int test, double tol, int64_t 
   LAUNCH_CHECK("stop_reset_kernel");
   const int64_t periods = max_iters / every, tail = max_iters % every;
   const bool graph = pl->graph_iters > 0 && !pl->timing;
-  if (graph && periods > 0 && (!pl->uexec || pl->utest != test || pl->uevery != every))
-    TRY(capture_until(pl, test, every));
+  UntilMode mode = kUntilDense;
+  if (test != MAM_STOP_DTHETA) {
+    if (sparse_use(pl, max_iters)) mode = kUntilSparse;
+  } else if (sparse_use(pl, every - 1)) {
+    mode = kUntilPeriod;
+  }
+  bool start = false;
+  if (mode == kUntilSparse) {
+    TRY(sparse_begin(pl, &start, st));
+  }
+  if (graph && periods > (start ? 1 : 0) &&
+      (!pl->uexec || pl->utest != test || pl->uevery != every || pl->umode != mode))
+    TRY(capture_until(pl, test, every, mode));
   const int64_t ahead = std::max<int64_t>(2, (32 + every - 1) / every);
   while ((int64_t)pl->uev.size() < ahead) {
     hipEvent_t e = nullptr;
@@ -1643,12 +2052,25 @@ mam_status until_run(Plan* pl, int64_t max_iters, int test, double tol, int64_t 
         break;
       }
     }
-    if (graph) HIP_TRY(hipGraphLaunch(pl->uexec, st));
-    else TRY(until_period(pl, st, test, every));
+    if (graph && !start) HIP_TRY(hipGraphLaunch(pl->uexec, st));
+    else TRY(until_period(pl, st, test, every, mode, start));
+    start = false;
     HIP_TRY(hipEventRecord(pl->uev[i % ahead], st));
   }
-  if (!seen_stop)
-    for (int64_t k = 0; k < tail; ++k) TRY(one_iteration(pl, st, 0));
+  if (!seen_stop) {
+    for (int64_t k = 0; k < tail; ++k) {
+      TRY(mode == kUntilSparse ? sparse_iteration(pl, start, st) : one_iteration(pl, st, 0));
+      start = false;
+    }
+  }
+  if (mode == kUntilSparse) {
+    // the gated launches left the iterate of the stop: it is written back
+    const int32_t* const gate = pl->gate;
+    pl->gate = nullptr;
+    const mam_status s = sparse_end(pl, st);
+    pl->gate = gate;
+    TRY(s);
+  }
   mam::StopState hs{};
   HIP_TRY(hipMemcpyAsync(&hs, ss, sizeof(hs), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
@@ -1772,8 +2194,12 @@ mam_status launch_copy(T* dst, const T* src, const Prob& p, hipStream_t st) {
 mam_status record_range(Plan* pl, int64_t k0, int64_t k1, int64_t rec_from, bool ckpt, hipStream_t st) {
   Adjoint& A = pl->adj;
   const Prob& p = pl->P[0];
+  const bool sparse = sparse_use(pl, k1 - k0);
+  bool first = false;
+  if (sparse) TRY(sparse_begin(pl, &first, st));
   for (int64_t k = k0; k < k1; ++k) {
     if (ckpt && k > 0 && k % A.C == 0) {
+      if (sparse && k > k0) TRY(sparse_end(pl, st));
       char* dst = A.ws + A.o_ckpt + (size_t)(k / A.C - 1) * A.ckpt_bytes;
       if (pl->dtype == MAM_F32)
         TRY(launch_copy<float>(reinterpret_cast<float*>(dst), static_cast<const float*>(p.theta), p, st));
@@ -1784,6 +2210,8 @@ mam_status record_range(Plan* pl, int64_t k0, int64_t k1, int64_t rec_from, bool
                              hipMemcpyDeviceToDevice, st));
     }
     if (A.unbal && k >= rec_from) {
+      if (sparse && k > k0)
+        TRY(pl->dtype == MAM_F32 ? launch_sparse_d2<float>(pl, st) : launch_sparse_d2<double>(pl, st));
       // the iteration's p^(m), p and d^2 partials, as its column kernel reads them
       const size_t sl = (size_t)(k % (A.C + 1));
       const size_t MR = (size_t)p.M * (size_t)p.R;
@@ -1793,9 +2221,12 @@ mam_status record_range(Plan* pl, int64_t k0, int64_t k1, int64_t rec_from, bool
       HIP_TRY(hipMemcpyAsync(A.ws + A.o_d2_rec + sl * (size_t)p.nb * 8, pl->ws + p.o_d2, (size_t)p.nb * 8,
                              hipMemcpyDeviceToDevice, st));
     }
-    TRY(one_iteration(pl, st, 0, k >= rec_from ? mask_slot(pl, k) : nullptr, A.mld));
+    uint8_t* const rec = k >= rec_from ? mask_slot(pl, k) : nullptr;
+    if (sparse) TRY(sparse_iteration(pl, first, st, rec, A.mld));
+    else TRY(one_iteration(pl, st, 0, rec, A.mld));
+    first = false;
   }
-  return MAM_OK;
+  return sparse ? sparse_end(pl, st) : MAM_OK;
 }
 
 mam_status plan_record(Plan* pl, int64_t K, int64_t C, void* ws, size_t bytes, hipStream_t st) {
@@ -2619,6 +3050,12 @@ mam_status mam_solve_static(const mam_desc* d, void* theta, const void* cost, co
   // the handle lives for this call only; the kernels queued on 'stream'
   // read only the caller's buffers and the static workspace, which outlive it
   std::unique_ptr<mam_problem, void (*)(mam_problem*)> h(raw, mam_destroy);
+  if (mam_workspace_bytes(h.get()) > kStaticScratchBytes) {
+    // the sparse iterations' tables may be what does not fit: dense then
+    h->plan.sp.off = true;
+    build_schedule(&h->plan);
+    build_layout(&h->plan);
+  }
   const size_t need = mam_workspace_bytes(h.get());
   if (need > kStaticScratchBytes)
     return fail(MAM_ENOMEM, "this problem needs %zu bytes of workspace; the static workspace holds %zu",

@@ -343,6 +343,37 @@ check_cost_kernel(const T* __restrict__ cost, int64_t cost_ld, int R, int64_t nc
   if (bad) flag[0] = 1.0;
 }
 
+// Start-up estimate of the active sets (whether a call keeps its plans as
+// patches): over the sampled columns, the number of rows within rho q_s of
+// the column's least cost, i.e. those the threshold of a column without
+// corrections could make active (w_max - q_s < w).  Whole numbers, so the
+// sum does not depend on the order of the additions.
+struct CandTask {
+  int32_t prob, m;
+  int64_t j;
+};
+template <typename T>
+__global__ void __launch_bounds__(256)
+candidates_kernel(const ProbDev<T>* __restrict__ probs, const CandTask* __restrict__ tasks, double* __restrict__ sum) {
+  __shared__ double sh[4];
+  const CandTask tk = tasks[blockIdx.x];
+  const ProbDev<T>& P = probs[tk.prob];
+  const int64_t cc = P.cost_mode == MAM_COST_INDEXED ? (int64_t)P.cidx[tk.j]
+                     : (P.cost_mode == MAM_COST_SHARED ? tk.j - P.col_off[tk.m] : tk.j);
+  const T* const col = P.cost + cc * P.cost_ld;
+  double mn = __builtin_huge_val();
+  for (int r = threadIdx.x; r < P.R; r += 256) mn = fmin(mn, (double)col[r]);
+  mn = wave_reduce<OpMin>(mn);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = mn;
+  __syncthreads();
+  mn = fmin(fmin(sh[0], sh[1]), fmin(sh[2], sh[3]));
+  const double width = (double)P.q[tk.j] * P.rho;
+  double n = 0.0;
+  for (int r = threadIdx.x; r < P.R; r += 256) n += (double)col[r] - mn < width ? 1.0 : 0.0;
+  n = wave_sum(n);
+  if ((threadIdx.x & 63) == 0) atomicAdd(sum, n);
+}
+
 __global__ void __launch_bounds__(256)
 check_index_kernel(const int32_t* __restrict__ idx, int64_t n, int64_t ncols, double* __restrict__ flag) {
   bool bad = false;

@@ -20,6 +20,34 @@ ColFn<T> pick_column_kc(int nt, int vpt, int vec, int stream);
 template <typename T>
 ColFn<T> pick_column_diag(int nt, int vpt, int vec);
 
+// First iteration of a sparse call (64 or more threads per column): theta
+// read, patches stored.
+template <typename T>
+ColFn<T> pick_column_sparse(int nt, int vpt, int vec);
+extern template ColFn<float> pick_column_sparse<float>(int, int, int);
+extern template ColFn<double> pick_column_sparse<double>(int, int, int);
+
+// Kernels of the sparse iterations (mam_sparse.hpp).
+template <typename T> struct SpArgs;
+struct SpTile;
+struct SpRows;
+struct SpCost;
+template <typename T>
+struct SparseFns {
+  void (*column)(SpArgs<T>) = nullptr;
+  void (*column_rec)(SpArgs<T>) = nullptr;  // records the active sets
+  void (*close)(const SpProb<T>*, const SpRows*, int, const uint8_t*, int, const int32_t*) = nullptr;
+  void (*next)(const SpProb<T>*, const SpRows*, const uint8_t*, int, const int32_t*) = nullptr;
+  void (*write)(const SpProb<T>*, const SpTile*, const int32_t*) = nullptr;
+  void (*d2)(const SpProb<T>*, const int32_t*) = nullptr;
+  void (*cost_min)(const SpProb<T>*, const SpCost*, const int32_t*) = nullptr;
+  void (*all_dense)(const SpProb<T>*, const SpTile*, int) = nullptr;
+};
+template <typename T>
+SparseFns<T> pick_sparse();
+extern template SparseFns<float> pick_sparse<float>();
+extern template SparseFns<double> pick_sparse<double>();
+
 // Sub-wave instance (16 or 32 lanes per column, one column in flight, no
 // diagnostics) or nullptr.
 template <typename T>

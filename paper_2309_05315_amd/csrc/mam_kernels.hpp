@@ -456,9 +456,13 @@ struct ProbDev {
   const double* Sd;       // S^m as double
 };
 
+constexpr int kPatch = 16;  // patches a column keeps between sparse iterations (mam_sparse.hpp)
+template <typename T> struct SpProb;
+
 template <typename T>
 struct ColArgs {
   const ProbDev<T>* probs;
+  const SpProb<T>* sp;    // SPARSE instances: where the columns' patches go, per problem
   const int32_t* seg_p;   // problem of each segment
   const int32_t* seg_m;   // measure of each segment
   const int64_t* seg_j0;  // first column
@@ -619,6 +623,12 @@ struct Rounds {
 // waits inside a step.  STREAM instances load and store theta with the
 // non-temporal policy (plans larger than the Infinity Cache).
 //
+// SPARSE instances (the first iteration of a call that keeps its plans as
+// patches, mam_sparse.hpp) read theta as the others do, but store a column of
+// at most kPatch active entries as the list of them (count, rows, values)
+// and only the others dense, with count -1.  A column with weight and no
+// active entry lists row 0 as an inactive entry.
+//
 // Dynamic LDS: VPT*NT doubles of b^(m) (with one group per workgroup each
 // thread reads and writes only its own slots), then NG*VPT*NT doubles of
 // row sums of pi_hat, one block per group (own slots per thread).
@@ -629,9 +639,10 @@ struct Rounds {
 template <typename T, int VPT, int KC>
 constexpr int col_waves() { return sizeof(T) * VPT * KC <= 16 ? 5 : (sizeof(T) * VPT * KC <= 32 ? 4 : 2); }
 
-template <typename T, int NT, int VPT, int VEC, int KC, bool DIAG, bool STREAM = false>
+template <typename T, int NT, int VPT, int VEC, int KC, bool DIAG, bool STREAM = false, bool SPARSE = false>
 __global__ void __launch_bounds__(GroupShape<NT>::WG, (col_waves<T, VPT, KC>()))
 column_kernel(ColArgs<T> a) {
+  static_assert(!SPARSE || (KC == 1 && !DIAG), "the sparse form takes one column at a time");
   constexpr int WG = GroupShape<NT>::WG;
   constexpr int NG = GroupShape<NT>::NG;  // independent column groups per workgroup
   constexpr int NW = NT / 64;             // waves per group
@@ -779,7 +790,12 @@ column_kernel(ColArgs<T> a) {
 
     // t^k of this problem from its d^2 partials
     const double t = damping_t(gptr(P.d2part), uniform_i(P.nb), uniform_d(P.rho), uniform_d(P.gamma), lane);
-    if (gtid == 0 && j0 == 0) gptr(P.t_out)[0] = t;
+    // (a sparse launch may leave out measure 0: every segment writes the same t)
+    if (gtid == 0 && (SPARSE || j0 == 0)) gptr(P.t_out)[0] = t;
+    if constexpr (SPARSE) {
+      const SpProb<T>& SP = a.sp[uniform_i(a.seg_p[si])];
+      if (gtid == 0) gptr(SP.par)[0] = gptr(SP.par)[1];
+    }
 
     // b^(m) = t (p - p^(m)) / S^m at this thread's rows, in LDS (a thread
     // holds the same rows in every column of the segment; with several
@@ -960,9 +976,27 @@ column_kernel(ColArgs<T> a) {
         T out[VPT];
 #pragma unroll
         for (int k = 0; k < VPT; ++k) out[k] = nb[k];
+        const bool listed = SPARSE && nact[kc] <= kPatch;
         if (__ballot(mask[kc] != 0) != 0ull) {
+          int at0 = 0;  // sparse: list entries of the waves and slots before this one
+          if constexpr (SPARSE && NW > 1) {
+            // the waves' counts of the round that settled the column
+            for (int i = 0; i < wv; ++i) at0 += red_i[(rounds.par ^ 1) * NW + i];
+          }
 #pragma unroll
           for (int k = 0; k < VPT; ++k) {
+            if constexpr (SPARSE) {
+              if (listed) {
+                const unsigned long long bal = __ballot((mask[kc] >> k) & 1);
+                if ((mask[kc] >> k) & 1) {
+                  const SpProb<T>& SP = a.sp[uniform_i(a.seg_p[si])];
+                  const int64_t at = (int64_t)(at0 + __popcll(bal & ((1ull << lane) - 1ull))) * SP.tcols + j;
+                  gptr(SP.prow)[at] = ((k / VEC) * NT + tid) * VEC + (k % VEC);
+                  gptr(SP.pval)[at] = (T)(fmax(w[kc][k] - lout[kc], 0.0) - lds_b[k * NT + tid]);
+                }
+                at0 += __popcll(bal);
+              }
+            }
             if ((mask[kc] >> k) & 1) {
               const double ph = fmax(w[kc][k] - lout[kc], 0.0);
               out[k] = (T)(ph - lds_b[k * NT + tid]);
@@ -974,10 +1008,22 @@ column_kernel(ColArgs<T> a) {
             }
           }
         }
+        if constexpr (SPARSE) {
+          if (tid == 0) {
+            const SpProb<T>& SP = a.sp[uniform_i(a.seg_p[si])];
+            const bool weight = tau[kc] > 0.0;
+            if (weight && nact[kc] == 0) {
+              gptr(SP.prow)[j] = 0;
+              gptr(SP.pval)[j] = nb[0];
+            }
+            gptr(SP.cnt)[j] = !listed ? -1 : (!weight ? 0 : (nact[kc] > 1 ? nact[kc] : 1));
+            gptr(SP.vg)[j] = __builtin_huge_val();  // nothing known about the other rows
+          }
+        }
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
           const int r0 = (c * NT + tid) * VEC;
-          if (r0 < R) {
+          if (r0 < R && !listed) {
             if constexpr (DIAG) {
 #pragma unroll
               for (int v = 0; v < VEC; ++v)

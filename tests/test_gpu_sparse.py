@@ -1,0 +1,155 @@
+"""Calls of several iterations against the same iterations one call at a time
+(MI355X only).
+
+A call of one iteration runs the dense column kernels; a call of eight or
+more on at least 5 MiB of plans keeps them as -b plus their active entries in
+between.  Both store the
+same values and add the same numbers in the same order, so plans, marginals
+and barycenters are compared bit for bit.  The dense kernels are held to the
+oracle in the other files; here the sizes are the edges of the sparse
+kernels: blocks of 64 rows, superblocks of 1024, partial vectors, columns
+with more active entries than a column lists, columns without weight or with
+a weight below the rounding of w, every cost layout.
+"""
+import dataclasses
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2309_05315_amd import inputs
+from paper_2309_05315_amd import mam
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+def state(s):
+    return (s.barycenter().cpu().numpy(), s.marginals().cpu().numpy(), s.theta.cpu().numpy())
+
+
+def both(p, iters, graph=0, **kw):
+    """(one call per iteration, one call) from the default start."""
+    out = []
+    for whole in (False, True):
+        say(f"case {p.name} R={p.R} M={p.M} T={p.T} {p.dtype} rho={p.rho} gamma={p.gamma} iters={iters} {kw} whole={whole}")
+        s = mam.solver_for(p, **kw)
+        if whole and graph:
+            s.graph(graph)
+        s.init()
+        if whole:
+            s.iterate(iters)
+        else:
+            for _ in range(iters):
+                s.iterate(1)
+        out.append(state(s))
+        s.close()
+    return out
+
+
+def same(a, b):
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y), float(np.abs(x - y).max())
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("R,S", [(5, [90001, 1, 180000]), (63, [9000, 12001]), (64, [21000]), (65, [10007, 11000]),
+                                 (1023, [700, 619, 7]), (1025, [707, 623]), (4099, [210, 113]), (8192, [84, 83])])
+def test_ragged_sizes(R, S, dtype):
+    """Random supports: rows at the edges of the blocks, columns without
+    weight, waves of 4 (up to 2^13 columns), 16 and 32 columns."""
+    p = inputs.tiny_problem(R + len(S), R=R, S=S, dtype=dtype, zero_frac=0.15)
+    same(*both(p, 14))
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("nt", [16, 64, 128, 256])
+def test_threshold_sums_keep_the_column_kernels_order(dtype, nt):
+    """Active sets of three and more entries in every thread shape (also the
+    sub-wave ones, which start a call differently), and more of them than a
+    column lists: rho widens the sets."""
+    p = inputs.balanced_plain(K=16, M=22, dtype=dtype)
+    for rho in (1.0, 3.0):
+        same(*both(dataclasses.replace(p, rho=rho), 9, threads_per_column=nt))
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("gamma,relaxed", [(0.05, False), (0.2, True), (0.0, False)])
+def test_unbalanced_and_relaxed(gamma, relaxed, dtype):
+    p = inputs.tiny_problem(23, R=1100, S=[470, 341, 488], masses=[0.7, 1.0, 1.3], gamma=gamma, dtype=dtype)
+    if relaxed:
+        p = dataclasses.replace(p, cost=(p.cost - 0.002).astype(np.float32).astype(np.float64))
+    same(*both(p, 20, relaxed=relaxed))
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_small_weights_and_graph_replay(dtype):
+    """Gaussian tails (weights far below the rounding of w: columns without
+    an active entry), an indexed cost, replayed from a graph."""
+    same(*both(inputs.balanced_plain(K=24, M=5, dtype=dtype), 40, graph=8))
+    same(*both(inputs.balanced_sparse(K=22, M=40, dtype=dtype), 30, graph=7))
+
+
+def test_unaligned_plans_and_a_cost_rebuilt_in_place():
+    """Column strides off the vector width; the cost changed between two
+    calls (its block minima belong to one call); padding rows untouched."""
+    p = inputs.tiny_problem(61, R=301, S=[2160, 2229], dtype="f32")
+    res = []
+    for whole in (False, True):
+        s = mam.Solver(301, p.S, dtype=torch.float32, cost_mode=mam.COST_PER_COLUMN, cost_ncols=p.T, ld=303, cost_ld=301)
+        cost = torch.from_numpy(p.cost).float().cuda()
+        theta = torch.full((p.T, 303), 123.0, device="cuda")
+        s.bind(theta, cost, torch.from_numpy(p.q).float().cuda())
+        s.init()
+        for _ in range(3):
+            if whole:
+                s.iterate(8)
+            else:
+                for _ in range(8):
+                    s.iterate(1)
+            cost.copy_(cost.roll(7, 0))
+        assert bool((theta[:, 301:] == 123.0).all())
+        res.append(state(s))
+        s.close()
+    same(*res)
+
+
+@pytest.mark.parametrize("test", ["dp", "dist", "dtheta"])
+def test_stopping_tests(test):
+    """A run stopped by its test leaves the iterate of the same plain iterations."""
+    p = inputs.balanced_sparse(K=26, M=4, dtype="f64")
+    s = mam.solver_for(p)
+    s.init()
+    s.graph(5)
+    probe = s.iterate_until(36, test, -1.0, 9)
+    s.init()
+    r = s.iterate_until(400, test, probe["value"], 9)
+    # (the value need not fall monotonically: an earlier check may meet it too)
+    assert r["converged"] and r["iterations"] <= 36 and r["value"] <= probe["value"]
+    got = state(s)
+    s.init()
+    for _ in range(r["iterations"]):
+        s.iterate(1)
+    same(state(s), got)
+
+
+def test_recorded_active_sets():
+    """Reverse mode over a recorded sparse run against windows of one
+    iteration, which the dense kernels record."""
+    for p in (inputs.adjoint_problem(K=24, M=3, dtype="f64")[0],
+              dataclasses.replace(inputs.unbalanced_dense(K=22, M=7, gamma=0.02, dtype="f32"), rho=3.0)):
+        g = torch.linspace(-1, 1, p.R, dtype=torch.float64, device="cuda")
+        grads = []
+        for ck in (0, 9, 1):
+            s = mam.solver_for(p)
+            s.init()
+            s.record(20, ck)
+            grads.append([x.cpu().numpy() for x in s.backward(g)])
+            s.close()
+        assert np.abs(grads[0][1]).max() > 0.0
+        for other in grads[1:]:
+            same(grads[0], other)
