@@ -160,6 +160,9 @@ struct BundleSched {
   size_t nseg = 0;
   size_t o_seg_p = 0, o_seg_m = 0, o_seg_j0 = 0, o_seg_j1 = 0, o_seg_st = 0, o_wg_seg = 0, o_mtasks = 0;
   size_t nmtasks = 0;
+  // sparse iterations: the bundle's tiles, and per measure whether it updates
+  // it (1), or does so as its first sparse iteration (2)
+  size_t ntiles = 0, o_tiles = 0, o_upd = 0, o_upd_first = 0;
 };
 
 struct Bundles {
@@ -2425,6 +2428,8 @@ struct BundleHost {
   std::vector<int32_t> seg_p, seg_m, wg_seg, seg_st;
   std::vector<int64_t> seg_j0, seg_j1;
   std::vector<mam::MargTask> mtasks;
+  std::vector<mam::SpTile> tiles;
+  std::vector<uint8_t> upd, upd_first;
 };
 
 mam_status bundle_check(const Plan* pl, const int32_t* bundle_of, int32_t nb) {
@@ -2475,6 +2480,15 @@ void bundle_build(const Plan* pl, const int32_t* bundle_of, int bi, BundleHost* 
   h->wg_seg.push_back((int32_t)h->seg_m.size());
   for (int64_t m : ms)
     for (int64_t r0 = 0; r0 < p.R; r0 += 256) h->mtasks.push_back({0, (int32_t)m, (int32_t)r0, (int32_t)m});
+  if (pl->sp.on) {
+    h->upd.assign(p.M, 0);
+    h->upd_first.assign(p.M, 0);
+    for (int64_t m : ms) {
+      add_tiles(h->tiles, p, 0, m, pl->sp.cols, m == ms[0]);
+      h->upd[m] = 1;
+      h->upd_first[m] = 2;
+    }
+  }
   *nwg_out = nwg;
 }
 
@@ -2505,6 +2519,10 @@ size_t bundle_layout(const Plan* pl, const int32_t* bundle_of, int32_t nb, Bundl
     bs.o_seg_st = take(bs.nseg * 4);
     bs.o_wg_seg = take(((size_t)nwg + 1) * 4);
     bs.o_mtasks = take(bs.nmtasks * sizeof(mam::MargTask));
+    bs.ntiles = h.tiles.size();
+    bs.o_tiles = take(bs.ntiles * sizeof(mam::SpTile));
+    bs.o_upd = take(h.upd.size());
+    bs.o_upd_first = take(h.upd_first.size());
   }
   if (out) *out = B;
   return o;
@@ -2536,6 +2554,9 @@ mam_status plan_set_bundles(Plan* pl, const int32_t* bundle_of, int32_t nb, void
     TRY(put(bs.o_seg_st, h.seg_st.data(), h.seg_st.size() * 4));
     TRY(put(bs.o_wg_seg, h.wg_seg.data(), h.wg_seg.size() * 4));
     TRY(put(bs.o_mtasks, h.mtasks.data(), h.mtasks.size() * sizeof(mam::MargTask)));
+    TRY(put(bs.o_tiles, h.tiles.data(), h.tiles.size() * sizeof(mam::SpTile)));
+    TRY(put(bs.o_upd, h.upd.data(), h.upd.size()));
+    TRY(put(bs.o_upd_first, h.upd_first.data(), h.upd_first.size()));
     HIP_TRY(hipStreamSynchronize(st));  // host staging is released at the end of this loop body
   }
   pl->bund = B;
@@ -2543,12 +2564,13 @@ mam_status plan_set_bundles(Plan* pl, const int32_t* bundle_of, int32_t nb, void
 }
 
 template <typename T>
-mam_status launch_bundle_columns(Plan* pl, const BundleSched& bs, hipStream_t st) {
+mam_status launch_bundle_columns(Plan* pl, const BundleSched& bs, hipStream_t st, bool sparse = false) {
   const Layout& L = pl->lay;
   const Group& g = pl->G[0];
   char* bw = pl->bund.ws;
   mam::ColArgs<T> a;
   a.probs = at<mam::ProbDev<T>>(pl, L.probdev);
+  a.sp = sparse ? at<mam::SpProb<T>>(pl, pl->sp.o_probs) : nullptr;
   a.seg_p = reinterpret_cast<const int32_t*>(bw + bs.o_seg_p);
   a.seg_m = reinterpret_cast<const int32_t*>(bw + bs.o_seg_m);
   a.seg_j0 = reinterpret_cast<const int64_t*>(bw + bs.o_seg_j0);
@@ -2563,7 +2585,8 @@ mam_status launch_bundle_columns(Plan* pl, const BundleSched& bs, hipStream_t st
   a.xcd_remap = 0;
   a.kb = group_block(g);
   const int kc = g.vec == 1 ? 1 : g.kc;
-  mam::ColFn<T> fn = mam::pick_column<T>(g.nt, g.vpt, g.vec, kc, 0, g.stream);
+  mam::ColFn<T> fn = sparse ? mam::pick_column_sparse<T>(g.nt, g.vpt, g.vec)
+                            : mam::pick_column<T>(g.nt, g.vpt, g.vec, kc, 0, g.stream);
   if (!fn) return fail(MAM_EUNSUPPORTED, "no column kernel for nt=%d vpt=%d vec=%d kc=%d", g.nt, g.vpt, g.vec, kc);
   const int wgsize = g.nt <= 64 ? 256 : g.nt;
   const size_t shmem = (size_t)g.vpt * g.nt * 8 * (1 + g.ng);
@@ -2572,6 +2595,44 @@ mam_status launch_bundle_columns(Plan* pl, const BundleSched& bs, hipStream_t st
                                 (int)shmem));
   hipLaunchKernelGGL(fn, dim3(bs.nwg), dim3(wgsize), shmem, st, a);
   LAUNCH_CHECK("column_kernel");
+  return MAM_OK;
+}
+
+// The draws of one call with sparse iterations.  A bundle's first draw reads
+// its measures' bound plans; measures that are not drawn keep theirs in theta.
+// Every iteration moves p and with it b of every measure, so the close kernel
+// forms the next b and the rise of base for all of them.
+template <typename T>
+mam_status iterate_bundles_sparse(Plan* pl, int64_t iters, const int32_t* seq, hipStream_t st) {
+  bool first = false;
+  TRY(sparse_begin_t<T>(pl, &first, st));
+  std::vector<char> seen(pl->bund.nb, 0);
+  char* const bw = pl->bund.ws;
+  for (int64_t k = 0; k < iters; ++k) {
+    const BundleSched& bs = pl->bund.b[seq[k]];
+    const bool fresh = !seen[seq[k]];
+    seen[seq[k]] = 1;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (fresh && k > 0) TRY(launch_sparse_d2<T>(pl, st));
+    if (pl->timing) {
+      e0 = next_event(pl);
+      e1 = next_event(pl);
+      if (!e0 || !e1) return fail(MAM_EHIP, "hipEventCreate failed");
+      HIP_TRY(hipEventRecord(e0, st));
+    }
+    if (fresh) TRY(launch_bundle_columns<T>(pl, bs, st, true));
+    else
+      TRY(launch_sparse_columns<T>(pl, reinterpret_cast<const mam::SpTile*>(bw + bs.o_tiles), bs.ntiles, nullptr, 0,
+                                   st));
+    if (pl->timing) HIP_TRY(hipEventRecord(e1, st));
+    TRY(launch_sparse_close<T>(pl, 0, reinterpret_cast<const uint8_t*>(bw + (fresh ? bs.o_upd_first : bs.o_upd)),
+                               k == 0 ? mam::kSpFirst : mam::kSpNext, st));
+  }
+  TRY(launch_sparse_d2<T>(pl, st));
+  for (int i = 0; i < pl->bund.nb; ++i) {
+    const BundleSched& bs = pl->bund.b[i];
+    if (seen[i]) TRY(launch_sparse_write<T>(pl, reinterpret_cast<const mam::SpTile*>(bw + bs.o_tiles), bs.ntiles, st));
+  }
   return MAM_OK;
 }
 
@@ -2584,6 +2645,14 @@ mam_status plan_iterate_bundles(Plan* pl, int64_t iters, const int32_t* seq, hip
     if (seq[k] < 0 || seq[k] >= pl->bund.nb)
       return fail(MAM_EINVAL, "seq[%lld] = %d is not a bundle", (long long)k, seq[k]);
   const Layout& L = pl->lay;
+  // (sub-wave groups have no SPARSE first iteration)
+  if (sparse_use(pl, iters / pl->bund.nb) && pl->G[0].nt >= 64) {
+    TRY(pl->dtype == MAM_F32 ? iterate_bundles_sparse<float>(pl, iters, seq, st)
+                             : iterate_bundles_sparse<double>(pl, iters, seq, st));
+    pl->iters_done += iters;
+    pl->diag_valid = false;
+    return MAM_OK;
+  }
   for (int64_t k = 0; k < iters; ++k) {
     const BundleSched& bs = pl->bund.b[seq[k]];
     hipEvent_t e0 = nullptr, e1 = nullptr;

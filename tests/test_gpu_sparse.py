@@ -153,3 +153,28 @@ def test_recorded_active_sets():
         assert np.abs(grads[0][1]).max() > 0.0
         for other in grads[1:]:
             same(grads[0], other)
+
+
+@pytest.mark.parametrize("dtype,gamma", [("f64", np.inf), ("f32", np.inf), ("f32", 0.05)])
+def test_bundles(dtype, gamma):
+    """Bundles that are first drawn late in a call, and one that is not drawn
+    at all (its plans stay as they were)."""
+    p = inputs.balanced_sparse(K=24, M=9, dtype=dtype)
+    if np.isfinite(gamma):
+        p = dataclasses.replace(p, gamma=gamma)
+    seq = [0, 0, 1, 0, 1, 1, 0] * 5 + [2] * 3 + [1, 2, 0, 1] * 4
+    res = []
+    for whole in (False, True):
+        say(f"case bundles {dtype} gamma={gamma} whole={whole}")
+        s = mam.solver_for(p)
+        s.init()
+        s.set_bundles([m % 4 for m in range(p.M)])
+        for part in (seq, seq[::-1]):
+            if whole:
+                s.iterate_bundles(part)
+            else:
+                for b in part:
+                    s.iterate_bundles([b])
+        res.append(state(s))
+        s.close()
+    same(*res)
