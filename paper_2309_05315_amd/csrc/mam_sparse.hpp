@@ -1119,8 +1119,8 @@ sparse_d2_kernel(const SpProb<T>* __restrict__ probs, const int32_t* __restrict_
 }
 
 // The plans back into theta: nbv with the patches in place (columns stored
-// dense are there already).  A workgroup takes one tile; a thread holds four
-// rows of nbv and walks the tile's columns.
+// dense are there already).  A workgroup takes one tile; a thread holds 16
+// bytes or two times 16 of nbv and walks the tile's columns.
 template <typename T>
 __global__ void __launch_bounds__(256)
 sparse_write_kernel(const SpProb<T>* __restrict__ probs, const SpTile* __restrict__ tiles,
@@ -1146,34 +1146,41 @@ sparse_write_kernel(const SpProb<T>* __restrict__ probs, const SpTile* __restric
   const bool vec = P->vec_theta != 0;
   const T* const nbv = gptr(P->nbv) + (int64_t)m * P->Rp;
   T* const theta = gptr(P->theta);
-  constexpr int VN = VecOf<T>::N;
-  for (int r0 = threadIdx.x * 4; r0 < R; r0 += 1024) {
-    T nb[4];
-    load_row4<T>(nbv + r0, nb);
+  // 1024 rows at a time, 16 bytes per thread and store, neighbouring threads
+  // on neighbouring vectors (32 contiguous bytes per thread instead, two
+  // half-line stores, took 2.15 ms for 3.2 GB of FP64 plans)
+  constexpr int VN = VecOf<T>::N, H = 4 / VN;
+  for (int c0 = 0; c0 < R; c0 += 1024) {
+    T nb[H][VN];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int r = c0 + (h * 256 + (int)threadIdx.x) * VN;
+      if (r < R) load_vec<T, VN>(nbv + r, nb[h]);  // nbv is padded to whole blocks
+    }
     for (int c = 0; c < n; ++c) {
       const int cn = s_n[c];
       if (cn < 0) continue;
-      T x[4] = {nb[0], nb[1], nb[2], nb[3]};
-      for (int e = 0; e < cn; ++e) {
-        const int d = s_r[c][e] - r0;
-        if (d >= 0 && d < 4) {
-          const T v = s_v[c][e];
+      T* const col = theta + (j0 + c) * ld;
 #pragma unroll
-          for (int k = 0; k < 4; ++k) x[k] = d == k ? v : x[k];
+      for (int h = 0; h < H; ++h) {
+        const int r = c0 + (h * 256 + (int)threadIdx.x) * VN;
+        T x[VN];
+#pragma unroll
+        for (int k = 0; k < VN; ++k) x[k] = nb[h][k];
+        for (int e = 0; e < cn; ++e) {
+          const int d = s_r[c][e] - r;
+          if (d >= 0 && d < VN) {
+            const T v = s_v[c][e];
+#pragma unroll
+            for (int k = 0; k < VN; ++k) x[k] = d == k ? v : x[k];
+          }
         }
-      }
-      T* const dst = theta + (j0 + c) * ld + r0;
-#pragma unroll
-      for (int h = 0; h < 4; h += VN) {
-        if (vec && r0 + h + VN <= R) {
-          T y[VN];
-#pragma unroll
-          for (int k = 0; k < VN; ++k) y[k] = x[h + k];
-          store_vec_nt<T, VN>(dst + h, y);
+        if (vec && r + VN <= R) {
+          store_vec_nt<T, VN>(col + r, x);
         } else {
 #pragma unroll
           for (int k = 0; k < VN; ++k)
-            if (r0 + h + k < R) dst[h + k] = x[h + k];
+            if (r + k < R) col[r + k] = x[k];
         }
       }
     }
