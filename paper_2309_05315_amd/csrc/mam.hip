@@ -128,6 +128,7 @@ struct Group {
 struct Layout {
   size_t partial = 0, diag = 0, seg_p = 0, seg_m = 0, seg_j0 = 0, seg_j1 = 0, seg_poff = 0, seg_idx = 0, seg_st = 0;
   size_t wg_seg = 0, mseg = 0, probdev = 0, probaux = 0, mtasks = 0, atasks = 0;
+  size_t meas_p = 0, meas_m = 0;  // every measure's problem and number
   size_t stop = 0, stop_part = 0;  // stopping-test state and row-block partials
   size_t total = 0;
 };
@@ -221,6 +222,7 @@ struct Plan {
   std::vector<int64_t> seg_j0, seg_j1, seg_poff;
   std::vector<mam::MargTask> mtasks;
   std::vector<mam::AvgTask> atasks;
+  std::vector<int32_t> meas_p, meas_m;
   size_t nseg_cap = 0, partial_cap = 0;
   int nwg_total = 0;
   Layout lay;
@@ -642,8 +644,14 @@ void build_schedule(Plan* pl) {
   pl->mpoff.clear();
   pl->mtasks.clear();
   pl->atasks.clear();
+  pl->meas_p.clear();
+  pl->meas_m.clear();
   for (size_t pi = 0; pi < pl->P.size(); ++pi) {
     const Prob& p = pl->P[pi];
+    for (int64_t m = 0; m < p.M; ++m) {
+      pl->meas_p.push_back((int32_t)pi);
+      pl->meas_m.push_back((int32_t)m);
+    }
     for (int64_t m = 0; m < p.M; ++m)
       for (int64_t r0 = 0; r0 < p.R; r0 += 256)
         pl->mtasks.push_back({(int32_t)pi, (int32_t)m, (int32_t)r0, (int32_t)m});
@@ -798,6 +806,8 @@ void build_layout(Plan* pl) {
   L.probaux = take(pl->P.size() * sizeof(mam::ProbAux));
   L.mtasks = take(pl->mtasks.size() * sizeof(mam::MargTask));
   L.atasks = take(pl->atasks.size() * sizeof(mam::AvgTask));
+  L.meas_p = take(nmeas * 4);
+  L.meas_m = take(nmeas * 4);
   L.stop = take(sizeof(mam::StopState));
   L.stop_part = take((size_t)pl->P[0].nb * 8);
   if (pl->lg.on) {
@@ -1175,6 +1185,10 @@ mam_status upload_tables(Plan* pl, hipStream_t st) {
   TRY(put(L.mseg, pl->mseg.data(), pl->mseg.size() * 4));
   TRY(put(L.mtasks, pl->mtasks.data(), pl->mtasks.size() * sizeof(mam::MargTask)));
   TRY(put(L.atasks, pl->atasks.data(), pl->atasks.size() * sizeof(mam::AvgTask)));
+  if (!pl->lg.on) {
+    TRY(put(L.meas_p, pl->meas_p.data(), pl->meas_p.size() * 4));
+    TRY(put(L.meas_m, pl->meas_m.data(), pl->meas_m.size() * 4));
+  }
   std::vector<mam::ProbAux> aux(pl->P.size());
   for (size_t i = 0; i < pl->P.size(); ++i) {
     Prob& p = pl->P[i];
@@ -1413,11 +1427,11 @@ mam_status sparse_writeback(Plan* pl, hipStream_t st) {
 }
 
 template <typename T>
-mam_status launch_long_rowsum(Plan* pl, hipStream_t st) {
+mam_status launch_long_rowsum(Plan* pl, hipStream_t st, bool given) {
   const LongPlan& lg = pl->lg;
   mam::LongFns<T> fn = mam::pick_long<T>(lg.vpt, lg.vec, pl->P[0].cost_mode == MAM_COST_GRID);
   if (!fn.rowsum) return fail(MAM_EUNSUPPORTED, "no long-column kernels for vpt=%d vec=%d", lg.vpt, lg.vec);
-  hipLaunchKernelGGL(fn.rowsum, dim3(lg.nwg), dim3(256), 0, st, long_args<T>(pl), lg.rows);
+  hipLaunchKernelGGL(given ? fn.rowsum : fn.rowsum_q, dim3(lg.nwg), dim3(256), 0, st, long_args<T>(pl), lg.rows);
   LAUNCH_CHECK("long_rowsum_kernel");
   return MAM_OK;
 }
@@ -1499,12 +1513,20 @@ mam_status launch_init(Plan* pl, const void* const* theta0, hipStream_t st) {
   const Layout& L = pl->lay;
   for (size_t i = 0; i < pl->P.size(); ++i) {
     Prob& p = pl->P[i];
-    const int blocks = (int)std::min<int64_t>(8192, std::max<int64_t>(1, (p.T * p.R + 255) / 256));
     if (theta0 && theta0[i]) {
       TRY(launch_plan_copy<T>(static_cast<T*>(p.theta), static_cast<const T*>(theta0[i]), p, st));
     } else {
-      hipLaunchKernelGGL(mam::fill_kernel<T>, dim3(blocks), dim3(256), 0, st, static_cast<T*>(p.theta), p.ld,
-                         (int)p.R, static_cast<const T*>(p.q), p.T);
+      constexpr int FV = sizeof(T) == 4 ? 4 : 2;
+      const bool vec = p.ld % FV == 0 && reinterpret_cast<uintptr_t>(p.theta) % 16 == 0;
+      const int64_t nv = (p.R + (vec ? FV : 1) - 1) / (vec ? FV : 1);
+      int ll = 0;
+      while (ll < 8 && ((int64_t)1 << ll) < nv) ++ll;
+      const int64_t per = 256 >> ll;
+      const int blocks = (int)std::min<int64_t>(16384, std::max<int64_t>(1, (p.T + per - 1) / per));
+      const int stream = p.ld * p.T * (int64_t)sizeof(T) > ((int64_t)256 << 20);
+      auto fill = vec ? &mam::fill_kernel<T, FV> : &mam::fill_kernel<T, 1>;
+      hipLaunchKernelGGL(fill, dim3(blocks), dim3(256), 0, st, static_cast<T*>(p.theta), p.ld, (int)p.R,
+                         static_cast<const T*>(p.q), p.T, ll, stream);
       LAUNCH_CHECK("fill_kernel");
     }
     hipLaunchKernelGGL(mam::fill_value_kernel, dim3((unsigned)std::min<int64_t>(4096, (p.T + 255) / 256)), dim3(256),
@@ -1512,7 +1534,7 @@ mam_status launch_init(Plan* pl, const void* const* theta0, hipStream_t st) {
     LAUNCH_CHECK("fill_value_kernel");
   }
   if (pl->lg.on) {
-    TRY(launch_long_rowsum<T>(pl, st));
+    TRY(launch_long_rowsum<T>(pl, st, theta0 && theta0[0]));
     return launch_marginals(pl, st, 0);
   }
   // short columns: the fixed-point accumulators start (and stay, between
@@ -1522,6 +1544,15 @@ mam_status launch_init(Plan* pl, const void* const* theta0, hipStream_t st) {
     hipLaunchKernelGGL(mam::fill_value_kernel, dim3((unsigned)std::min<int64_t>(4096, (n + 255) / 256)), dim3(256), 0,
                        st, at<double>(pl, p.o_acc), n, 0.0);
     LAUNCH_CHECK("fill_value_kernel");
+  }
+  bool own = true;  // the library's own start in every problem
+  for (size_t i = 0; i < pl->P.size(); ++i) own = own && !(theta0 && theta0[i]);
+  if (own) {
+    hipLaunchKernelGGL(mam::start_marginal_kernel<T>, dim3((unsigned)pl->meas_p.size()), dim3(256), 0, st,
+                       at<mam::ProbDev<T>>(pl, L.probdev), at<mam::ProbAux>(pl, L.probaux), at<int32_t>(pl, L.meas_p),
+                       at<int32_t>(pl, L.meas_m));
+    LAUNCH_CHECK("start_marginal_kernel");
+    return launch_average(pl, st, 0);
   }
   // vector loads when every problem's plans are 16-byte aligned with a
   // leading dimension that is a multiple of the vector

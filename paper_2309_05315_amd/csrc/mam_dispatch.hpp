@@ -76,6 +76,7 @@ struct LongFns {
   void (*thresh)(LongArgs<T>) = nullptr;
   void (*write)(LongArgs<T>) = nullptr;
   void (*rowsum)(LongArgs<T>, int) = nullptr;
+  void (*rowsum_q)(LongArgs<T>, int) = nullptr;  // of the library's own start, from q
   void (*materialize)(LongArgs<T>) = nullptr;  // sparse store write-back
   void (*scan_sparse)(LongArgs<T>) = nullptr;  // sparse-store scan
   void (*thresh_diag)(LongArgs<T>) = nullptr;  // with the iteration's diagnostics

@@ -830,14 +830,32 @@ long_write_kernel(LongArgs<T> a) {
   }
 }
 
-// Row sums of the plans into the item partials (initialisation).
-template <typename T>
+// Row sums of the plans into the item partials (initialisation).  OWN: the
+// plans are the library's own start, (T)(q_s/R) in every row of column s, so
+// every row of an item has the same sum, taken over its columns in the same
+// order without reading the plans (9.8 GB of them took 8.0 ms).
+template <typename T, bool OWN>
 __global__ void __launch_bounds__(256)
 long_rowsum_kernel(LongArgs<T> a, int rows_per_tile) {
   const int ib = a.wg_it[blockIdx.x], ie = a.wg_it[blockIdx.x + 1];
   for (int it = ib; it < ie; ++it) {
     const int rbase = a.it_rb[it] * rows_per_tile;
     const int rend = rbase + rows_per_tile < a.R ? rbase + rows_per_tile : a.R;
+    if constexpr (OWN) {
+      constexpr int U = 16;
+      const int64_t j0 = a.it_j0[it], j1 = a.it_j1[it];
+      double s = 0.0;
+      for (int64_t j = j0; j < j1; j += U) {
+        double x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = (double)(T)((double)a.q[j + u < j1 ? j + u : j0] / (double)a.R);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (j + u < j1) s += x[u];
+      }
+      for (int r = rbase + threadIdx.x; r < rend; r += 256) a.partial[a.it_poff[it] + (r - rbase)] = s;
+      continue;
+    }
     for (int r = rbase + threadIdx.x; r < rend; r += 256) {
       double s = 0.0;
       for (int64_t j = a.it_j0[it]; j < a.it_j1[it]; ++j) s += (double)a.theta[j * a.ld + r];

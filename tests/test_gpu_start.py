@@ -1,0 +1,43 @@
+"""The library's own start against the same start given (MI355X only): one
+value per column, filled in vectors, and marginals taken from q."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2309_05315_amd import inputs
+from paper_2309_05315_amd import mam
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+@pytest.mark.parametrize("R,S,dtype,sched", [
+    (1, [3, 70], "f64", {}), (7, [5, 4, 130], "f32", {}), (64, [257], "f32", {}), (513, [66, 1], "f64", {}),
+    (1027, [65, 9], "f32", {}), (2051, [37, 64], "f64", dict(rows_per_tile=1024)),
+    (8193, [9, 67], "f32", {}),
+])
+def test_default_start_equals_given_start(R, S, dtype, sched):
+    """init() fills the plans with (T)(q_s/R) and takes their marginals from q;
+    init(theta0) reads them: the same plans, and after an iteration (which
+    reads both) the same plans and barycenter bit for bit."""
+    p = inputs.tiny_problem(51, R=R, S=S, dtype=dtype)
+    say(f"case start R={R} S={S} {dtype} {sched}")
+    s = mam.solver_for(p, **sched)
+    s.init()
+    start = s.theta.clone()
+    q = s.q.cpu().numpy().astype(np.float64)
+    want = (q / R).astype(np.float32 if dtype == "f32" else np.float64)
+    got = start.cpu().numpy()
+    assert np.array_equal(got[:, :R], np.repeat(want[:, None], R, axis=1))
+    m0 = s.marginals().cpu().numpy().copy()
+    s.iterate(1)
+    a = (s.theta[:, :R].cpu().numpy().copy(), s.barycenter().cpu().numpy().copy())
+    s.init(start)
+    np.testing.assert_array_equal(m0, s.marginals().cpu().numpy())
+    s.iterate(1)
+    np.testing.assert_array_equal(a[0], s.theta[:, :R].cpu().numpy())
+    np.testing.assert_array_equal(a[1], s.barycenter().cpu().numpy())
