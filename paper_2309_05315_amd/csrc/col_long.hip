@@ -10,17 +10,21 @@ template <typename T, int VPT, bool GRID>
 LongFns<T> pick_long_vec(int vec) {
   constexpr int VN = VecOf<T>::N;
   if (vec == VN)
-    return {&long_scan_kernel<T, VPT, VN, GRID, false>, &long_threshold_kernel<T, VPT, VN, false>,
+    return {&long_scan_kernel<T, VPT, VN, GRID>, &long_threshold_kernel<T, VPT, VN, false, false>,
             &long_write_kernel<T, VPT, VN, false>, &long_rowsum_kernel<T, false>, &long_rowsum_kernel<T, true>,
             &long_materialize_kernel<T, VPT, VN>,
-            &long_scan_kernel<T, VPT, VN, GRID, true>, &long_threshold_kernel<T, VPT, VN, true>,
-            &long_write_kernel<T, VPT, VN, true>};
+            &long_scan_sparse_kernel<T, VPT, VN, GRID>, &long_threshold_kernel<T, VPT, VN, true, false>,
+            &long_threshold_kernel<T, VPT, VN, false, true>, &long_threshold_kernel<T, VPT, VN, true, true>,
+            &long_write_kernel<T, VPT, VN, true>, &long_cost_min_kernel<T, VPT, VN, GRID>, &long_base_kernel<T, VPT, VN>,
+            &long_limit_kernel<T, VPT, VN>};
   if (vec == 1)
-    return {&long_scan_kernel<T, VPT, 1, GRID, false>, &long_threshold_kernel<T, VPT, 1, false>,
+    return {&long_scan_kernel<T, VPT, 1, GRID>, &long_threshold_kernel<T, VPT, 1, false, false>,
             &long_write_kernel<T, VPT, 1, false>, &long_rowsum_kernel<T, false>, &long_rowsum_kernel<T, true>,
             &long_materialize_kernel<T, VPT, 1>,
-            &long_scan_kernel<T, VPT, 1, GRID, true>, &long_threshold_kernel<T, VPT, 1, true>,
-            &long_write_kernel<T, VPT, 1, true>};
+            &long_scan_sparse_kernel<T, VPT, 1, GRID>, &long_threshold_kernel<T, VPT, 1, true, false>,
+            &long_threshold_kernel<T, VPT, 1, false, true>, &long_threshold_kernel<T, VPT, 1, true, true>,
+            &long_write_kernel<T, VPT, 1, true>, &long_cost_min_kernel<T, VPT, 1, GRID>, &long_base_kernel<T, VPT, 1>,
+            &long_limit_kernel<T, VPT, 1>};
   return {};
 }
 

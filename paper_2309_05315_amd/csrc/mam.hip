@@ -189,6 +189,8 @@ struct LongPlan {
   // (column, sub-tile), the two halves of the common values, the parity
   bool sparse = false;
   size_t o_pcnt = 0, o_prow = 0, o_pval = 0, o_nbv = 0, o_spar = 0;
+  size_t o_cmin = 0, o_limit = 0, o_wit = 0, o_smask = 0, o_gmask = 0;  // what its scan can leave out
+  size_t o_b2v = 0, o_basev = 0, o_bmax = 0, o_wsub = 0, o_wgrp = 0, o_wcol = 0, o_colm = 0;
   // diagnostics: 4 doubles per column (threshold kernel), DIAG_STRIDE per
   // write workgroup
   size_t o_ldiag = 0, o_wdiag = 0;
@@ -833,7 +835,21 @@ void build_layout(Plan* pl) {
       lg.o_prow = take(nh * (size_t)lg.cap * 4);
       lg.o_pval = take(nh * (size_t)lg.cap * eb);
       lg.o_nbv = take(2 * (size_t)pl->P[0].M * (size_t)pl->P[0].R * eb);
-      lg.o_spar = take(4);
+      lg.o_spar = take(12);
+      lg.o_cmin = take((size_t)lg.nrb * 4 * (size_t)pl->P[0].cost_ncols * eb);
+      lg.o_limit = take(T * 8);
+      lg.o_wit = take(T * 4);
+      lg.o_smask = take(T * (size_t)((lg.nrb * 4 + 63) / 64) * 8);
+      const size_t nword = (size_t)lg.nrb * 4 * ((T + 63) / 64);
+      lg.o_gmask = take(nword * 8);
+      lg.o_wsub = take(nword * (64 / mam::kScanCols) * 4);
+      lg.o_wgrp = take(nword * (64 / mam::kScanCols) * 4);
+      lg.o_wcol = take(nword * (64 / mam::kScanCols) * 8);
+      lg.o_colm = take(T * 4);
+      const size_t nslot = (size_t)pl->P[0].M * (size_t)lg.nrb * (size_t)lg.vpt * mam::LNT;
+      lg.o_b2v = take(nslot * 8);
+      lg.o_basev = take(nslot * 8);
+      lg.o_bmax = take((size_t)pl->P[0].M * (size_t)lg.nrb * 4 * 8);
     }
   }
   SparsePlan& sp = pl->sp;
@@ -1369,6 +1385,21 @@ mam::LongArgs<T> long_args(Plan* pl) {
     a.prow = at<int32_t>(pl, lg.o_prow);
     a.pval = at<T>(pl, lg.o_pval);
     a.nbv = at<T>(pl, lg.o_nbv);
+    a.cmin = at<T>(pl, lg.o_cmin);
+    a.ncost = p.cost_ncols;
+    a.limit = at<double>(pl, lg.o_limit);
+    a.wit = at<int32_t>(pl, lg.o_wit);
+    a.smask = at<unsigned long long>(pl, lg.o_smask);
+    a.nmask = (lg.nrb * 4 + 63) / 64;
+    a.gmask = at<unsigned long long>(pl, lg.o_gmask);
+    a.ngrp = (int32_t)((p.T + 63) / 64);
+    a.b2v = at<double>(pl, lg.o_b2v);
+    a.basev = at<double>(pl, lg.o_basev);
+    a.bmax = at<double>(pl, lg.o_bmax);
+    a.wsub = at<int32_t>(pl, lg.o_wsub);
+    a.wgrp = at<int32_t>(pl, lg.o_wgrp);
+    a.wcol = at<unsigned long long>(pl, lg.o_wcol);
+    a.colm = at<int32_t>(pl, lg.o_colm);
   }
   return a;
 }
@@ -1383,10 +1414,19 @@ mam_status launch_long_columns(Plan* pl, hipStream_t st, int diag) {
   mam::LongArgs<T> a = long_args<T>(pl);
   hipLaunchKernelGGL(mam::damping_kernel, dim3(1), dim3(256), 0, st, a.d2part, p.nb, p.rho, p.gamma, a.t, a.stop);
   LAUNCH_CHECK("damping_kernel");
-  if (lg.sparse) hipLaunchKernelGGL(fn.scan_sparse, dim3(lg.nwg), dim3(mam::LNT), (size_t)lg.vpt * mam::LNT * 8, st, a);
-  else hipLaunchKernelGGL(fn.scan, dim3(lg.nwg), dim3(mam::LNT), 0, st, a);
+  if (lg.sparse) {
+    hipLaunchKernelGGL(fn.base, dim3(lg.nrb, (unsigned)p.M), dim3(mam::LNT), 0, st, a);
+    LAUNCH_CHECK("long_base_kernel");
+    hipLaunchKernelGGL(fn.limit, dim3((unsigned)((p.T + 63) / 64)), dim3(64 * mam::kLimitWaves), 0, st, a);
+    LAUNCH_CHECK("long_limit_kernel");
+    hipLaunchKernelGGL(fn.scan_sparse, dim3(768), dim3(mam::LNT), 0, st, a);
+    LAUNCH_CHECK("long_scan_sparse_kernel");
+  }
+  // (with the sparse store it scans the first iteration of a call only)
+  hipLaunchKernelGGL(fn.scan, dim3(lg.nwg), dim3(mam::LNT), 0, st, a);
   LAUNCH_CHECK("long_scan_kernel");
-  hipLaunchKernelGGL(diag ? fn.thresh_diag : fn.thresh, dim3((unsigned)((p.T + 3) / 4)), dim3(256), 0, st, a);
+  auto thresh = lg.sparse ? (diag ? fn.thresh_sparse_diag : fn.thresh_sparse) : (diag ? fn.thresh_diag : fn.thresh);
+  hipLaunchKernelGGL(thresh, dim3((unsigned)((p.T + 3) / 4)), dim3(256), 0, st, a);
   LAUNCH_CHECK("long_threshold_kernel");
   hipLaunchKernelGGL(diag ? fn.write_diag : fn.write, dim3(lg.nwg), dim3(mam::LNT), (size_t)lg.vpt * mam::LNT * 8, st,
                      a);
@@ -1409,6 +1449,34 @@ mam_status long_sparse_reset(Plan* pl, hipStream_t st) {
                      at<int32_t>(pl, lg.o_spar));
   LAUNCH_CHECK("long_sparse_reset_kernel");
   return MAM_OK;
+}
+
+// Start of a call with the sparse store: the cost's sub-tile minima (the cost
+// may have been rebuilt in place since the last call).  The first iteration
+// of a call scans everything (its plans are dense), so a call of one needs
+// none.
+template <typename T>
+mam_status long_begin_t(Plan* pl, hipStream_t st) {
+  const LongPlan& lg = pl->lg;
+  mam::LongFns<T> fn = mam::pick_long<T>(lg.vpt, lg.vec, pl->P[0].cost_mode == MAM_COST_GRID);
+  if (!fn.cost_min) return fail(MAM_EUNSUPPORTED, "no long-column kernels for vpt=%d vec=%d", lg.vpt, lg.vec);
+  const int64_t nc = pl->P[0].cost_ncols;
+  mam::LongArgs<T> a = long_args<T>(pl);
+  for (int64_t c0 = 0; c0 < nc; c0 += (int64_t)65535 * 16) {
+    // cost columns past c0: the grid's second dimension holds 65535 of 16
+    mam::LongArgs<T> b = a;
+    b.ncost = nc;
+    const int64_t n = std::min<int64_t>(nc - c0, (int64_t)65535 * 16);
+    b.c_first = c0;
+    hipLaunchKernelGGL(fn.cost_min, dim3((unsigned)lg.nrb, (unsigned)((n + 15) / 16)), dim3(mam::LNT), 0, st, b);
+    LAUNCH_CHECK("long_cost_min_kernel");
+  }
+  return MAM_OK;
+}
+
+mam_status long_begin(Plan* pl, int64_t iters, hipStream_t st) {
+  if (!pl->lg.on || !pl->lg.sparse || iters < 2) return MAM_OK;
+  return pl->dtype == MAM_F32 ? long_begin_t<float>(pl, st) : long_begin_t<double>(pl, st);
 }
 
 template <typename T>
@@ -1952,6 +2020,7 @@ mam_status plan_iterate(Plan* pl, int64_t iters, hipStream_t st) {
     TRY(run_iterations(pl, first ? 1 : 0, plain, true, st));
     TRY(sparse_end(pl, st));
   } else {
+    TRY(long_begin(pl, iters, st));
     TRY(run_iterations(pl, 0, plain, false, st));
   }
   if (diag) {
@@ -2065,9 +2134,8 @@ mam_status until_run(Plan* pl, int64_t max_iters, int test, double tol, int64_t 
     mode = kUntilPeriod;
   }
   bool start = false;
-  if (mode == kUntilSparse) {
-    TRY(sparse_begin(pl, &start, st));
-  }
+  if (mode == kUntilSparse) TRY(sparse_begin(pl, &start, st));
+  TRY(long_begin(pl, max_iters, st));
   if (graph && periods > (start ? 1 : 0) &&
       (!pl->uexec || pl->utest != test || pl->uevery != every || pl->umode != mode))
     TRY(capture_until(pl, test, every, mode));

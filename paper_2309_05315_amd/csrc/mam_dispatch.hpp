@@ -80,7 +80,12 @@ struct LongFns {
   void (*materialize)(LongArgs<T>) = nullptr;  // sparse store write-back
   void (*scan_sparse)(LongArgs<T>) = nullptr;  // sparse-store scan
   void (*thresh_diag)(LongArgs<T>) = nullptr;  // with the iteration's diagnostics
+  void (*thresh_sparse)(LongArgs<T>) = nullptr;
+  void (*thresh_sparse_diag)(LongArgs<T>) = nullptr;
   void (*write_diag)(LongArgs<T>) = nullptr;
+  void (*cost_min)(LongArgs<T>) = nullptr;     // sparse store: least cost of every sub-tile
+  void (*base)(LongArgs<T>) = nullptr;         // sparse store: 2b and common value + 2b of every row
+  void (*limit)(LongArgs<T>) = nullptr;        // sparse store: lower bounds of the thresholds
 };
 template <typename T>
 LongFns<T> pick_long(int vpt, int vec, bool grid);

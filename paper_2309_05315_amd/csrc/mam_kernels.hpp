@@ -237,6 +237,14 @@ __device__ __forceinline__ double damping_t(const double* d2part, int nb, double
   return (__builtin_isinf(gam) || rho * sqrt(d2) <= gam) ? 1.0 : gam / (rho * sqrt(d2));
 }
 
+// Orders one wave's LDS writes before its later LDS reads (the hardware
+// keeps a wave's LDS operations in order; this keeps the compiler to it).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
 // The nearest float to x and its neighbours: float_up(x) >= x and
 // float_down(x) <= x (the float conversion rounds to nearest; one step in the
 // last place fixes the side), NaN for NaN.  The bounds of the threshold

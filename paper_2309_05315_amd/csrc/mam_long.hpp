@@ -30,6 +30,24 @@
 // more than E candidates is recomputed from theta and c where it is needed
 // (threshold rounds, and the write pass before theta is overwritten).  Every
 // sum has a fixed order: results are bitwise reproducible.
+//
+// With the sparse store an iteration of a call after its first has three more
+// kernels' worth of choices to make, so that work follows the active entries
+// and not T x R:
+//
+//   base       per (measure, row): 2b and the common value + 2b
+//   limit      per column: a lower bound of its threshold from its last active
+//              entries, and from it the sub-tiles that can hold an active one
+//              (their bound: least cost, largest common value + 2b)
+//   scan       the (column, sub-tile) pairs left, from a work list; candidates
+//              above the bound only
+//
+// Ten 40 x 40 images (R = 152,881, 16,000 columns, FP32), per iteration:
+// scanning every sub-tile 2.9 ms scan, 0.24 ms threshold, 0.28 ms write; now
+// 13 us base, 41 us limit, 90 us scan, 34 us threshold, 45 us write.  About
+// three of a column's 152 sub-tiles are scanned, two of them for their
+// patches.  20 iterations of a call: 63 -> 14.5 ms, of which 7.8 ms are the
+// start's fill, the first scan and the write-back: 9.8 GB each.
 #pragma once
 
 #include <utility>
@@ -88,7 +106,8 @@ struct LongArgs {
   // slots h*cap + e with h = j*nsub + s, over the value nbv[par][m][r] that
   // every other entry of measure m's row r holds
   int32_t sparse, pad1;
-  int32_t* spar;                 // par: which half of nbv holds the stored plans
+  int32_t* spar;                 // [0] par: which half of nbv holds the stored plans; [1] all of them dense;
+                                 // [2] entries of the work list
   int32_t* pcnt;
   int32_t* prow;                 // h*cap + e: row of patch e
   T* pval;                       //            its value
@@ -100,7 +119,34 @@ struct LongArgs {
   // store only)
   double* ldiag;
   double* wdiag;
+  // sparse store: what the scan can leave out (see long_limit_kernel)
+  T* cmin;                       // nsub x ncost: least cost of each sub-tile, per cost column
+  int64_t ncost, c_first;        // cost columns; the first one of a cost_min launch
+  double* limit;                 // T: a lower bound of the column's threshold (-inf: none)
+  int32_t* wit;                  // T: a row of the column's largest w, or -1
+  unsigned long long* smask;     // T x nmask words: the sub-tiles the scan looked at (the others have no header)
+  unsigned long long* gmask;     // nsub x ngrp words: the same by sub-tile, for groups of 64 columns
+  int32_t nmask, ngrp;
+  // per (measure m, tile rb, slot k, thread tid) at ((m*nrb + rb)*VPT + k)*256
+  // + tid: 2 b of the slot's row and the common value + 2 b (-inf past R);
+  // and per (m, sub-tile) the largest of the latter
+  double* b2v;
+  double* basev;
+  double* bmax;                  // M x nsub
+  // work list of the sparse-store scan, spar[2] entries: sub-tile, group of 64
+  // columns, and which of them
+  int32_t* wsub;
+  int32_t* wgrp;
+  unsigned long long* wcol;
+  int32_t* colm;                 // T: measure of the column
 };
+
+// Columns of an entry of the sparse-store scan's work list (a group of 64 is
+// up to eight of them).
+constexpr int kScanCols = 8;
+
+// Waves of a workgroup of long_limit_kernel.
+constexpr int kLimitWaves = 16;
 
 // Coordinate k of grid index i: origin + i * spacing, each operation rounded
 // (no fused multiply-add).
@@ -213,36 +259,63 @@ __device__ void stored_rows(const LongArgs<T>& a, int64_t j, int si, int rbase, 
   }
 }
 
+// The candidates of one sub-tile's column: entries w > thr of the wave's
+// lanes into the slots at h*cap, in slot-major order inside the wave (position
+// = candidates of earlier slots + earlier lanes of this slot; rows past R have
+// w = -inf and are never candidates).  Returns their number.  With none (q_s
+// below the rounding of w, or the bound), slot 0 names a row of the maximum,
+// for long_limit_kernel.
+template <typename T, int VPT, typename Row>
+__device__ __forceinline__ int keep_candidates(const LongArgs<T>& a, int64_t h, const double (&w)[VPT],
+                                               Row&& row, double mx, double thr, bool any) {
+  int32_t* const crow = gptr(a.crow) + h * a.cap;
+  double* const cw = gptr(a.cw) + h * a.cap;
+  int n = 0;
+  if (any) {
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) {
+      const bool sel = w[k] > thr;
+      const unsigned long long bal = __ballot(sel);
+      if (sel) {
+        const int pos = n + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+        if (pos < a.cap) {
+          crow[pos] = row(k);
+          cw[pos] = w[k];
+        }
+      }
+      n += __popcll(bal);
+    }
+    if (n == 0) {
+#pragma unroll
+      for (int k = 0; k < VPT; ++k)
+        if (w[k] == mx) crow[0] = row(k);
+    }
+  }
+  return n;
+}
+
 // ---- scan: w, sub-tile maxima, candidates -------------------------------
-// GRID: the cost is formed from the row's grid point and the column's point
-// instead of being read (only theta is streamed).  SP: the sparse-store
-// instance; an unpatched entry of a sparse sub-tile has theta = the common
-// value, so theta + 2b is a per-row constant of the item ('base', in
-// registers) and w costs one fused multiply-add; 2b itself sits in LDS for
-// dense sub-tiles and patched rows (dynamic LDS: VPT*256 doubles, each
-// thread reading only its own slots).
-template <typename T, int VPT, int VEC, bool GRID, bool SP>
+// The dense plans: every iteration of the dense store, the first one of a
+// call with the sparse store (spar[1]).  GRID: the cost is formed from the
+// row's grid point and the column's point instead of being read (only theta
+// is streamed).
+template <typename T, int VPT, int VEC, bool GRID>
 __global__ void __launch_bounds__(LNT)
 long_scan_kernel(LongArgs<T> a) {
   constexpr int NCH = VPT / VEC, RB = LNT * VPT;
   // columns in flight per wave: two where the registers allow it at two
-  // waves per SIMD (FP32 tiles of 16 values in vectors), else one (and one
-  // in the sparse-store instance, whose columns mostly load no theta)
-  constexpr int PF = (!SP && sizeof(T) == 4 && VPT == 16 && VEC > 1) ? 2 : 1;
+  // waves per SIMD (FP32 tiles of 16 values in vectors), else one
+  constexpr int PF = (sizeof(T) == 4 && VPT == 16 && VEC > 1) ? 2 : 1;
   static_assert(VPT % VEC == 0 && VPT <= 16, "tile shape");
   if (a.stop != nullptr && uniform_i(*gptr(a.stop)) != 0) return;
+  if (a.sparse && uniform_i(gptr(a.spar)[1]) == 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = uniform_i(tid >> 6);
-  const int R = a.R, cap = a.cap, nsub = a.nrb * 4;
+  const int R = a.R, nsub = a.nrb * 4;
   const double t = uniform_d(*gptr(a.t)), inv_rho = a.inv_rho;
   const T* const theta = gptr(a.theta);
   const T* const qv = gptr(a.q);
-  int32_t* const crow = gptr(a.crow);
-  double* const cw = gptr(a.cw);
-  constexpr bool sparse = SP;
-  const int par = sparse ? uniform_i(*gptr(a.spar)) : 0;
-  extern __shared__ double lds_dyn[];
-  double* const lds_b2 = lds_dyn;  // SP: [VPT][LNT]
   const int ib = uniform_i(a.wg_it[blockIdx.x]), ie = uniform_i(a.wg_it[blockIdx.x + 1]);
   for (int it = ib; it < ie; ++it) {
     const int rb = uniform_i(a.it_rb[it]), m = uniform_i(a.it_m[it]);
@@ -255,20 +328,12 @@ long_scan_kernel(LongArgs<T> a) {
     int row[VPT];
     // 2 b_r, or -inf for rows past R: their w is then -inf (theta and c are
     // finite), below every threshold, without a select per entry
-    double b2[SP ? 1 : VPT];
-    double base[SP ? VPT : 1];  // SP: common value + 2b of the row
+    double b2[VPT];
     double gx0[GRID ? VPT : 1], gx1[GRID ? VPT : 1];  // grid coordinates of the rows
-    const T* __restrict__ nbm = sparse ? gptr(a.nbv) + ((size_t)par * a.M + m) * R : nullptr;
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
       row[k] = rbase + ((k / VEC) * LNT + tid) * VEC + (k % VEC);
-      const double b2k = row[k] < R ? 2.0 * long_b(t, pv, pmm, row[k], Sm) : -__builtin_huge_val();
-      if constexpr (SP) {
-        lds_b2[k * LNT + tid] = b2k;
-        base[k] = (double)(row[k] < R ? nbm[row[k]] : T(0)) + b2k;
-      } else {
-        b2[k] = b2k;
-      }
+      b2[k] = row[k] < R ? 2.0 * long_b(t, pv, pmm, row[k], Sm) : -__builtin_huge_val();
       if constexpr (GRID) {
         const int i0 = row[k] / a.gn1;
         gx0[k] = grid_coord(a, 0, i0);
@@ -276,38 +341,21 @@ long_scan_kernel(LongArgs<T> a) {
       }
     }
     // raw theta and c (or the column's point) of the next PF columns in
-    // flight while one is scanned: PF buffers, used in turn; with the sparse
-    // store, the column's patch count and lane e's patch instead of theta
-    // when the sub-tile is not dense
+    // flight while one is scanned: PF buffers, used in turn
     T rt[PF][VPT], rc[PF][GRID ? 1 : VPT], rq[PF];
     double rz[PF][2];
-    int pcs[PF], prs[PF];
-    T pvs[PF];
-    // columns run in blocks: the whole item, or 64 columns with the sparse
-    // store (lane l then holds the patch count of column jlo + l)
-    int64_t jlo = j0, jhi = j1;
-    int pcl = -1;
     auto issue = [&](auto S, int64_t j) {
       constexpr int s = decltype(S)::value;
       const T* __restrict__ thp = theta + j * a.ld;
       rq[s] = qv[j];
       if constexpr (GRID) grid_point(a, j, off_m, &rz[s][0], &rz[s][1]);
-      const int pc = sparse ? __builtin_amdgcn_readlane(pcl, (int)(j - jlo)) : -1;
-      pcs[s] = pc;
-      if (pc >= 0) {
-        const int64_t h = j * nsub + rb * 4 + wv;
-        prs[s] = lane < pc ? gptr(a.prow)[h * cap + lane] : 0;
-        pvs[s] = lane < pc ? gptr(a.pval)[h * cap + lane] : T(0);
-      }
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
         const int r0 = row[c * VEC] < R ? row[c * VEC] : rbase;  // rows past R read the tile's first (masked)
-        if (pc < 0) {
-          T tv[VEC];
-          load_vec_nt<T, VEC>(thp + r0, tv);
+        T tv[VEC];
+        load_vec_nt<T, VEC>(thp + r0, tv);
 #pragma unroll
-          for (int v = 0; v < VEC; ++v) rt[s][c * VEC + v] = tv[v];
-        }
+        for (int v = 0; v < VEC; ++v) rt[s][c * VEC + v] = tv[v];
         if constexpr (!GRID) {
           T cv[VEC];
           load_vec<T, VEC>(long_cost_col(a, j, off_m) + r0, cv);
@@ -324,76 +372,19 @@ long_scan_kernel(LongArgs<T> a) {
       double w[VPT];
       double mx = -__builtin_huge_val();
       const double z0 = uniform_d(rz[s][0]), z1 = uniform_d(rz[s][1]);
-      auto cost_k = [&](int k) -> double {
-        if constexpr (GRID) return grid_cost_xy<T>(gx0[k], gx1[k], z0, z1);
-        else return (double)rc[s][k];
-      };
-      if constexpr (SP) {
-        // theta + 2b of every entry: base for a sparse sub-tile, the dense
-        // rows plus 2b from LDS otherwise; w is one fused multiply-add each
-        const bool sp = pcs[s] >= 0;
-        double bs[VPT];
-        if (sp) {
 #pragma unroll
-          for (int k = 0; k < VPT; ++k) bs[k] = base[k];
-        } else {
-#pragma unroll
-          for (int k = 0; k < VPT; ++k) bs[k] = (double)rt[s][k] + lds_b2[k * LNT + tid];
-        }
-#pragma unroll
-        for (int k = 0; k < VPT; ++k) {
-          w[k] = __builtin_fma(-cost_k(k), inv_rho, bs[k]);
-          mx = fmax(mx, w[k]);
-        }
-        if (sp) {
-          // the patched rows (each patch raises its entry, so the maximum
-          // only grows)
-          for (int e = 0; e < pcs[s]; ++e) {
-            const int rr = __builtin_amdgcn_readlane(prs[s], e) - rbase;
-            const T v = read_lane(pvs[s], e);
-            if (slot_owner(rr, VEC) == tid) {
-              const int kp = slot_of(rr, VEC), r = rbase + rr;
-              const double c = GRID ? grid_cost(a, r, z0, z1) : (double)long_cost_col(a, j, off_m)[r];
-              const double wn = long_w((double)v, lds_b2[kp * LNT + tid], c, inv_rho);
-#pragma unroll
-              for (int kk = 0; kk < VPT; ++kk)
-                if (kk == kp) w[kk] = wn;
-              mx = fmax(mx, wn);
-            }
-          }
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < VPT; ++k) {
-          w[k] = long_w((double)rt[s][k], b2[k], cost_k(k), inv_rho);
-          mx = fmax(mx, w[k]);
-        }
+      for (int k = 0; k < VPT; ++k) {
+        double c;
+        if constexpr (GRID) c = grid_cost_xy<T>(gx0[k], gx1[k], z0, z1);
+        else c = (double)rc[s][k];
+        w[k] = long_w((double)rt[s][k], b2[k], c, inv_rho);
+        mx = fmax(mx, w[k]);
       }
       const double tau = uniform_d((double)rq[s]);
-      if constexpr (decltype(NEXT)::value) issue(S, j + PF < jhi ? j + PF : jhi - 1);
+      if constexpr (decltype(NEXT)::value) issue(S, j + PF < j1 ? j + PF : j1 - 1);
       mx = wave_max(mx);
-      const double thr = mx - tau;
-      // slots in slot-major order inside the wave: position = candidates of
-      // earlier slots + earlier lanes of this slot (rows past R have w = -inf
-      // and are never candidates)
       const int64_t h = j * nsub + rb * 4 + wv;
-      int n = 0;
-      if (tau > 0.0) {
-#pragma unroll
-        for (int k = 0; k < VPT; ++k) {
-          const bool sel = w[k] > thr;
-          const unsigned long long bal = __ballot(sel);
-          if (sel) {
-            const int pos = n + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
-                                                              __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-            if (pos < cap) {
-              crow[h * cap + pos] = row[k];
-              cw[h * cap + pos] = w[k];
-            }
-          }
-          n += __popcll(bal);
-        }
-      }
+      const int n = keep_candidates<T, VPT>(a, h, w, [&](int k) { return row[k]; }, mx, mx - tau, tau > 0.0);
       if (lane == 0) {
         gptr(a.hmax)[h] = mx;
         gptr(a.hcnt)[h] = n;
@@ -401,30 +392,175 @@ long_scan_kernel(LongArgs<T> a) {
     };
     using YES = std::true_type;
     using NO = std::false_type;
-    const int64_t jstep = sparse ? 64 : j1 - j0;
-    for (jlo = j0; jlo < j1; jlo += jstep) {
-      jhi = jlo + jstep < j1 ? jlo + jstep : j1;
-      if (sparse) pcl = jlo + lane < jhi ? gptr(a.pcnt)[(int64_t)(rb * 4 + wv) * a.T_cols + jlo + lane] : -1;
-      // buffer i holds column j + i (clamped to the block's last column)
-      static_for<PF>([&](auto I) { issue(I, jlo + I < jhi ? jlo + I : jhi - 1); });
-      int64_t j = jlo;
-      for (; j + PF - 1 < jhi; j += PF) static_for<PF>([&](auto I) { column(I, YES{}, j + I); });
-      static_for<PF - 1>([&](auto I) {
-        if (j + I < jhi) column(I, NO{}, j + I);
-      });
+    // buffer i holds column j + i (clamped to the item's last column)
+    static_for<PF>([&](auto I) { issue(I, j0 + I < j1 ? j0 + I : j1 - 1); });
+    int64_t j = j0;
+    for (; j + PF - 1 < j1; j += PF) static_for<PF>([&](auto I) { column(I, YES{}, j + I); });
+    static_for<PF - 1>([&](auto I) {
+      if (j + I < j1) column(I, NO{}, j + I);
+    });
+  }
+}
+
+// The sparse plans: the columns of the work list (long_limit_kernel), an
+// entry being up to kScanCols columns of one sub-tile and group of 64 that
+// long_limit_kernel did not rule out.  An unpatched entry of a sparse
+// sub-tile has theta = the common value, so theta + 2b is a per-row constant
+// ('base', formed once per iteration) and w costs one fused multiply-add.
+// Waves take the entries in turn: the columns left gather in the few
+// sub-tiles that carry the barycenter, and with fixed shares of the columns
+// the waves of those took 0.32 ms of an iteration on 40 x 40 images.  Which
+// wave scans a column changes nothing: its header and slots are its own.
+template <typename T, int VPT, int VEC, bool GRID>
+__global__ void __launch_bounds__(LNT, 3)
+long_scan_sparse_kernel(LongArgs<T> a) {
+  constexpr int RB = LNT * VPT;
+  if (a.stop != nullptr && uniform_i(*gptr(a.stop)) != 0) return;
+  const int lane = threadIdx.x & 63;
+  const int R = a.R, cap = a.cap, nsub = a.nrb * 4;
+  const double inv_rho = a.inv_rho;
+  const int count = uniform_i(gptr(a.spar)[2]), step = (int)gridDim.x * 4;
+  for (int i = (int)blockIdx.x * 4 + uniform_i((int)(threadIdx.x >> 6)); i < count; i += step) {
+    const int si = uniform_i(gptr(a.wsub)[i]);
+    const int64_t jlo = (int64_t)uniform_i(gptr(a.wgrp)[i]) * 64;
+    unsigned long long todo = (unsigned long long)uniform_l((int64_t)gptr(a.wcol)[i]);
+    const int rb = si >> 2, tid = (si & 3) * 64 + lane, rbase = rb * RB;
+    // lane l: measure, patch count, weight, bound and point of column jlo + l
+    const int64_t jl = jlo + lane < a.T_cols ? jlo + lane : a.T_cols - 1;
+    const int ml = gptr(a.colm)[jl], pcl = gptr(a.pcnt)[(int64_t)si * a.T_cols + jl];
+    const double tl = (double)gptr(a.q)[jl], ll = gptr(a.limit)[jl];
+    const int64_t offl = gptr(a.col_off)[ml];
+    double zl0 = 0.0, zl1 = 0.0;
+    if constexpr (GRID) grid_point(a, jl, offl, &zl0, &zl1);
+    int m = -1;
+    constexpr int NCH = VPT / VEC;
+    double base[VPT];
+    size_t o = 0;
+    auto row = [&](int k) { return rbase + ((k / VEC) * LNT + tid) * VEC + (k % VEC); };
+    // grid indices of each vector's first row (all rows' coordinates would be
+    // 64 registers, and with them one wave per SIMD)
+    int gi0[GRID ? NCH : 1], gi1[GRID ? NCH : 1];
+    if constexpr (GRID) {
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        gi0[c] = row(c * VEC) / a.gn1;
+        gi1[c] = row(c * VEC) - gi0[c] * a.gn1;
+      }
+    }
+    // one column ahead: its costs and, in lane e, row and parts of w of patch e
+    T rc[GRID ? 1 : VPT], pvv = T(0), pcv = T(0);
+    int pr = 0;
+    double pb2 = 0.0;
+    auto issue = [&](int l) {
+      const int64_t j = jlo + l, h = j * nsub + si;
+      const int np = __builtin_amdgcn_readlane(pcl, l);
+      if (lane < np) {
+        pr = gptr(a.prow)[h * cap + lane];
+        pvv = gptr(a.pval)[h * cap + lane];
+        const size_t om = ((size_t)__builtin_amdgcn_readlane(ml, l) * a.nrb + rb) * VPT * LNT;
+        pb2 = gptr(a.b2v)[om + slot_of(pr - rbase, VEC) * LNT + slot_owner(pr - rbase, VEC)];
+        if constexpr (!GRID) pcv = long_cost_col(a, j, gptr(a.col_off)[__builtin_amdgcn_readlane(ml, l)])[pr];
+      }
+      if constexpr (!GRID) {
+        const T* const cp = long_cost_col(a, j, uniform_l(gptr(a.col_off)[__builtin_amdgcn_readlane(ml, l)]));
+#pragma unroll
+        for (int c = 0; c < VPT / VEC; ++c) {
+          T cv[VEC];
+          load_vec<T, VEC>(cp + (row(c * VEC) < R ? row(c * VEC) : rbase), cv);
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) rc[c * VEC + v] = cv[v];
+        }
+      }
+    };
+    issue(__builtin_ctzll(todo));
+    while (todo != 0ull) {
+      const int l = __builtin_ctzll(todo);
+      const int64_t j = jlo + l;
+      todo &= todo - 1ull;
+      if (__builtin_amdgcn_readlane(ml, l) != m) {
+        m = __builtin_amdgcn_readlane(ml, l);
+        o = ((size_t)m * a.nrb + rb) * VPT * LNT + tid;
+#pragma unroll
+        for (int k = 0; k < VPT; ++k) base[k] = gptr(a.basev)[o + k * LNT];
+      }
+      const double z0 = read_lane(zl0, l), z1 = read_lane(zl1, l), tau = read_lane(tl, l), lim = read_lane(ll, l);
+      const int np = __builtin_amdgcn_readlane(pcl, l), prs = pr;
+      const double pw = lane < np ? long_w((double)pvv, pb2, GRID ? grid_cost(a, pr, z0, z1) : (double)pcv, inv_rho) : 0.0;
+      double w[VPT], mx = -__builtin_huge_val();
+      // f(k, c) for every slot's cost
+      auto costs = [&](auto&& f) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+          int i0 = GRID ? gi0[c] : 0, i1 = GRID ? gi1[c] : 0;
+          // (keeps the compiler from holding every row's coordinates over the
+          // columns after all)
+          if constexpr (GRID) asm volatile("" : "+v"(i0), "+v"(i1));
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) {
+            if constexpr (GRID) {
+              f(c * VEC + v, grid_cost_xy<T>(grid_coord(a, 0, i0), grid_coord(a, 1, i1), z0, z1));
+              const bool wrap = ++i1 == a.gn1;
+              i0 += wrap ? 1 : 0;
+              i1 = wrap ? 0 : i1;
+            } else {
+              f(c * VEC + v, (double)rc[c * VEC + v]);
+            }
+          }
+        }
+      };
+      if (np >= 0) {
+        costs([&](int kk, double c) { w[kk] = __builtin_fma(-c, inv_rho, base[kk]); });
+        // the patched rows
+        for (int e = 0; e < np; ++e) {
+          const int rr = __builtin_amdgcn_readlane(prs, e) - rbase;
+          const double v = read_lane(pw, e);
+          const int kp = slot_owner(rr, VEC) == tid ? slot_of(rr, VEC) : -1;
+#pragma unroll
+          for (int kk = 0; kk < VPT; ++kk) w[kk] = kk == kp ? v : w[kk];
+        }
+      } else {
+        const T* const thp = gptr(a.theta) + j * a.ld;
+        costs([&](int kk, double c) {
+          w[kk] = long_w((double)thp[row(kk) < R ? row(kk) : rbase], gptr(a.b2v)[o + kk * LNT], c, inv_rho);
+        });
+      }
+#pragma unroll
+      for (int kk = 0; kk < VPT; ++kk) mx = fmax(mx, w[kk]);
+      const int64_t h = j * nsub + si;
+      if (todo != 0ull) issue(__builtin_ctzll(todo));
+      mx = wave_max(mx);
+      // (an entry at or below the column's bound is inactive too)
+      const int n = keep_candidates<T, VPT>(a, h, w, row, mx, fmax(mx - tau, lim), tau > 0.0);
+      if (lane == 0) {
+        gptr(a.hmax)[h] = mx;
+        gptr(a.hcnt)[h] = n;
+      }
     }
   }
+}
+
+// x of the lanes in bal, the i-th of them moved to lane (first + i) mod 64.
+__device__ __forceinline__ double rank_lane(unsigned long long bal, int first, double x) {
+  const int lane = threadIdx.x & 63;
+  const int up = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+  const int to = ((bal >> lane) & 1ull) ? first + up : first + __popcll(bal) + lane - up;  // a permutation
+  const int lo = __builtin_amdgcn_ds_permute((to & 63) * 4, __double2loint(x));
+  const int hi = __builtin_amdgcn_ds_permute((to & 63) * 4, __double2hiint(x));
+  return __hiloint2double(hi, lo);
 }
 
 // ---- threshold: one wave per column -------------------------------------
 // Only sub-tiles with w_loc > w_max - q_s are visited, in index order; inside
 // one, lane e takes kept entry e, or (more than E candidates) lane l
-// recomputes the VPT values of thread 64*wave + l of the tile.  The wave
-// sums in a fixed tree: the order is fixed.
-template <typename T, int VPT, int VEC, bool DIAG>
+// recomputes the VPT values of thread 64*wave + l of the tile.  The entries
+// above the threshold are dealt to the lanes by their rank in the column and
+// summed in a fixed tree: the sum depends on which entries are active and not
+// on which others were kept.
+template <typename T, int VPT, int VEC, bool DIAG, bool SP>
 __global__ void __launch_bounds__(256)
 long_threshold_kernel(LongArgs<T> a) {
-  constexpr int RB = LNT * VPT;
+  constexpr int RB = LNT * VPT, LW = 256;
+  __shared__ double s_list[4][LW];
   if (a.stop != nullptr && uniform_i(*gptr(a.stop)) != 0) return;
   const int lane = threadIdx.x & 63;
   const int64_t j = (int64_t)blockIdx.x * 4 + uniform_i(threadIdx.x >> 6);
@@ -446,9 +582,15 @@ long_threshold_kernel(LongArgs<T> a) {
   const int32_t* __restrict__ hc = gptr(a.hcnt) + j * nsub;
   const double* __restrict__ cwj = gptr(a.cw) + j * nsub * (int64_t)cap;
   double wmx = -__builtin_huge_val();
-  for (int s = lane; s < nsub; s += 64) wmx = fmax(wmx, hm[s]);
+  // sparse store: only the sub-tiles that the scan looked at have a header
+  const unsigned long long* const smk = SP ? gptr(a.smask) + j * a.nmask : nullptr;
+  auto looked = [&](int s) -> bool { return s < nsub && (smk == nullptr || ((smk[s >> 6] >> (s & 63)) & 1ull)); };
+  for (int s = lane; s < nsub; s += 64)
+    if (looked(s)) wmx = fmax(wmx, hm[s]);
   wmx = wave_max(wmx);
-  const double lo = wmx - tau;  // the root is >= w_max - tau
+  // the root is >= w_max - tau, and >= the column's bound, below which the
+  // sparse-store scan keeps no entry
+  const double lo = SP ? fmax(wmx - tau, uniform_d(gptr(a.limit)[j])) : wmx - tau;
   // an overflowed sub-tile is recomputed from theta and c: the column's
   // measure and b
   int m = 0;
@@ -458,7 +600,7 @@ long_threshold_kernel(LongArgs<T> a) {
   const int64_t off_m = gptr(a.col_off)[m];
   const double* __restrict__ pmm = gptr(a.pm) + (size_t)m * R;
   const double* __restrict__ pv = gptr(a.p);
-  const int par = a.sparse ? uniform_i(*gptr(a.spar)) : 0;
+  const int par = SP ? uniform_i(*gptr(a.spar)) : 0;
   const T* __restrict__ cp = long_cost_col(a, j, off_m);
   double z0 = 0.0, z1 = 0.0;
   if (a.gdim) grid_point(a, j, off_m, &z0, &z1);
@@ -466,13 +608,15 @@ long_threshold_kernel(LongArgs<T> a) {
   auto visit = [&](auto&& f) {
     for (int s0 = 0; s0 < nsub; s0 += 64) {
       const int s = s0 + lane;
-      unsigned long long rel = __ballot(s < nsub && hm[s < nsub ? s : 0] > lo);
+      unsigned long long rel = __ballot(looked(s) && hm[s < nsub ? s : 0] > lo);
       while (rel) {
         const int si = s0 + __builtin_ctzll(rel);
         rel &= rel - 1;
         const int n = uniform_i(hc[si]);
         if (n <= cap) {
-          if (lane < n) f(cwj[(int64_t)si * cap + lane], gptr(a.crow)[(j * nsub + si) * (int64_t)cap + lane]);
+          const bool in = lane < n;
+          f(in, in ? cwj[(int64_t)si * cap + lane] : 0.0,
+            in ? gptr(a.crow)[(j * nsub + si) * (int64_t)cap + lane] : 0);
         } else {
           const int rbase = (si >> 2) * RB, tt = (si & 3) * 64 + lane;
           T th[VPT];
@@ -480,33 +624,104 @@ long_threshold_kernel(LongArgs<T> a) {
 #pragma unroll
           for (int k = 0; k < VPT; ++k) {
             const int r = rbase + ((k / VEC) * LNT + tt) * VEC + (k % VEC);
-            if (r < R) f(long_w((double)th[k], 2.0 * long_b(t, pv, pmm, r, Sm), costv(r), a.inv_rho), r);
+            const int rl = r < R ? r : rbase;
+            // (long_base_kernel's 2 b with the sparse store)
+            const double b2 = SP ? gptr(a.b2v)[(((size_t)m * a.nrb + (si >> 2)) * VPT + k) * LNT + tt]
+                                       : 2.0 * long_b(t, pv, pmm, rl, Sm);
+            f(r < R, long_w((double)th[k], b2, costv(rl), a.inv_rho), r);
           }
         }
       }
     }
   };
+  // The kept entries of every sub-tile that counts, in order, in LDS: lane l
+  // copies those of sub-tile s0 + l.  Columns with more than LW of them, or
+  // with an overflowed sub-tile, read them again in every round.
+  double* const list = s_list[threadIdx.x >> 6];
+  int nlist = 0, wrow = -1;
+  for (int s0 = 0; s0 < nsub && nlist <= LW; s0 += 64) {
+    const int s = s0 + lane;
+    const bool rel = looked(s) && hm[s < nsub ? s : 0] > lo;
+    const int n = rel ? hc[s] : 0;
+    if (__ballot(n > cap) != 0ull) {
+      nlist = LW + 1;
+      break;
+    }
+    if (__ballot(rel) == 0ull) continue;
+    int off = n;  // inclusive prefix sum over the lanes
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+      const int v = __shfl_up(off, d);
+      if (lane >= d) off += v;
+    }
+    const int tot = __builtin_amdgcn_readlane(off, 63);
+    off += nlist - n;
+    nlist += tot;
+    if (nlist > LW) break;
+    const int64_t h0 = (int64_t)(s < nsub ? s : 0) * cap;
+    for (int e0 = 0; __ballot(e0 < n) != 0ull; e0 += 4) {
+      double x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = e0 + u < n ? cwj[h0 + e0 + u] : 0.0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (e0 + u < n) {
+          list[off + e0 + u] = x[u];
+          if (x[u] == wmx) wrow = gptr(a.crow)[j * nsub * (int64_t)cap + h0 + e0 + u];
+        }
+    }
+  }
+  wave_lds_sync();
   const double lprev = lamv[j];
   double lam = (a.warm && lprev == lprev && lprev > lo) ? lprev : lo;
+  // a list made in a round holds the entries above that round's threshold
+  // lfrom; mxout is the largest of the others
+  double lfrom = -__builtin_huge_val(), mxout = -__builtin_huge_val();
   int nprev = -1, nrounds = 0, nact = 0;
   for (int round = 0; round < R + 4; ++round) {
-    ++nrounds;
-    double S = 0.0, mnA = __builtin_huge_val(), mxN = -__builtin_huge_val();
-    double nd = 0.0;
-    visit([&](double x, int) {
-      if (x > lam) {
-        S += x;
-        nd += 1.0;
-        mnA = fmin(mnA, x);
-      } else {
-        mxN = fmax(mxN, x);
+    double S = 0.0, mnA = __builtin_huge_val(), mxN = mxout;
+    int n = 0;
+    const bool all = nlist > LW;  // every entry, read again
+    if (all) {
+      // each 64 entries above lam go through the list's LDS to the lanes
+      visit([&](bool in, double x, int r) {
+        if (in && x == wmx) wrow = r;
+        const bool act = in && x > lam;
+        const unsigned long long bal = __ballot(act);
+        mnA = fmin(mnA, act ? x : __builtin_huge_val());
+        mxN = fmax(mxN, in && !act ? x : -__builtin_huge_val());
+        if (act) {
+          const int pos = n + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+          list[pos & (LW - 1)] = x;
+        }
+        const int n0 = n & ~63;
+        n += __popcll(bal);
+        if ((n & ~63) != n0) {
+          wave_lds_sync();
+          S += list[(n0 & (LW - 1)) + lane];
+          wave_lds_sync();
+        }
+      });
+      wave_lds_sync();
+      if (lane < (n & 63)) S += list[((n & ~63) & (LW - 1)) + lane];
+    } else {
+      for (int i = 0; i < nlist; i += 64) {
+        const double x = list[i + lane < nlist ? i + lane : 0];
+        const bool act = i + lane < nlist && x > lam;
+        const unsigned long long bal = __ballot(act);
+        mnA = fmin(mnA, act ? x : __builtin_huge_val());
+        mxN = fmax(mxN, i + lane < nlist && !act ? x : -__builtin_huge_val());
+        if (bal == 0ull) continue;
+        const double y = rank_lane(bal, n, x);
+        if (((lane - n) & 63) < __popcll(bal)) S += y;
+        n += __popcll(bal);
       }
-    });
+    }
+    ++nrounds;
     S = wave_sum(S);
-    nd = wave_sum(nd);
     mnA = wave_reduce<OpMin>(mnA);
     mxN = wave_max(mxN);
-    const int n = (int)nd;
     if (n == 0) {
       if (lam > lo) {  // a warm start at or above w_max: restart from the bound
         lam = lo;
@@ -519,25 +734,53 @@ long_threshold_kernel(LongArgs<T> a) {
     }
     const double ln = (S - tau) / (double)n;
     if (ln >= lo && (n == nprev || (mnA >= ln && mxN <= ln))) {
-      lam = ln;  // the set above lam is exactly the active set
+      // the set above lam is exactly the active set
+      lam = ln;
       nact = n;
       break;
     }
     nprev = n;
+    if (all && n <= LW) {  // they fit: the list from here on
+      nlist = n;
+      lfrom = lam;
+      mxout = mxN;
+    }
     lam = fmax(ln, lo);
+    if (lam < lfrom) {  // (a warm start above the threshold): entries are missing
+      nlist = LW + 1;
+      lfrom = mxout = -__builtin_huge_val();
+    }
   }
   // relaxed columns: max(w - max(lam, 0), 0) is the projection onto
   // {u >= 0, sum u <= q_s} (the write pass patches only entries above it)
   if (a.relaxed) lam = fmax(lam, 0.0);
   if (lane == 0) lamv[j] = lam;
+  if (SP) {
+    // the row of the column's maximum, for long_limit_kernel: a kept entry,
+    // or (q_s below the rounding of w) slot 0 of a sub-tile that kept none
+    const unsigned long long has = __ballot(wrow >= 0);
+    if (has) {
+      wrow = __builtin_amdgcn_readlane(wrow, __builtin_ctzll(has));
+    } else {
+      for (int s0 = 0; s0 < nsub; s0 += 64) {
+        const int s = s0 + lane;
+        const unsigned long long at = __ballot(looked(s) && hm[s < nsub ? s : 0] == wmx);
+        if (at == 0ull) continue;
+        const int si = s0 + __builtin_ctzll(at);
+        if (uniform_i(hc[si]) == 0) wrow = uniform_i(gptr(a.crow)[(j * nsub + si) * (int64_t)cap]);
+        break;
+      }
+    }
+    if (lane == 0) gptr(a.wit)[j] = wrow;
+  }
   if constexpr (DIAG) {
     // the column's pi_hat = max(w - lam, 0) at the same entries and in the
     // same arithmetic as the write pass: its sum against q_s and against the
     // cost (fixed order: sub-tiles in order, lanes by the wave sum)
     double cs = 0.0, wc = 0.0;
     if (lam < __builtin_huge_val()) {
-      visit([&](double x, int r) {
-        if (x > lam) {
+      visit([&](bool in, double x, int r) {
+        if (in && x > lam) {
           const double ph = fmax(x - lam, 0.0);
           cs += ph;
           wc += costv(r) * ph;
@@ -589,6 +832,123 @@ long_write_kernel(LongArgs<T> a) {
   const double* const lamv = gptr(a.lam);
   const bool sparse = a.sparse != 0;
   const int par = sparse ? uniform_i(*gptr(a.spar)) : 0;
+  // Sparse store.  A sub-tile that the scan left out of a column keeps its
+  // patch count of 0, so only the columns of gmask's set bits need work, in
+  // order and 64 at a time: lane l takes column l's header, compares its kept
+  // entries with the threshold and stores the patches; the updates then go to
+  // the row sums in column order, those of one row one after the other.
+  // (Taken one column at a time, each with its own chain of loads, the 40 x 40
+  // images took 0.27 ms: the patches gather in few tiles.)
+  constexpr int LP = 256;  // updates of a batch
+  __shared__ int s_col[4][128], s_slot[4][LP];
+  __shared__ double s_upd[4][LP];
+  auto write_sparse = [&](auto&& column, int rb, int64_t j0, int64_t j1, int rbase, double tt, double Sm,
+                          const double* pv, const double* pmm) {
+    const int lane = tid & 63, sub = rb * 4 + wv;
+    int* const col = s_col[wv];
+    int* const slot = s_slot[wv];
+    double* const upd = s_upd[wv];
+    auto batch = [&](int nc) {
+      const bool in = lane < nc;
+      const int64_t j = in ? col[lane] : j0;
+      const int64_t h = j * nsub + sub;
+      const double lam = lamv[j];
+      const double lmax = in ? hm[h] : -__builtin_huge_val();
+      const bool act = lmax > lam;
+      const int n = act ? hc[h] : 0;
+      int32_t* const pcj = gptr(a.pcnt) + (int64_t)sub * a.T_cols + j;
+      if (in && !act) *pcj = 0;
+      int kept = 0;
+      const bool over = __ballot(n > cap) != 0ull;
+      if (!over)
+        for (int e0 = 0; __ballot(e0 < n) != 0ull; e0 += 4) {
+          double x[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) x[u] = e0 + u < n ? cw[h * cap + e0 + u] : -__builtin_huge_val();
+#pragma unroll
+          for (int u = 0; u < 4; ++u) kept += x[u] > lam ? 1 : 0;
+        }
+      int off = kept;
+#pragma unroll
+      for (int d = 1; d < 64; d *= 2) {
+        const int v = __shfl_up(off, d);
+        if (lane >= d) off += v;
+      }
+      const int tot = __builtin_amdgcn_readlane(off, 63);
+      if (over || tot > LP) {
+        for (unsigned long long am = __ballot(act); am != 0ull; am &= am - 1ull) {
+          const int l = __builtin_ctzll(am);
+          column((int64_t)__builtin_amdgcn_readlane((int)j, l), read_lane(lam, l), read_lane(lmax, l),
+                 __builtin_amdgcn_readlane(n, l));
+        }
+        return;
+      }
+      off -= kept;
+      int pos = 0;
+      for (int e0 = 0; __ballot(e0 < n) != 0ull; e0 += 4) {
+        double x[4], b[4];
+        int r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          x[u] = e0 + u < n ? cw[h * cap + e0 + u] : -__builtin_huge_val();
+          r[u] = x[u] > lam ? crow[h * cap + e0 + u] : rbase;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) b[u] = long_b(tt, pv, pmm, r[u], Sm);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (x[u] > lam) {
+            const double d = fmax(x[u] - lam, 0.0);  // theta' - (-b) before rounding
+            gptr(a.prow)[h * cap + pos] = r[u];
+            gptr(a.pval)[h * cap + pos] = (T)(d - b[u]);
+            const int rr = r[u] - rbase;
+            slot[off + pos] = slot_of(rr, VEC) * LNT + slot_owner(rr, VEC);
+            upd[off + pos] = d;
+            ++pos;
+          }
+      }
+      if (act) *pcj = kept;
+      wave_lds_sync();
+      for (int i0 = 0; i0 < tot; i0 += 64) {
+        const int ni = tot - i0 < 64 ? tot - i0 : 64;
+        const int sl = lane < ni ? slot[i0 + lane] : -1 - lane;
+        int before = 0;  // earlier updates of the same row
+        for (int l = 0; l + 1 < ni; ++l)
+          before += (lane > l && __builtin_amdgcn_readlane(sl, l) == sl) ? 1 : 0;
+        for (int k = 0; __ballot(lane < ni && before >= k) != 0ull; ++k) {
+          if (lane < ni && before == k) fix[sl] += upd[i0 + lane];
+          wave_lds_sync();
+        }
+      }
+      wave_lds_sync();
+    };
+    int nc = 0;
+    const int64_t g1 = (j1 + 63) >> 6;
+    for (int64_t g0 = j0 >> 6; g0 < g1; g0 += 64) {
+      unsigned long long word = g0 + lane < g1 ? gptr(a.gmask)[(int64_t)sub * a.ngrp + g0 + lane] : 0ull;
+      for (unsigned long long some = __ballot(word != 0ull); some != 0ull; some &= some - 1ull) {
+        const int l = __builtin_ctzll(some);
+        const int64_t j = ((g0 + l) << 6) + lane;
+        const unsigned long long w = (unsigned long long)__double_as_longlong(read_lane(__longlong_as_double((long long)word), l));
+        const unsigned long long bits = __ballot(((w >> lane) & 1ull) && j >= j0 && j < j1);
+        if ((bits >> lane) & 1ull)
+          col[nc + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bits >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((unsigned)bits, 0u))] = (int)j;
+        nc += __popcll(bits);
+        wave_lds_sync();
+        if (nc >= 64) {
+          batch(64);
+          nc -= 64;
+          const int v = lane < nc ? col[64 + lane] : 0;
+          wave_lds_sync();
+          if (lane < nc) col[lane] = v;
+          wave_lds_sync();
+        }
+      }
+    }
+    if (nc > 0) batch(nc);
+    wave_lds_sync();
+  };
   const int ib = uniform_i(a.wg_it[blockIdx.x]), ie = uniform_i(a.wg_it[blockIdx.x + 1]);
   for (int it = ib; it < ie; ++it) {
     const int rb = uniform_i(a.it_rb[it]), m = uniform_i(a.it_m[it]);
@@ -600,10 +960,16 @@ long_write_kernel(LongArgs<T> a) {
     const int rbase = rb * RB;
     const int sub = rb * 4 + wv;
     auto row = [&](int k) { return rbase + ((k / VEC) * LNT + tid) * VEC + (k % VEC); };
+    // b of slot k's row (sparse store: half the 2 b that long_base_kernel left)
+    const size_t o2 = ((size_t)m * a.nrb + rb) * VPT * LNT + tid;
+    auto b_of = [&](int k) {
+      const double v = sparse ? 0.5 * gptr(a.b2v)[o2 + k * LNT] : long_b(t, pv, pmm, row(k) < R ? row(k) : rbase, Sm);
+      return row(k) < R ? v : 0.0;
+    };
     T nb[VPT];  // -b rounded to the storage type: every inactive entry's new value
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
-      nb[k] = (T)(-(row(k) < R ? long_b(t, pv, pmm, row(k), Sm) : 0.0));
+      nb[k] = (T)(-b_of(k));
       fix[k * LNT + tid] = 0.0;  // each thread touches only its own slots
     }
     // sparse store: the tile's new common values of measure m, written once
@@ -616,23 +982,7 @@ long_write_kernel(LongArgs<T> a) {
         if (row(k) < R) nbn[row(k)] = nb[k];
     }
     const T* __restrict__ nbo = sparse ? gptr(a.nbv) + ((size_t)par * a.M + m) * R : nullptr;
-    for (int64_t jb = j0; jb < j1; jb += WB) {
-      // thresholds and this tile's four sub-tile headers of 256 columns
-      __syncthreads();  // the previous block's readers are done
-      if (tid < WB && jb + tid < j1) {
-        const int64_t jj = jb + tid;
-        s_lam[tid] = lamv[jj];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          s_max[q][tid] = hm[jj * nsub + rb * 4 + q];
-          s_cnt[q][tid] = hc[jj * nsub + rb * 4 + q];
-        }
-      }
-      __syncthreads();
-      const int64_t je = jb + WB < j1 ? jb + WB : j1;
-    auto column = [&](int64_t j) {
-      const double lam = uniform_d(s_lam[j - jb]), lmax = uniform_d(s_max[wv][j - jb]);
-      const int n = uniform_i(s_cnt[wv][j - jb]);
+    auto column = [&](int64_t j, double lam, double lmax, int n) {
       T* __restrict__ thp = theta + j * a.ld;
       const bool some = lmax > lam;  // some entry of this sub-tile is active
       const int64_t h = j * nsub + sub;
@@ -649,11 +999,10 @@ long_write_kernel(LongArgs<T> a) {
         const int lane = tid & 63;
         const int pr = lane < pc ? gptr(a.prow)[h * cap + lane] : 0;
         const T pvv = lane < pc ? gptr(a.pval)[h * cap + lane] : T(0);
-#pragma unroll 1
-        for (int c = 0; c < NCH; ++c) {
+        // stored values tv, b and w of vector c (w = -inf past R)
+        auto vec_w = [&](int c, T (&tv)[VEC], double (&bk)[VEC], double (&w)[VEC]) {
           const int r0 = rbase + (c * LNT + tid) * VEC;
           const int rl = r0 < R ? r0 : rbase;  // rows past R read the tile's first (masked)
-          T tv[VEC], out[VEC];
           if (pc < 0) {
             load_vec<T, VEC>(thp + rl, tv);
           } else {
@@ -671,16 +1020,63 @@ long_write_kernel(LongArgs<T> a) {
           }
 #pragma unroll
           for (int v = 0; v < VEC; ++v) {
+            const int rv = r0 + v < R ? r0 + v : rbase;
+            bk[v] = sparse ? 0.5 * gptr(a.b2v)[o2 + (c * VEC + v) * LNT] : long_b(t, pv, pmm, rv, Sm);
+            const double cc = a.gdim ? grid_cost(a, rv, z0, z1) : (double)cp[rv];
+            w[v] = r0 + v < R ? long_w((double)tv[v], 2.0 * bk[v], cc, inv_rho) : -__builtin_huge_val();
+          }
+        };
+        if (sparse) {
+          // no more active entries than slots (the usual case: the slots ran
+          // out of candidates, not of active entries): patches
+          int na = 0;
+#pragma unroll 1
+          for (int c = 0; c < NCH; ++c) {
+            T tv[VEC];
+            double bk[VEC], w[VEC];
+            vec_w(c, tv, bk, w);
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) na += __popcll(__ballot(w[v] > lam));
+          }
+          if (na <= cap) {
+            int pos = 0;
+#pragma unroll 1
+            for (int c = 0; c < NCH; ++c) {
+              T tv[VEC];
+              double bk[VEC], w[VEC];
+              vec_w(c, tv, bk, w);
+#pragma unroll
+              for (int v = 0; v < VEC; ++v) {
+                const unsigned long long bal = __ballot(w[v] > lam);
+                if (w[v] > lam) {
+                  const int e = pos + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+                  const double ph = fmax(w[v] - lam, 0.0);
+                  gptr(a.prow)[h * cap + e] = row(c * VEC + v);
+                  gptr(a.pval)[h * cap + e] = (T)(ph - bk[v]);
+                  fix[(c * VEC + v) * LNT + tid] += ph;
+                }
+                pos += __popcll(bal);
+              }
+            }
+            if (lane == 0) *pcj = na;
+            return;
+          }
+        }
+#pragma unroll 1
+        for (int c = 0; c < NCH; ++c) {
+          const int r0 = rbase + (c * LNT + tid) * VEC;
+          T tv[VEC], out[VEC];
+          double bk[VEC], w[VEC];
+          vec_w(c, tv, bk, w);
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) {
             out[v] = T(0);  // rows past R are not stored
             if (r0 + v < R) {
-              const double bk = long_b(t, pv, pmm, r0 + v, Sm);
-              const T nbk = (T)(-bk);  // the entry's value when inactive (nb of its slot)
-              const double cc = a.gdim ? grid_cost(a, r0 + v, z0, z1) : (double)cp[r0 + v];
-              const double w = long_w((double)tv[v], 2.0 * bk, cc, inv_rho);
-              out[v] = nbk;
-              if (w > lam) {
-                const double ph = fmax(w - lam, 0.0);
-                out[v] = (T)(ph - bk);
+              out[v] = (T)(-bk[v]);  // the entry's value when inactive (nb of its slot)
+              if (w[v] > lam) {
+                const double ph = fmax(w[v] - lam, 0.0);
+                out[v] = (T)(ph - bk[v]);
                 fix[(c * VEC + v) * LNT + tid] += ph;  // theta' - (-b) before rounding
               }
             }
@@ -789,24 +1185,25 @@ long_write_kernel(LongArgs<T> a) {
         }
       }
     };
-      if (sparse) {
-        // sparse store: only columns whose sub-tile has an active entry need
-        // work; the others get a patch count of 0, 64 columns at a time
-        const int lane = tid & 63;
-        for (int64_t c0 = jb; c0 < je; c0 += 64) {
-          const int64_t jl = c0 + lane;
-          const bool in = jl < je;
-          const bool act = in && s_max[wv][in ? jl - jb : 0] > s_lam[in ? jl - jb : 0];
-          if (in && !act) gptr(a.pcnt)[(int64_t)sub * a.T_cols + jl] = 0;
-          unsigned long long am = __ballot(act);
-          while (am != 0ull) {
-            const int64_t j = c0 + __builtin_ctzll(am);
-            am &= am - 1ull;
-            column(j);
+    if (sparse) {
+      write_sparse(column, rb, j0, j1, rbase, t, Sm, pv, pmm);
+    } else {
+      for (int64_t jb = j0; jb < j1; jb += WB) {
+        // thresholds and this tile's four sub-tile headers of WB columns
+        __syncthreads();  // the previous block's readers are done
+        if (tid < WB && jb + tid < j1) {
+          const int64_t jj = jb + tid;
+          s_lam[tid] = lamv[jj];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            s_max[q][tid] = hm[jj * nsub + rb * 4 + q];
+            s_cnt[q][tid] = hc[jj * nsub + rb * 4 + q];
           }
         }
-      } else {
-        for (int64_t j = jb; j < je; ++j) column(j);
+        __syncthreads();
+        const int64_t je = jb + WB < j1 ? jb + WB : j1;
+        for (int64_t j = jb; j < je; ++j)
+          column(j, uniform_d(s_lam[j - jb]), uniform_d(s_max[wv][j - jb]), uniform_i(s_cnt[wv][j - jb]));
       }
     }
     // the item's row sums: (#columns) * (-b) plus the patches, in double
@@ -817,7 +1214,7 @@ long_write_kernel(LongArgs<T> a) {
     double* __restrict__ part = gptr(a.partial) + uniform_l(a.it_poff[it]);
 #pragma unroll
     for (int k = 0; k < VPT; ++k)
-      if (row(k) < R) part[row(k) - rbase] = fix[k * LNT + tid] - ncols * long_b(t, pv, pmm, row(k), Sm);
+      if (row(k) < R) part[row(k) - rbase] = fix[k * LNT + tid] - ncols * b_of(k);
   }
   if constexpr (DIAG) {
     __shared__ double sh_dth[4];
@@ -864,6 +1261,225 @@ long_rowsum_kernel(LongArgs<T> a, int rows_per_tile) {
   }
 }
 
+// ---- sparse store: what the scan can leave out ---------------------------
+// Least cost of every (sub-tile, cost column), once per call: the cost of a
+// call does not change.  A workgroup takes one row tile and 16 cost columns.
+template <typename T, int VPT, int VEC, bool GRID>
+__global__ void __launch_bounds__(LNT)
+long_cost_min_kernel(LongArgs<T> a) {
+  constexpr int RB = LNT * VPT;
+  if (a.stop != nullptr && uniform_i(*gptr(a.stop)) != 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wv = uniform_i(tid >> 6);
+  const int R = a.R, rb = blockIdx.x, rbase = rb * RB;
+  int row[VPT];
+  double gx0[GRID ? VPT : 1], gx1[GRID ? VPT : 1];
+#pragma unroll
+  for (int k = 0; k < VPT; ++k) {
+    row[k] = rbase + ((k / VEC) * LNT + tid) * VEC + (k % VEC);
+    if constexpr (GRID) {
+      const int i0 = row[k] / a.gn1;
+      gx0[k] = grid_coord(a, 0, i0);
+      gx1[k] = grid_coord(a, 1, row[k] - i0 * a.gn1);
+    }
+  }
+  const int64_t c0 = a.c_first + (int64_t)blockIdx.y * 16;
+  const int64_t c1 = c0 + 16 < a.ncost ? c0 + 16 : a.ncost;
+  for (int64_t c = c0; c < c1; ++c) {
+    double z0 = 0.0, z1 = 0.0;
+    if constexpr (GRID) grid_point(a, c, 0, &z0, &z1);
+    double mn = __builtin_huge_val();
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) {
+      double v;
+      if constexpr (GRID) v = grid_cost_xy<T>(gx0[k], gx1[k], z0, z1);
+      else v = (double)a.cost[c * a.cost_ld + (row[k] < R ? row[k] : rbase)];
+      if (row[k] < R) mn = fmin(mn, v);
+    }
+    mn = wave_reduce<OpMin>(mn);
+    if (lane == 0) gptr(a.cmin)[(int64_t)(rb * 4 + wv) * a.ncost + c] = (T)mn;
+  }
+}
+
+// A lower bound of every column's threshold for the iteration to come.  With
+// the sums taken over the column's patches alone (its last active entries),
+// (sum w - q_s)/n is one Newton step of Prop. 3 from below, hence at most the
+// threshold of those entries, hence at most the column's; so is w - q_s of any
+// single entry.  A column without patches (no active entry, or a sub-tile that
+// overflowed its slots) uses the row of its last maximum, whose stored value
+// is at least the one read here.  A margin of 2^-40 of the magnitudes covers the rounding.  One
+// thread per (column, 1/kLimitWaves of the sub-tiles), 64 columns per workgroup:
+// the counts are stored with the column index fastest.  Then the sub-tiles of
+// each column to scan, as masks and as the scan's work list.
+template <typename T, int VPT, int VEC>
+__global__ void __launch_bounds__(64 * kLimitWaves)
+long_limit_kernel(LongArgs<T> a) {
+  constexpr int RB = LNT * VPT;
+  __shared__ double s_top[kLimitWaves][64], s_sum[kLimitWaves][64];
+  __shared__ int s_n[kLimitWaves][64];
+  if (a.stop != nullptr && uniform_i(*gptr(a.stop)) != 0) return;
+  const int lane = threadIdx.x & 63, q = uniform_i((int)(threadIdx.x >> 6));
+  const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+  const bool in = j < a.T_cols;
+  const int nsub = a.nrb * 4;
+  const bool dense = uniform_i(gptr(a.spar)[1]) != 0;  // everything is scanned
+  if (in)
+    for (int k = q; k < a.nmask; k += kLimitWaves) gptr(a.smask)[j * a.nmask + k] = dense ? ~0ull : 0ull;
+  if (dense)
+    for (int s = threadIdx.x; s < nsub; s += 64 * kLimitWaves) gptr(a.gmask)[(int64_t)s * a.ngrp + blockIdx.x] = ~0ull;
+  double top = -__builtin_huge_val(), sum = 0.0;
+  int n = 0, m = 0;
+  double z0 = 0.0, z1 = 0.0;
+  int64_t off_m = 0;
+  if (in) {
+    while (m + 1 < a.M && gptr(a.col_off)[m + 1] <= j) ++m;
+    off_m = gptr(a.col_off)[m];
+    if (a.gdim) grid_point(a, j, off_m, &z0, &z1);
+  }
+  const double* const b2m = gptr(a.b2v) + (size_t)m * a.nrb * VPT * LNT;
+  auto w_of = [&](int r, T v) -> double {
+    const double c = a.gdim ? grid_cost(a, r, z0, z1) : (double)long_cost_col(a, j, off_m)[r];
+    const int rr = r % RB;
+    const double b2 = b2m[((size_t)(r / RB) * VPT + slot_of(rr, VEC)) * LNT + slot_owner(rr, VEC)];
+    return long_w((double)v, b2, c, a.inv_rho);
+  };
+  constexpr int U = 8;
+  const int s1 = nsub * (q + 1) / kLimitWaves;
+  for (int s0 = dense ? s1 : nsub * q / kLimitWaves; s0 < s1; s0 += U) {
+    int pc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) pc[u] = in && s0 + u < s1 ? gptr(a.pcnt)[(int64_t)(s0 + u) * a.T_cols + j] : 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t h = j * nsub + s0 + u;
+      for (int e = 0; e < pc[u]; ++e) {
+        const double w = w_of(gptr(a.prow)[h * a.cap + e], gptr(a.pval)[h * a.cap + e]);
+        top = fmax(top, w);
+        sum += w;
+        ++n;
+      }
+    }
+  }
+  s_top[q][lane] = top;
+  s_sum[q][lane] = sum;
+  s_n[q][lane] = n;
+  __syncthreads();
+  if (q == 0) {
+    for (int k = 1; k < kLimitWaves; ++k) {
+      top = fmax(top, s_top[k][lane]);
+      sum += s_sum[k][lane];
+      n += s_n[k][lane];
+    }
+    const double tau = in ? (double)gptr(a.q)[j] : 0.0;
+    double lim = -__builtin_huge_val();
+    if (n > 0) {
+      lim = fmax(top - tau, (sum - tau) / (double)n);
+    } else if (in) {
+      const int r = gptr(a.wit)[j];
+      if (r >= 0 && r < a.R) {
+        const int par = *gptr(a.spar);
+        const int si = r / RB * 4 + (slot_owner(r % RB, VEC) >> 6);
+        const bool th = gptr(a.pcnt)[(int64_t)si * a.T_cols + j] < 0;
+        lim = w_of(r, th ? gptr(a.theta)[j * a.ld + r] : gptr(a.nbv)[((size_t)par * a.M + m) * a.R + r]) - tau;
+      }
+    }
+    // a column of weight 0 is 0 whatever its w
+    lim = tau > 0.0 ? lim - (fabs(lim) + tau) * 0x1p-40 : __builtin_huge_val();
+    if (in) {
+      gptr(a.limit)[j] = lim;
+      gptr(a.colm)[j] = m;
+    }
+    s_top[0][lane] = lim;
+  }
+  __syncthreads();
+  if (dense) return;
+  // The sub-tiles to scan: those with a patch or dense, and those whose bound
+  // of w (by the multiply-add that forms w) exceeds the column's bound.
+  const double lim = s_top[0][lane];
+  const int64_t cc = !in ? 0
+                     : a.cost_mode == MAM_COST_INDEXED ? (int64_t)a.cidx[j]
+                     : a.cost_mode == MAM_COST_PER_COLUMN ? j : j - off_m;
+  const double* const bm = gptr(a.bmax) + (int64_t)m * nsub;
+  for (int s0 = nsub * q / kLimitWaves; s0 < s1; s0 += 64) {  // lane l keeps the word of sub-tile s0 + l
+    unsigned long long word = 0ull;
+    unsigned long long mine = 0ull;  // this column's sub-tiles
+    const int ns = s1 - s0 < 64 ? s1 - s0 : 64;
+    for (int u0 = 0; u0 < ns; u0 += U) {
+      int pc[U];
+      double bd[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int s = u0 + u < ns ? s0 + u0 + u : s0;
+        pc[u] = in ? gptr(a.pcnt)[(int64_t)s * a.T_cols + j] : 0;
+        bd[u] = __builtin_fma(-(double)gptr(a.cmin)[(int64_t)s * a.ncost + cc], a.inv_rho, bm[s]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool go = in && u0 + u < ns && (pc[u] != 0 || !(bd[u] <= lim));
+        const unsigned long long b = __ballot(go);
+        if (lane == u0 + u) word = b;
+        if (go) mine |= 1ull << (u0 + u);
+      }
+    }
+    if (in && mine != 0ull) {
+      const int k = s0 >> 6, sh = s0 & 63;
+      unsigned long long* const mk = gptr(a.smask) + j * a.nmask + k;
+      atomicOr(mk, mine << sh);
+      if (sh != 0 && (mine >> (64 - sh)) != 0ull) atomicOr(mk + 1, mine >> (64 - sh));
+    }
+    if (lane < ns) gptr(a.gmask)[(int64_t)(s0 + lane) * a.ngrp + blockIdx.x] = word;
+    const int nc = (__popcll(word) + kScanCols - 1) / kScanCols;
+    int off = nc;
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+      const int v = __shfl_up(off, d);
+      if (lane >= d) off += v;
+    }
+    const int tot = __builtin_amdgcn_readlane(off, 63);
+    int first = 0;
+    if (lane == 0 && tot > 0) first = atomicAdd(gptr(a.spar) + 2, tot);
+    first = uniform_i(first) + off - nc;
+    for (int c = 0; c < nc; ++c) {
+      unsigned long long rest = word;
+      for (int k = 0; k < kScanCols; ++k) rest &= rest - 1ull;  // 0 stays 0
+      gptr(a.wsub)[first + c] = s0 + lane;
+      gptr(a.wgrp)[first + c] = (int32_t)blockIdx.x;
+      gptr(a.wcol)[first + c] = word & ~rest;
+      word = rest;
+    }
+  }
+}
+
+// ---- sparse store: the per-row terms -------------------------------------
+// 2 b and the common value + 2 b of every row, once per iteration for the scan
+// and write kernels: formed in each of their workgroups they were most of the
+// time of both (two dependent loads and a division per row, at 16 rows a
+// thread; the scan of ten 40 x 40 images 0.36 ms).
+template <typename T, int VPT, int VEC>
+__global__ void __launch_bounds__(LNT)
+long_base_kernel(LongArgs<T> a) {
+  if (a.stop != nullptr && uniform_i(*gptr(a.stop)) != 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wv = uniform_i(tid >> 6);
+  const int rb = blockIdx.x, m = blockIdx.y, R = a.R, rbase = rb * LNT * VPT;
+  const int par = uniform_i(*gptr(a.spar));
+  if (rb == 0 && m == 0 && tid == 0) gptr(a.spar)[2] = 0;
+  const double t = uniform_d(*gptr(a.t)), Sm = uniform_d(gptr(a.Sd)[m]);
+  const double* const pmm = gptr(a.pm) + (size_t)m * R;
+  const T* const nbm = gptr(a.nbv) + ((size_t)par * a.M + m) * R;
+  const size_t o = ((size_t)m * a.nrb + rb) * VPT * LNT + tid;
+  double mx = -__builtin_huge_val();
+#pragma unroll
+  for (int k = 0; k < VPT; ++k) {
+    const int r = rbase + ((k / VEC) * LNT + tid) * VEC + (k % VEC), rl = r < R ? r : rbase;
+    const double b2 = r < R ? 2.0 * long_b(t, gptr(a.p), pmm, rl, Sm) : -__builtin_huge_val();
+    const double bs = (double)nbm[rl] + b2;
+    gptr(a.b2v)[o + k * LNT] = b2;
+    gptr(a.basev)[o + k * LNT] = bs;
+    mx = fmax(mx, bs);
+  }
+  mx = wave_max(mx);
+  if (lane == 0) gptr(a.bmax)[((int64_t)m * a.nrb + rb) * 4 + wv] = mx;
+}
+
 // ---- sparse store: write-back --------------------------------------------
 // Write the stored plans back into theta: every sparse sub-tile is stored as
 // its common values (whole vectors) and then its patches (each by the thread
@@ -877,6 +1493,7 @@ long_materialize_kernel(LongArgs<T> a) {
   const int R = a.R, cap = a.cap, nsub = a.nrb * 4;
   const int par = uniform_i(*gptr(a.spar));
   T* const theta = gptr(a.theta);
+  if (blockIdx.x == 0 && tid == 0) gptr(a.spar)[1] = 1;  // (read by no other workgroup of this kernel)
   const int ib = uniform_i(a.wg_it[blockIdx.x]), ie = uniform_i(a.wg_it[blockIdx.x + 1]);
   for (int it = ib; it < ie; ++it) {
     const int rb = uniform_i(a.it_rb[it]), m = uniform_i(a.it_m[it]);

@@ -129,14 +129,6 @@ __device__ __forceinline__ ConstPtr<U> cptr(const U* p) {
   return (ConstPtr<U>)(uint64_t)p;
 }
 
-// Orders one wave's LDS writes before its later LDS reads (the hardware
-// keeps a wave's LDS operations in order; this keeps the compiler to it).
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-}
-
 // Maxima of results of arithmetic: one instruction each (max_arith).
 struct OpMaxA {
   static constexpr double id() { return -__builtin_huge_val(); }
