@@ -128,6 +128,7 @@ struct Group {
 struct Layout {
   size_t partial = 0, diag = 0, seg_p = 0, seg_m = 0, seg_j0 = 0, seg_j1 = 0, seg_poff = 0, seg_idx = 0, seg_st = 0;
   size_t wg_seg = 0, mseg = 0, probdev = 0, probaux = 0, mtasks = 0, atasks = 0;
+  size_t chk = 0, nchk = 0;       // what init reads back
   size_t meas_p = 0, meas_m = 0;  // every measure's problem and number
   size_t stop = 0, stop_part = 0;  // stopping-test state and row-block partials
   size_t total = 0;
@@ -860,7 +861,6 @@ void build_layout(Plan* pl) {
     sp.o_rows = take(sp.rows.size() * sizeof(mam::SpRows));
     sp.o_costs = take(sp.costs.size() * sizeof(mam::SpCost));
     sp.o_cand = take(sp.cand.size() * sizeof(mam::CandTask));
-    sp.o_stat = take(8);
   }
   for (Prob& p : pl->P) {
     const size_t R = (size_t)p.R, M = (size_t)p.M;
@@ -889,7 +889,6 @@ void build_layout(Plan* pl) {
     p.o_d2 = take((size_t)p.nb * 8);
     p.o_t = take(2 * 8);
     p.o_lam = take((size_t)p.T * 8);
-    p.o_check = take((M + 2) * 8);
     p.o_coloff = take((M + 1) * 8);
     p.o_Sd = take(M * 8);
     p.o_aw = take(M * 8);
@@ -898,6 +897,18 @@ void build_layout(Plan* pl) {
       p.o_fx = take(2 * M * 8);
     }
   }
+  // what init reads back, in one piece: every problem's masses and flags, and
+  // the sum of sampled candidates
+  size_t nchk = 1;
+  for (const Prob& p : pl->P) nchk += (size_t)p.M + 2;
+  L.nchk = nchk;
+  L.chk = take(nchk * 8);
+  size_t ochk = L.chk;
+  for (Prob& p : pl->P) {
+    p.o_check = ochk;
+    ochk += ((size_t)p.M + 2) * 8;
+  }
+  sp.o_stat = ochk;
   L.total = o;
 }
 
@@ -1212,7 +1223,8 @@ mam_status upload_tables(Plan* pl, hipStream_t st) {
               at<double>(pl, p.o_d2), at<double>(pl, p.o_aw), at<double>(pl, p.o_Sd), (int32_t)p.R,
               (int32_t)p.M, p.mbase, p.nb,
               pl->lg.on ? nullptr : at<unsigned long long>(pl, p.o_acc),
-              pl->lg.on ? nullptr : at<double>(pl, p.o_fx) + p.M, p.rho, p.gamma, at<double>(pl, p.o_t)};
+              pl->lg.on ? nullptr : at<double>(pl, p.o_fx) + p.M, p.rho, p.gamma, at<double>(pl, p.o_t),
+              pl->lg.on ? nullptr : at<double>(pl, p.o_fx), at<double>(pl, p.o_check), p.T, p.cost_ncols};
     TRY(put(p.o_coloff, p.col_off.data(), p.col_off.size() * 8));
     TRY(put(p.o_Sd, p.Sd.data(), p.Sd.size() * 8));
     TRY(put(p.o_aw, p.aw.data(), p.aw.size() * 8));
@@ -1579,42 +1591,46 @@ mam_status launch_plan_copy(T* dst, const T* src, const Prob& p, hipStream_t st)
 template <typename T>
 mam_status launch_init(Plan* pl, const void* const* theta0, hipStream_t st) {
   const Layout& L = pl->lay;
+  bool own = true;  // the library's own start in every problem
+  for (size_t i = 0; i < pl->P.size(); ++i) own = own && !(theta0 && theta0[i]);
+  int64_t need = 1, bytes = 0;  // workgroups of the largest problem's fill, bytes of all plans
+  for (const Prob& p : pl->P) {
+    int per = 256;  // columns a workgroup fills at a time, four rows a thread
+    for (int64_t rows = 4; per > 1 && rows < p.R; rows *= 2) per /= 2;
+    need = std::max(need, (p.T + per - 1) / per);
+    bytes += p.ld * p.T * (int64_t)sizeof(T);
+  }
+  const int stream = bytes > ((int64_t)256 << 20);
+  const unsigned wide = (unsigned)std::min<int64_t>(need, std::max<int64_t>(64, 16384 / (int64_t)pl->P.size()));
   for (size_t i = 0; i < pl->P.size(); ++i) {
     Prob& p = pl->P[i];
     if (theta0 && theta0[i]) {
       TRY(launch_plan_copy<T>(static_cast<T*>(p.theta), static_cast<const T*>(theta0[i]), p, st));
-    } else {
+    } else if (!own || pl->lg.on) {
       constexpr int FV = sizeof(T) == 4 ? 4 : 2;
       const bool vec = p.ld % FV == 0 && reinterpret_cast<uintptr_t>(p.theta) % 16 == 0;
-      const int64_t nv = (p.R + (vec ? FV : 1) - 1) / (vec ? FV : 1);
-      int ll = 0;
-      while (ll < 8 && ((int64_t)1 << ll) < nv) ++ll;
-      const int64_t per = 256 >> ll;
-      const int blocks = (int)std::min<int64_t>(16384, std::max<int64_t>(1, (p.T + per - 1) / per));
-      const int stream = p.ld * p.T * (int64_t)sizeof(T) > ((int64_t)256 << 20);
       auto fill = vec ? &mam::fill_kernel<T, FV> : &mam::fill_kernel<T, 1>;
-      hipLaunchKernelGGL(fill, dim3(blocks), dim3(256), 0, st, static_cast<T*>(p.theta), p.ld, (int)p.R,
-                         static_cast<const T*>(p.q), p.T, ll, stream);
+      hipLaunchKernelGGL(fill, dim3(wide), dim3(256), 0, st, static_cast<T*>(p.theta), p.ld, (int)p.R,
+                         static_cast<const T*>(p.q), p.T, stream);
       LAUNCH_CHECK("fill_kernel");
     }
+  }
+  if (pl->lg.on) {
+    Prob& p = pl->P[0];
     hipLaunchKernelGGL(mam::fill_value_kernel, dim3((unsigned)std::min<int64_t>(4096, (p.T + 255) / 256)), dim3(256),
                        0, st, at<double>(pl, p.o_lam), p.T, (double)NAN);
     LAUNCH_CHECK("fill_value_kernel");
-  }
-  if (pl->lg.on) {
     TRY(launch_long_rowsum<T>(pl, st, theta0 && theta0[0]));
     return launch_marginals(pl, st, 0);
   }
   // short columns: the fixed-point accumulators start (and stay, between
   // iterations) at zero; the marginals of the start are plain row sums
-  for (Prob& p : pl->P) {
-    const int64_t n = p.M * p.R;
-    hipLaunchKernelGGL(mam::fill_value_kernel, dim3((unsigned)std::min<int64_t>(4096, (n + 255) / 256)), dim3(256), 0,
-                       st, at<double>(pl, p.o_acc), n, 0.0);
-    LAUNCH_CHECK("fill_value_kernel");
+  for (size_t i = 0; i < pl->P.size(); i += 65535) {
+    hipLaunchKernelGGL(mam::start_kernel<T>, dim3(wide, (unsigned)std::min<size_t>(65535, pl->P.size() - i)), dim3(256),
+                       0, st, at<mam::ProbDev<T>>(pl, L.probdev) + i, at<mam::ProbAux>(pl, L.probaux) + i, own ? 1 : 0,
+                       stream);
+    LAUNCH_CHECK("start_kernel");
   }
-  bool own = true;  // the library's own start in every problem
-  for (size_t i = 0; i < pl->P.size(); ++i) own = own && !(theta0 && theta0[i]);
   if (own) {
     hipLaunchKernelGGL(mam::start_marginal_kernel<T>, dim3((unsigned)pl->meas_p.size()), dim3(256), 0, st,
                        at<mam::ProbDev<T>>(pl, L.probdev), at<mam::ProbAux>(pl, L.probaux), at<int32_t>(pl, L.meas_p),
@@ -1636,26 +1652,42 @@ mam_status launch_init(Plan* pl, const void* const* theta0, hipStream_t st) {
 
 template <typename T>
 mam_status launch_checks(Plan* pl, hipStream_t st) {
-  for (Prob& p : pl->P) {
-    double* chk = at<double>(pl, p.o_check);
-    hipLaunchKernelGGL(mam::zero_kernel, dim3((unsigned)((p.M + 2 + 255) / 256)), dim3(256), 0, st, chk,
-                       (int)(p.M + 2));
-    LAUNCH_CHECK("zero_kernel");
-    hipLaunchKernelGGL(mam::check_q_kernel<T>, dim3((unsigned)p.M), dim3(256), 0, st, static_cast<const T*>(p.q),
-                       at<int64_t>(pl, p.o_coloff), chk, (int)p.M);
-    LAUNCH_CHECK("check_q_kernel");
-    if (p.cost_mode == MAM_COST_GRID) {
-      // the measures' points: cost_ncols rows of gdim doubles
-      const int blocks = (int)std::min<int64_t>(4096, std::max<int64_t>(1, (p.cost_ncols * p.gdim + 255) / 256));
-      hipLaunchKernelGGL(mam::check_cost_kernel<double>, dim3(blocks), dim3(256), 0, st,
-                         static_cast<const double*>(p.cost), (int64_t)p.gdim, p.gdim, p.cost_ncols, chk + p.M + 1);
-    } else {
-      const int blocks = (int)std::min<int64_t>(4096, std::max<int64_t>(1, (p.cost_ncols * p.R + 255) / 256));
-      hipLaunchKernelGGL(mam::check_cost_kernel<T>, dim3(blocks), dim3(256), 0, st, static_cast<const T*>(p.cost),
-                         p.cost_ld, (int)p.R, p.cost_ncols, chk + p.M + 1);
+  const Layout& L = pl->lay;
+  hipLaunchKernelGGL(mam::fill_value_kernel, dim3((unsigned)std::min<size_t>(1024, (L.nchk + 255) / 256)), dim3(256), 0,
+                     st, at<double>(pl, L.chk), (int64_t)L.nchk, 0.0);
+  LAUNCH_CHECK("fill_value_kernel");
+  if (!pl->lg.on) {
+    auto* const probs = at<mam::ProbDev<T>>(pl, L.probdev);
+    auto* const aux = at<mam::ProbAux>(pl, L.probaux);
+    hipLaunchKernelGGL(mam::start_check_kernel<T>, dim3((unsigned)pl->meas_p.size()), dim3(256), 0, st, probs, aux,
+                       at<int32_t>(pl, L.meas_p), at<int32_t>(pl, L.meas_m));
+    LAUNCH_CHECK("start_check_kernel");
+    int64_t need = 1;
+    for (const Prob& p : pl->P) need = std::max(need, (p.cost_ncols * p.R + 255) / 256);
+    const unsigned wide = (unsigned)std::min<int64_t>(need, std::max<int64_t>(32, 4096 / (int64_t)pl->P.size()));
+    for (size_t i = 0; i < pl->P.size(); i += 65535) {
+      hipLaunchKernelGGL(mam::start_cost_kernel<T>, dim3(wide, (unsigned)std::min<size_t>(65535, pl->P.size() - i)),
+                         dim3(256), 0, st, probs + i, aux + i);
+      LAUNCH_CHECK("start_cost_kernel");
     }
-    LAUNCH_CHECK("check_cost_kernel");
+    return MAM_OK;
   }
+  Prob& p = pl->P[0];
+  double* chk = at<double>(pl, p.o_check);
+  hipLaunchKernelGGL(mam::check_q_kernel<T>, dim3((unsigned)p.M), dim3(256), 0, st, static_cast<const T*>(p.q),
+                     at<int64_t>(pl, p.o_coloff), chk, (int)p.M);
+  LAUNCH_CHECK("check_q_kernel");
+  if (p.cost_mode == MAM_COST_GRID) {
+    // the measures' points: cost_ncols rows of gdim doubles
+    const int blocks = (int)std::min<int64_t>(4096, std::max<int64_t>(1, (p.cost_ncols * p.gdim + 255) / 256));
+    hipLaunchKernelGGL(mam::check_cost_kernel<double>, dim3(blocks), dim3(256), 0, st,
+                       static_cast<const double*>(p.cost), (int64_t)p.gdim, p.gdim, p.cost_ncols, chk + p.M + 1);
+  } else {
+    const int blocks = (int)std::min<int64_t>(4096, std::max<int64_t>(1, (p.cost_ncols * p.R + 255) / 256));
+    hipLaunchKernelGGL(mam::check_cost_kernel<T>, dim3(blocks), dim3(256), 0, st, static_cast<const T*>(p.cost),
+                       p.cost_ld, (int)p.R, p.cost_ncols, chk + p.M + 1);
+  }
+  LAUNCH_CHECK("check_cost_kernel");
   return MAM_OK;
 }
 
@@ -1710,20 +1742,13 @@ mam_status resident_workgroups(Plan* pl, bool* changed) {
 constexpr double kSparseMaxCandidates = 48.0;
 
 template <typename T>
-mam_status sparse_decide(Plan* pl, hipStream_t st) {
+mam_status launch_candidates(Plan* pl, hipStream_t st) {
   SparsePlan& sp = pl->sp;
-  sp.use = false;
   if (pl->lg.on || !sp.on) return MAM_OK;
-  double* const stat = at<double>(pl, sp.o_stat);
-  hipLaunchKernelGGL(mam::zero_kernel, dim3(1), dim3(64), 0, st, stat, 1);
-  LAUNCH_CHECK("zero_kernel");
   hipLaunchKernelGGL(mam::candidates_kernel<T>, dim3((unsigned)sp.cand.size()), dim3(256), 0, st,
-                     at<mam::ProbDev<T>>(pl, pl->lay.probdev), at<mam::CandTask>(pl, sp.o_cand), stat);
+                     at<mam::ProbDev<T>>(pl, pl->lay.probdev), at<mam::CandTask>(pl, sp.o_cand),
+                     at<double>(pl, sp.o_stat));
   LAUNCH_CHECK("candidates_kernel");
-  double sum = 0.0;
-  HIP_TRY(hipMemcpyAsync(&sum, stat, 8, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
-  sp.use = sum <= kSparseMaxCandidates * (double)sp.cand.size();
   return MAM_OK;
 }
 
@@ -1751,30 +1776,19 @@ mam_status plan_init(Plan* pl, const void* const* theta0, hipStream_t st) {
   else
     TRY(pl->dtype == MAM_F32 ? resident_workgroups<float>(pl, &rebuilt) : resident_workgroups<double>(pl, &rebuilt));
   if (rebuilt) build_schedule(pl);
-  drop_graphs(pl);
+  // captured iterations hold the tables' places and the schedule: they stay
+  // while neither changes
+  if (!pl->tables_uploaded) drop_graphs(pl);
   TRY(upload_tables(pl, st));
   TRY(pl->dtype == MAM_F32 ? launch_checks<float>(pl, st) : launch_checks<double>(pl, st));
-  TRY(pl->dtype == MAM_F32 ? sparse_decide<float>(pl, st) : sparse_decide<double>(pl, st));
-  std::vector<double> fx;
+  TRY(pl->dtype == MAM_F32 ? launch_candidates<float>(pl, st) : launch_candidates<double>(pl, st));
+  std::vector<double> all(pl->lay.nchk);
+  HIP_TRY(hipMemcpyAsync(all.data(), pl->ws + pl->lay.chk, all.size() * 8, hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  pl->sp.use = !pl->lg.on && pl->sp.on && all.back() <= kSparseMaxCandidates * (double)pl->sp.cand.size();
   for (size_t i = 0; i < pl->P.size(); ++i) {
     Prob& p = pl->P[i];
-    std::vector<double> chk(p.M + 2);
-    HIP_TRY(hipMemcpyAsync(chk.data(), pl->ws + p.o_check, (p.M + 2) * 8, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    if (!pl->lg.on) {
-      // fixed-point scales of the marginal sums: 2^E_m with mass_m <= 2^(62 - E_m),
-      // so no row sum of pi_hat (at most mass_m) exceeds 2^62; then 2^-E_m
-      fx.assign(2 * p.M, 0.0);
-      for (int64_t m = 0; m < p.M; ++m) {
-        int e = 0;
-        if (chk[m] > 0.0 && std::isfinite(chk[m])) std::frexp(chk[m], &e);  // mass = f 2^e, f in [0.5, 1)
-        const int E = std::min(1000, 62 - e);
-        fx[m] = std::ldexp(1.0, E);
-        fx[p.M + m] = std::ldexp(1.0, -E);
-      }
-      HIP_TRY(hipMemcpyAsync(pl->ws + p.o_fx, fx.data(), fx.size() * 8, hipMemcpyHostToDevice, st));
-      HIP_TRY(hipStreamSynchronize(st));  // fx is reused for the next problem
-    }
+    const double* const chk = all.data() + (p.o_check - pl->lay.chk) / 8;
     if (chk[p.M] != 0.0) return fail(MAM_ENONFINITE, "problem %zu: q holds a negative or non-finite weight", i);
     if (chk[p.M + 1] != 0.0) return fail(MAM_ENONFINITE, "problem %zu: cost holds a non-finite entry", i);
     if (std::isinf(p.gamma) && !(p.flags & MAM_FLAG_RELAXED)) {

@@ -295,12 +295,13 @@ damping_kernel(const double* __restrict__ d2part, int nb, double rho, double gam
 // with one per element and a 64-bit division for its place wrote 1.6 GB in
 // 0.70 ms.  Rows past R stay untouched.
 template <typename T, int VEC>
-__global__ void __launch_bounds__(256)
-fill_kernel(T* __restrict__ theta, int64_t ld, int R, const T* __restrict__ q, int64_t T_cols, int lanes_log2,
-            int stream) {
+__device__ __forceinline__ void fill_columns(T* __restrict__ theta, int64_t ld, int R, const T* __restrict__ q,
+                                             int64_t T_cols, int stream, int64_t first, int64_t step) {
+  int lanes_log2 = 0;
+  while (lanes_log2 < 8 && ((1 << lanes_log2) * VEC) < R) ++lanes_log2;
   const int lanes = 1 << lanes_log2, per = 256 >> lanes_log2;
   const int c = threadIdx.x >> lanes_log2, l = threadIdx.x & (lanes - 1);
-  for (int64_t j = (int64_t)blockIdx.x * per + c; j < T_cols; j += (int64_t)gridDim.x * per) {
+  for (int64_t j = first * per + c; j < T_cols; j += step * per) {
     const T v = (T)((double)q[j] / (double)R);
     T* const col = theta + j * ld;
     T x[VEC];
@@ -315,6 +316,34 @@ fill_kernel(T* __restrict__ theta, int64_t ld, int R, const T* __restrict__ q, i
       }
     }
   }
+}
+
+template <typename T, int VEC>
+__global__ void __launch_bounds__(256)
+fill_kernel(T* __restrict__ theta, int64_t ld, int R, const T* __restrict__ q, int64_t T_cols, int stream) {
+  fill_columns<T, VEC>(theta, ld, R, q, T_cols, stream, blockIdx.x, gridDim.x);
+}
+
+// The start of short columns, every problem of a plan at once (blockIdx.y):
+// the library's own plans (fill), no stored thresholds, accumulators at zero.
+// (One launch per problem and array left 256 small problems at 10 ms of
+// initialisation, most of it launches and copies.)
+template <typename T>
+__global__ void __launch_bounds__(256)
+start_kernel(const ProbDev<T>* __restrict__ probs, const ProbAux* __restrict__ aux, int fill, int stream) {
+  const ProbDev<T>& P = probs[blockIdx.y];
+  const ProbAux& A = aux[blockIdx.y];
+  const int64_t n = A.T, first = blockIdx.x * 256ll + threadIdx.x, step = (int64_t)gridDim.x * 256;
+  if (fill) {
+    constexpr int VN = VecOf<T>::N;
+    if (P.ld % VN == 0 && reinterpret_cast<uintptr_t>(P.theta) % 16 == 0)
+      fill_columns<T, VN>(P.theta, P.ld, P.R, P.q, n, stream, blockIdx.x, gridDim.x);
+    else
+      fill_columns<T, 1>(P.theta, P.ld, P.R, P.q, n, stream, blockIdx.x, gridDim.x);
+  }
+  for (int64_t i = first; i < n; i += step) P.lam[i] = __builtin_nan("");
+  const int64_t na = (int64_t)A.M * A.R;
+  for (int64_t i = first; i < na; i += step) A.acc[i] = 0ull;
 }
 
 // The R stored rows of T_cols columns at stride ld, src to dst (padding
@@ -360,23 +389,71 @@ stream_copy_kernel(const f4nt* __restrict__ src, f4nt* __restrict__ dst, int64_t
 // Input validation: per-measure mass of q (fixed order) and a flag for any
 // negative or non-finite weight, or non-finite cost entry.
 template <typename T>
-__global__ void __launch_bounds__(256)
-check_q_kernel(const T* __restrict__ q, const int64_t* __restrict__ col_off, double* __restrict__ out,
-               int M) {
+__device__ __forceinline__ void check_measure(const T* __restrict__ q, int64_t j0, int64_t j1, double* __restrict__ mass,
+                                              double* __restrict__ flag) {
   __shared__ double sh[4];
-  const int m = blockIdx.x;
   double s = 0.0;
   bool bad = false;
-  for (int64_t j = col_off[m] + threadIdx.x; j < col_off[m + 1]; j += 256) {
+  for (int64_t j = j0 + threadIdx.x; j < j1; j += 256) {
     const double v = (double)q[j];
     bad |= !(v >= 0.0) || __builtin_isinf(v);
     s += v;
   }
   s = wave_sum(s);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
-  if (bad) out[M] = 1.0;
+  if (bad) flag[0] = 1.0;
   __syncthreads();
-  if (threadIdx.x == 0) out[m] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+  if (threadIdx.x == 0) mass[0] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+check_q_kernel(const T* __restrict__ q, const int64_t* __restrict__ col_off, double* __restrict__ out,
+               int M) {
+  const int m = blockIdx.x;
+  check_measure<T>(q, col_off[m], col_off[m + 1], out + m, out + M);
+}
+
+// Short columns, every measure of every problem: its mass, and from it the
+// fixed-point scales of its marginal sums: 2^E_m with mass_m <= 2^(62 - E_m),
+// so no row sum of pi_hat (at most mass_m) exceeds 2^62; then 2^-E_m.
+template <typename T>
+__global__ void __launch_bounds__(256)
+start_check_kernel(const ProbDev<T>* __restrict__ probs, const ProbAux* __restrict__ aux,
+                   const int32_t* __restrict__ prob_of, const int32_t* __restrict__ m_of) {
+  const int pi = prob_of[blockIdx.x], m = m_of[blockIdx.x];
+  const ProbDev<T>& P = probs[pi];
+  const ProbAux& A = aux[pi];
+  check_measure<T>(P.q, P.col_off[m], P.col_off[m + 1], A.chk + m, A.chk + A.M);
+  if (threadIdx.x == 0) {
+    const double mass = A.chk[m];
+    int e = 0;
+    if (mass > 0.0 && !__builtin_isinf(mass) && mass == mass) (void)frexp(mass, &e);  // mass = f 2^e, f in [0.5, 1)
+    const int E = 62 - e < 1000 ? 62 - e : 1000;
+    A.fx[m] = ldexp(1.0, E);
+    A.fx[A.M + m] = ldexp(1.0, -E);
+  }
+}
+
+// Short columns: the flag of non-finite costs, every problem (blockIdx.y).
+template <typename T>
+__global__ void __launch_bounds__(256)
+start_cost_kernel(const ProbDev<T>* __restrict__ probs, const ProbAux* __restrict__ aux) {
+  const ProbDev<T>& P = probs[blockIdx.y];
+  const ProbAux& A = aux[blockIdx.y];
+  int lanes_log2 = 0;
+  while (lanes_log2 < 8 && (1 << lanes_log2) < P.R) ++lanes_log2;
+  const int lanes = 1 << lanes_log2, per = 256 >> lanes_log2;
+  bool bad = false;
+  for (int64_t j = (int64_t)blockIdx.x * per + (threadIdx.x >> lanes_log2); j < A.cost_ncols;
+       j += (int64_t)gridDim.x * per) {
+    const T* const c = P.cost + j * P.cost_ld;
+    for (int r = threadIdx.x & (lanes - 1); r < P.R; r += lanes) {
+      const double v = (double)c[r];
+      bad |= !(v == v) || __builtin_isinf(v);
+    }
+  }
+  if (bad) A.chk[A.M + 1] = 1.0;
 }
 
 template <typename T>

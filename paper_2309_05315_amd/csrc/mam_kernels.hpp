@@ -291,6 +291,9 @@ struct ProbAux {
   const double* fxinv;      // M inverse scales 2^-E_m of those sums
   double rho, gamma;
   const double* t;          // t^k of the iteration, as its column kernel formed it
+  double* fx;               // M scales 2^E_m of those sums, then M inverse ones
+  double* chk;              // M masses, then two flags (start_check_kernel)
+  int64_t T, cost_ncols;    // columns, cost columns
 };
 
 struct MargTask {

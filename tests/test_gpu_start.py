@@ -41,3 +41,48 @@ def test_default_start_equals_given_start(R, S, dtype, sched):
     s.iterate(1)
     np.testing.assert_array_equal(a[0], s.theta[:, :R].cpu().numpy())
     np.testing.assert_array_equal(a[1], s.barycenter().cpu().numpy())
+
+
+def test_graphs_outlive_an_init_and_follow_its_inputs():
+    """init() keeps the captured iterations while buffers and schedule stay:
+    new costs and weights in the same buffers, a given start and the default
+    one are followed as by a solver of their own."""
+    a, b = (inputs.tiny_problem(seed, R=130, S=[40, 33, 70], dtype="f64", rho=2.0) for seed in (61, 62))
+    say("case graph over init R=130 f64")
+    s = mam.solver_for(a)
+    s.graph(5)
+    got = []
+    for k, p in enumerate((a, b, a, b)):
+        o = mam.solver_for(p)
+        s.cost.copy_(o.cost)
+        s.q.copy_(o.q)
+        o.init()
+        if k == 2:
+            start = 0.5 * o.theta
+            o.init(start)
+            s.init(start)
+        else:
+            s.init()
+        for x in (s, o):
+            x.iterate(13)
+        np.testing.assert_array_equal(s.theta.cpu().numpy(), o.theta.cpu().numpy())
+        np.testing.assert_array_equal(s.barycenter().cpu().numpy(), o.barycenter().cpu().numpy())
+        got.append(s.barycenter().cpu().numpy())
+        o.close()
+    assert not np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("bad", ["weight", "cost", "mass"])
+def test_batch_refuses_a_bad_problem_by_its_number(bad):
+    """The checks of all problems in one launch name the problem at fault."""
+    probs = [inputs.tiny_problem(70 + i, R=9 + 60 * i, S=[5, 30 + i], dtype="f32") for i in range(5)]
+    p = probs[3]
+    if bad == "weight":
+        p.q[2] = -1e-3
+    elif bad == "cost":
+        p.cost.flat[-1] = np.inf
+    else:
+        p.q[:5] *= 1.5
+    say(f"case bad {bad}")
+    with pytest.raises(mam.MAMError, match="problem 3"):
+        mam.Batch(probs).init()
