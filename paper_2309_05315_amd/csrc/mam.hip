@@ -131,6 +131,7 @@ struct Layout {
   size_t chk = 0, nchk = 0;       // what init reads back
   size_t meas_p = 0, meas_m = 0;  // every measure's problem and number
   size_t stop = 0, stop_part = 0;  // stopping-test state and row-block partials
+  size_t extra = 0;  // of the total, what no solve needs to be taken (mam_solve_static)
   size_t total = 0;
 };
 
@@ -809,8 +810,13 @@ void build_layout(Plan* pl) {
   L.probaux = take(pl->P.size() * sizeof(mam::ProbAux));
   L.mtasks = take(pl->mtasks.size() * sizeof(mam::MargTask));
   L.atasks = take(pl->atasks.size() * sizeof(mam::AvgTask));
-  L.meas_p = take(nmeas * 4);
-  L.meas_m = take(nmeas * 4);
+  L.extra = 0;
+  size_t before = o;
+  if (!pl->lg.on) {
+    L.meas_p = take(nmeas * 4);
+    L.meas_m = take(nmeas * 4);
+    L.extra += o - before;
+  }
   L.stop = take(sizeof(mam::StopState));
   L.stop_part = take((size_t)pl->P[0].nb * 8);
   if (pl->lg.on) {
@@ -829,7 +835,8 @@ void build_layout(Plan* pl) {
     lg.o_hcnt = take(nh * 4);
     lg.o_crow = take(nh * (size_t)lg.cap * 4);
     lg.o_cw = take(nh * (size_t)lg.cap * 8);
-    lg.sparse = (pl->P[0].flags & MAM_FLAG_SPARSE_STORE) != 0;
+    // (sp.off: no room for what follows; the dense store gives the same bits)
+    lg.sparse = (pl->P[0].flags & MAM_FLAG_SPARSE_STORE) != 0 && !pl->sp.off;
     if (lg.sparse) {
       const size_t eb = elem_bytes(pl->dtype);
       lg.o_pcnt = take(nh * 4);
@@ -837,20 +844,26 @@ void build_layout(Plan* pl) {
       lg.o_pval = take(nh * (size_t)lg.cap * eb);
       lg.o_nbv = take(2 * (size_t)pl->P[0].M * (size_t)pl->P[0].R * eb);
       lg.o_spar = take(12);
-      lg.o_cmin = take((size_t)lg.nrb * 4 * (size_t)pl->P[0].cost_ncols * eb);
+    }
+    // The scan's tables of the sparse store, a few per cent of the slots in
+    // use, are part of every long plan: the flag adds the patch slots alone.
+    if (!pl->sp.off) {
+      before = o;
+      const size_t eb = elem_bytes(pl->dtype), M = (size_t)pl->P[0].M, nsub = (size_t)lg.nrb * 4;
+      const size_t nword = nsub * ((T + 63) / 64), nslot = M * (size_t)lg.rows * (size_t)lg.nrb;
+      lg.o_cmin = take(nsub * (size_t)pl->P[0].cost_ncols * eb);
       lg.o_limit = take(T * 8);
       lg.o_wit = take(T * 4);
-      lg.o_smask = take(T * (size_t)((lg.nrb * 4 + 63) / 64) * 8);
-      const size_t nword = (size_t)lg.nrb * 4 * ((T + 63) / 64);
+      lg.o_colm = take(T * 4);
+      lg.o_smask = take(T * ((nsub + 63) / 64) * 8);
       lg.o_gmask = take(nword * 8);
       lg.o_wsub = take(nword * (64 / mam::kScanCols) * 4);
       lg.o_wgrp = take(nword * (64 / mam::kScanCols) * 4);
       lg.o_wcol = take(nword * (64 / mam::kScanCols) * 8);
-      lg.o_colm = take(T * 4);
-      const size_t nslot = (size_t)pl->P[0].M * (size_t)lg.nrb * (size_t)lg.vpt * mam::LNT;
       lg.o_b2v = take(nslot * 8);
       lg.o_basev = take(nslot * 8);
-      lg.o_bmax = take((size_t)pl->P[0].M * (size_t)lg.nrb * 4 * 8);
+      lg.o_bmax = take(M * nsub * 8);
+      L.extra += o - before;
     }
   }
   SparsePlan& sp = pl->sp;
@@ -2912,7 +2925,9 @@ mam_status plan_support_update(Plan* pl, const double* alpha, const double* zeta
 // only that pointer is ever handed to kernels or copies.
 // ---------------------------------------------------------------------------
 constexpr size_t kStaticScratchBytes = size_t(128) << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// room for the tables of every measure's start beyond that (Layout::extra)
+constexpr size_t kStaticExtraBytes = size_t(1) << 20;
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticExtraBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -3232,14 +3247,16 @@ mam_status mam_solve_static(const mam_desc* d, void* theta, const void* cost, co
   // the handle lives for this call only; the kernels queued on 'stream'
   // read only the caller's buffers and the static workspace, which outlive it
   std::unique_ptr<mam_problem, void (*)(mam_problem*)> h(raw, mam_destroy);
-  if (mam_workspace_bytes(h.get()) > kStaticScratchBytes) {
-    // the sparse iterations' tables may be what does not fit: dense then
+  size_t need = mam_workspace_bytes(h.get());
+  const bool fits = !h->plan.lg.on || need - h->plan.lay.extra <= kStaticScratchBytes;
+  if (fits && need > kStaticScratchBytes) {
+    // the tables of the sparse iterations may be what does not fit: dense then
     h->plan.sp.off = true;
     build_schedule(&h->plan);
     build_layout(&h->plan);
+    need = mam_workspace_bytes(h.get());
   }
-  const size_t need = mam_workspace_bytes(h.get());
-  if (need > kStaticScratchBytes)
+  if (!fits || need - h->plan.lay.extra > kStaticScratchBytes || need > kStaticScratchBytes + kStaticExtraBytes)
     return fail(MAM_ENOMEM, "this problem needs %zu bytes of workspace; the static workspace holds %zu",
                 need, kStaticScratchBytes);
   void* ws = nullptr;

@@ -962,8 +962,7 @@ constexpr int kSpNone = 0, kSpFirst = 1, kSpNext = 2;
 // 0 sums p and d^2 in the order m = 0, 1, ... from LDS (every wave summing p
 // by itself read 16 times as much LDS, and the divisions of d^2 were one
 // wave's: 8.8 us at 1024 rows and 50 measures with a finite gamma, 7.2 us now).
-// upd: null, or per measure how
-// the iteration updated it.
+// upd: null, or per measure how the iteration updated it.
 template <typename T>
 __global__ void __launch_bounds__(1024)
 sparse_close_kernel(const SpProb<T>* __restrict__ probs, const SpRows* __restrict__ tasks, int save_prev,
