@@ -15,8 +15,9 @@ workload on the long-column path, the reverse mode) are reported under
 "extras".
 
 Prints one JSON line:  metric, value (plan-entry updates per second), the
-roofline of the dominant kernel (the column kernel, timed with HIP events on
-the launch stream), the FP64 run and the oracle's CPU rate on a bounded
+roofline of the column kernel (timed with HIP events on the launch stream, in
+calls of one iteration, which read and write the plans whole; longer calls
+keep them as -b plus their active entries in between), the FP64 run and the oracle's CPU rate on a bounded
 sample of the same workload.
 
     python bench.py [--gpus 1] [--steps 500] [--warmup 10] [--no-cpu]
@@ -64,6 +65,23 @@ def algorithmic_bytes(p) -> int:
     return eb * (2 * p.R * p.T + p.R * p.distinct_cost_columns() + p.T)
 
 
+def column_times(s, n):
+    """Average duration (ms) of the column kernels of n iterations: of calls
+    of one iteration, whose kernel reads and writes the whole plans, and of
+    one call of n, which keeps the plans as -b plus their active entries after
+    its first iteration (where the plans are large enough and sparse)."""
+    s.timing(True)
+    for _ in range(n):
+        s.iterate(1)
+    dense, nd = s.timing_read()
+    s.timing(False)
+    s.timing(True)
+    s.iterate(n)
+    call, nc = s.timing_read()
+    s.timing(False)
+    return dense / max(nd, 1), call / max(nc, 1), nd
+
+
 def run_gpu(p, steps, warmup, torch, mam):
     s = mam.solver_for(p, device="cuda:0")
     s.init()
@@ -75,16 +93,13 @@ def run_gpu(p, steps, warmup, torch, mam):
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
     pbar = s.barycenter().cpu().numpy()
-    # dominant-kernel duration: HIP events around every column-kernel launch
-    s.timing(True)
-    s.iterate(min(steps, 100))
-    col_ms, n = s.timing_read()
-    s.timing(False)
+    # column-kernel durations: HIP events around every launch
+    col_ms, call_ms, n = column_times(s, min(steps, 100))
     sched = s.schedule()
     s.close()
     del s
     torch.cuda.empty_cache()
-    return dt, pbar, col_ms / max(n, 1), n, sched
+    return dt, pbar, col_ms, call_ms, n, sched
 
 
 def final_state(p, iters, torch, mam, relaxed=False):
@@ -289,10 +304,8 @@ def extra_workloads(torch, mam, inputs, log, only=None):
         s.init()
         s.iterate(10)
         dt = timed(lambda: s.iterate(p3.iters)) / p3.iters
-        s.timing(True)
-        s.iterate(100)
-        col, n = s.timing_read()
-        s.timing(False)
+        col, call, n = column_times(s, 100)
+        col *= n
         # the same iterations replayed from a captured graph (50 per launch)
         s.graph(50)
         s.init()
@@ -336,10 +349,8 @@ def extra_workloads(torch, mam, inputs, log, only=None):
         s.init()
         s.iterate(10)
         dt = timed(lambda: s.iterate(n_it)) / n_it
-        s.timing(True)
-        s.iterate(100)
-        col, n = s.timing_read()
-        s.timing(False)
+        col, call, n = column_times(s, 100)
+        col *= n
         s.init()
         s.iterate(n_it)
         pb = s.barycenter().cpu().numpy()
@@ -378,7 +389,8 @@ def extra_workloads(torch, mam, inputs, log, only=None):
         dt = timed(lambda: b.iterate(iters4)) / iters4
         b.graph(0)
         b.timing(True)
-        b.iterate(50)
+        for _ in range(50):  # the whole plans every time
+            b.iterate(1)
         col, n = b.timing_read()
         b.close()
         ab = sum(algorithmic_bytes(p) for p in probs)
@@ -609,26 +621,27 @@ def main():
 
     p32 = inputs.balanced_sparse(dtype="f32")
     log(f"workload {p32.name}: R={p32.R} M={p32.M} T={p32.T} S in [{min(p32.S)}, {max(p32.S)}]")
-    dt32, pb32, col_ms32, ncol, sched = run_gpu(p32, args.steps, args.warmup, torch, mam)
+    dt32, pb32, col_ms32, call_ms32, ncol, sched = run_gpu(p32, args.steps, args.warmup, torch, mam)
     entries = p32.R * p32.T
     value = entries * args.steps / dt32
     ab = algorithmic_bytes(p32)
     achieved = ab / (col_ms32 * 1e-3) / 1e9
-    log(f"fp32: {dt32 / args.steps * 1e3:.4f} ms/iter, column kernel {col_ms32:.4f} ms, "
-        f"{achieved:.0f} GB/s algorithmic, schedule {sched}")
+    log(f"fp32: {dt32 / args.steps * 1e3:.4f} ms/iter, column kernel {col_ms32:.4f} ms on the whole "
+        f"plans ({achieved:.0f} GB/s algorithmic), {call_ms32:.4f} ms on average in a call, schedule {sched}")
     state32 = final_state(p32, args.warmup + args.steps, torch, mam)
     log(f"fp32 state after {state32['iterations']} iterations: {state32}")
 
     fp64 = None
     if not args.no_fp64:
         p64 = inputs.balanced_sparse(dtype="f64")
-        dt64, pb64, col_ms64, _, sched64 = run_gpu(p64, args.steps, args.warmup, torch, mam)
+        dt64, pb64, col_ms64, call_ms64, _, sched64 = run_gpu(p64, args.steps, args.warmup, torch, mam)
         ab64 = algorithmic_bytes(p64)
         state64 = final_state(p64, args.warmup + args.steps, torch, mam)
         fp64 = {
             "value": entries * args.steps / dt64,
             "ms_per_step": dt64 / args.steps * 1e3,
             "column_kernel_ms": col_ms64,
+            "column_kernel_ms_in_a_call": call_ms64,
             "achieved_GBs": ab64 / (col_ms64 * 1e-3) / 1e9,
             "fp32_speedup": dt64 / dt32,
             "barycenter_rel_l1_fp32_vs_fp64": float(np.abs(pb32 - pb64).sum() / np.abs(pb64).sum()),
@@ -686,7 +699,9 @@ def main():
                      "traffic_source": traffic_note,
                      "measured_copy_GBs": copy_gbs, "frac_of_measured_copy": achieved / copy_gbs,
                      "copy_probe": copy,
-                     "avg_launch_ms": col_ms32, "launches_timed": ncol},
+                     "avg_launch_ms": col_ms32, "launches_timed": ncol,
+                     "launch": "calls of one iteration: the plans read and written whole",
+                     "avg_launch_ms_in_a_call": call_ms32},
         "fp64": fp64,
         "cpu_baseline": cpu,
         "cpu_baseline_parallel": cpu_par,

@@ -253,7 +253,9 @@ mam_status mam_bind(mam_problem* p, void* theta, const void* cost,
 mam_status mam_init(mam_problem* p, const void* theta0, void* stream);
 
 /* Run 'iters' >= 0 deterministic MAM iterations (M^k = all measures,
- * Alg. 1).  Asynchronous.  Errors: MAM_ESTATE before mam_init. */
+ * Alg. 1).  Asynchronous; theta holds the plans when the call's work is done
+ * (between its iterations they may be kept in the workspace, as -b^(m) plus
+ * their active entries).  Errors: MAM_ESTATE before mam_init. */
 mam_status mam_iterate(mam_problem* p, int64_t iters, void* stream);
 
 /* Grid of a MAM_COST_GRID problem (Theorem c: with measures on one grid and
