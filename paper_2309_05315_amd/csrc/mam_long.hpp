@@ -44,7 +44,7 @@
 //
 // Ten 40 x 40 images (R = 152,881, 16,000 columns, FP32), per iteration:
 // scanning every sub-tile 2.9 ms scan, 0.24 ms threshold, 0.28 ms write; now
-// 13 us base, 41 us limit, 90 us scan, 34 us threshold, 45 us write.  About
+// 13 us base, 41 us limit, 71 us scan, 32 us threshold, 45 us write.  About
 // three of a column's 152 sub-tiles are scanned, two of them for their
 // patches.  20 iterations of a call: 63 -> 14.5 ms, of which 7.8 ms are the
 // start's fill, the first scan and the write-back: 9.8 GB each.
