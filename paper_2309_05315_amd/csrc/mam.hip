@@ -1883,7 +1883,8 @@ mam_status launch_sparse_close(Plan* pl, int save_prev, const uint8_t* upd, int 
                      pl->gate);
   LAUNCH_CHECK("sparse_close_kernel");
   if (sp.finite) {
-    hipLaunchKernelGGL(fn.next, dim3((unsigned)sp.rows.size()), dim3(64 * waves), 0, st,
+    hipLaunchKernelGGL(fn.next, dim3((unsigned)sp.rows.size(), (unsigned)((sp.mmax + waves - 1) / waves)),
+                       dim3(64 * waves), 0, st,
                        at<mam::SpProb<T>>(pl, sp.o_probs), at<mam::SpRows>(pl, sp.o_rows), upd, mode, pl->gate);
     LAUNCH_CHECK("sparse_next_kernel");
   }

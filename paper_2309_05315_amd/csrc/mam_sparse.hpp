@@ -1073,7 +1073,10 @@ sparse_close_kernel(const SpProb<T>* __restrict__ probs, const SpRows* __restric
 
 // The last part of the close of problems with a finite gamma: t^{k+1} needs
 // every block's part of d^2, so it is a launch of its own; it also publishes
-// t^{k+1}.  Same workgroups as the close kernel.
+// t^{k+1}.  The measures of a block are dealt over gridDim.y workgroups, one
+// measure to a wave: with all of them in one workgroup, as in the close
+// kernel, a wave took four in turn and 1024 rows x 50 measures 6.4 us on 16
+// workgroups (4.2 us now).
 template <typename T>
 __global__ void __launch_bounds__(1024)
 sparse_next_kernel(const SpProb<T>* __restrict__ probs, const SpRows* __restrict__ tasks,
@@ -1093,14 +1096,14 @@ sparse_next_kernel(const SpProb<T>* __restrict__ probs, const SpRows* __restrict
   const int rr = in ? r : R - 1;
   const ConstPtr<double> Sd = cptr(P->Sd);
   const double pr = gptr(P->p)[rr];
-  for (int m = wv; m < M; m += W) {
+  for (int m = (int)blockIdx.y * W + wv; m < M; m += W * (int)gridDim.y) {
     const bool reset = mode != kSpNext || (upd != nullptr && upd[m] == 2);
     const double b = t * (pr - gptr(P->pm)[(int64_t)m * R + rr]) / Sd[m];
     sparse_next<T>(P, m, blk, lane, in, b, (double)gptr(P->nbv)[(int64_t)m * Rp + rr],
                    gptr(P->bb)[(int64_t)m * Rp + rr], rpar ^ 1, reset);
     if (blk == 0) sparse_absorb<T>(P, m, lane, rpar, reset);
   }
-  if (blk == 0 && threadIdx.x == 0) {
+  if (blk == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     gptr(P->par)[1] = rpar ^ 1;
     gptr(P->t_out)[1] = t;
   }

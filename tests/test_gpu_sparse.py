@@ -178,3 +178,14 @@ def test_bundles(dtype, gamma):
         res.append(state(s))
         s.close()
     same(*res)
+
+
+@pytest.mark.parametrize("dtype,M", [("f32", 16), ("f64", 17), ("f32", 33), ("f32", 95)])
+def test_measures_over_several_workgroups(dtype, M):
+    """With a finite gamma the second part of the close deals a block's
+    measures over workgroups of 16: one workgroup, one measure in the second,
+    several, the most that the sparse iterations take."""
+    rng = np.random.default_rng(M)
+    S = [int(x) for x in rng.integers(1, 3 * 5_400_000 // (130 * 4 * M) + 30, size=M)]
+    p = inputs.tiny_problem(80 + M, R=130, S=S, dtype=dtype, rho=1.0, masses=list(rng.uniform(0.5, 1.5, M)), gamma=0.05)
+    same(*both(p, 11))
