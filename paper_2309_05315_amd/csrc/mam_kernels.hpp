@@ -937,6 +937,9 @@ column_kernel(ColArgs<T> a) {
         for (int kc = 0; kc < KC; ++kc) {
           if (!act[kc]) continue;
           ++nrounds[kc];
+          // (the entries of mask: with some exactly at the threshold the
+          // rounds may alternate between two sets until the last one)
+          if constexpr (SPARSE) nact[kc] = n[kc];
           if (n[kc] == 0) {
             if (cold[kc]) {
               // start from the exact lower bound w_max - tau

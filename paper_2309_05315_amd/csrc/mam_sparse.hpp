@@ -34,9 +34,10 @@
 //    last drift) are evaluated too: a V taken from their bound would open the
 //    column again at once.  The minima of every cost column are taken once
 //    per call (cost_min_kernel), the maxima of base by the close kernel.
-//  * A column with more than kPatch candidates is taken by a whole wave over
-//    all its rows, and stored dense in theta while it has more than kPatch
-//    active entries (count -1).
+//  * A column with more than kPatch candidates, or with an entry at its
+//    threshold (kTie), is taken by a whole wave over all its rows, in the
+//    column kernel's rounds from its stored threshold, and stored dense in
+//    theta while it has more than kPatch active entries (count -1).
 //
 // What bounds it: a column costs some 40 bytes (q, V, count, one patch, a
 // cost and a b) where a dense iteration streams R rows of theta twice and of
@@ -271,6 +272,24 @@ __device__ __forceinline__ double shfl_d(double v, int src) {
   return __hiloint2double(__shfl(__double2hiint(v), src), __shfl(__double2loint(v), src));
 }
 
+// Entries at the threshold.  With w_r = lambda within rounding the set that a
+// threshold is formed over is not unique: the column kernel's depends on the
+// round that settled the column, and with it the last bit of lambda (and the
+// recorded set).  On data of few binary digits (integer costs, equal weights)
+// such bits decide where mass goes, so these columns are left to the whole
+// wave, which repeats the column kernel's rounds.  Everywhere else the set is
+// unique and its sum, taken in the column kernel's order, gives the same bits.
+// The margin covers the rounding of a sum of kPatch entries within tau of
+// lambda.  The largest entry is always in the set, unless lambda = w_max - tau
+// rounds to w_max; it is 0 then either way, and it is in the recorded set only
+// if the float bounds of the column kernel's certificate hold with equality.
+constexpr double kTie = 0x1p-46;
+template <bool REC>
+__device__ __forceinline__ bool is_tie(int near, double top, double lam, double tau) {
+  if (near > (top - lam <= (fabs(lam) + tau) * kTie ? 1 : 0)) return true;
+  return REC && top == lam && (double)(float)top == top;
+}
+
 // Entries of a thread that a whole wave takes at a time (a thread of the
 // column kernel holds up to 16; 8 keep the kernel at 128 registers, four
 // waves per SIMD).
@@ -374,7 +393,11 @@ sparse_column_kernel(SpArgs<T> a) {
     if (lo > lam) lam = (sum3(w[0], row[0], w[1], row[1], w[2], row[2], ntl, vecl) - tau) / 3.0;
   }
   const double lout = relaxed ? max_arith(lam, 0.0) : lam;
-  const bool ok = lanes_take && vg + G + (fabs(vg) + fabs(G) + fabs(lam)) * 0x1p-46 <= lout;
+  int near = 0;  // entries that the threshold may or may not have met, by its rounding
+#pragma unroll
+  for (int k = 0; k < NL; ++k) near += fabs(w[k] - lam) <= (fabs(lam) + tau) * kTie ? 1 : 0;
+  const bool ok = lanes_take && !is_tie<REC>(near, hi, lam, tau) &&
+                  vg + G + (fabs(vg) + fabs(G) + fabs(lam) + tau) * kTie <= lout;
   unsigned long long open = __ballot(have && cnt != 0 && !ok);
   if (have && ok) {
     bool in[NL];
@@ -563,11 +586,11 @@ sparse_column_kernel(SpArgs<T> a) {
     const double lcr = relaxed ? max_arith(lc, 0.0) : lc;
     // a column that is here for its many patches only
     const double vgs = shfl_d(vg, src);
-    const bool settled = many && vgs + G + (fabs(vgs) + fabs(G) + fabs(lc)) * 0x1p-46 <= lcr;
+    const bool settled = many && vgs + G + (fabs(vgs) + fabs(G) + fabs(lc) + tq) * kTie <= lcr;
     const bool look = live && !settled;
     // entries this far below the candidates' threshold cannot be active (the
     // margin covers the rounding of a threshold over a larger set)
-    double lim = lcr - (fabs(lcr) + tq) * 0x1p-46;
+    double lim = lcr - (fabs(lcr) + tq) * kTie;
 
     // w of a lane's four rows of block blk; patched rows and rows past the
     // end as -inf
@@ -615,7 +638,7 @@ sparse_column_kernel(SpArgs<T> a) {
       const double gm = row16_reduce<OpMaxA>(max_arith(max_arith(x[0], x[1]), max_arith(x[2], x[3])));
       double l1 = gm - tq;
       if (relaxed) l1 = max_arith(l1, 0.0);
-      if (fresh && l1 > lcr) lim = l1 - (fabs(l1) + tq) * 0x1p-46;
+      if (fresh && l1 > lcr) lim = l1 - (fabs(l1) + tq) * kTie;
     }
 
     // blocks to evaluate: by their bound, and those with a patch (their bound
@@ -740,7 +763,11 @@ sparse_column_kernel(SpArgs<T> a) {
       const double S = lw[0];
       if (tree) lm = (S - tq) / (double)total;
     }
-    if (live) {
+    const double top = row16_reduce<OpMaxA>(cand ? ew : -__builtin_huge_val());
+    const unsigned near = group_bits(cand && fabs(ew - lm) <= (fabs(lm) + tq) * kTie);
+    const bool tie = live && is_tie<REC>(__popc(near), top, lm, tq);
+    whole |= columns_where(mine, tie);
+    if (live && !tie) {
       const double lo16 = relaxed ? max_arith(lm, 0.0) : lm;
       const bool in = cand && (relaxed ? ew > lo16 : ((set >> l) & 1u) != 0u);
       unsigned bits = group_bits(in);
@@ -753,7 +780,6 @@ sparse_column_kernel(SpArgs<T> a) {
       }
       if (bits == 0u) {
         // nothing active: the largest entry stays as a witness (pi_hat = 0)
-        const double top = row16_reduce<OpMaxA>(cand ? ew : -__builtin_huge_val());
         const unsigned eq = group_bits(cand && ew == top);
         bits = eq & (0u - eq);
         if (bits == 0u) bits = 1u;
@@ -821,57 +847,81 @@ sparse_column_kernel(SpArgs<T> a) {
         x[i] = rx[i] >= 0 ? __builtin_fma(-(double)cv[i], inv_rho, t + 2.0 * bx[i]) : -__builtin_huge_val();
       }
     };
-    double best = -__builtin_huge_val();
-    int brow = 0;
-    for (int v = 0; v < nwave; ++v)
-      for (int k0 = 0; k0 < vpt; k0 += KW) {
-        rows_of(v, k0);
-#pragma unroll
-        for (int i = 0; i < KW; ++i)
-          if (x[i] > best) {
-            best = x[i];
-            brow = rx[i];
-          }
-      }
-    const double top = wave_reduce<OpMaxA>(best);
-    const unsigned long long eq = __ballot(best == top);
-    brow = __builtin_amdgcn_readlane(brow, eq ? __builtin_ctzll(eq) : 0);
-    double lset = top - tq, lm = lset;  // lset: the bound whose set gives lm
-    int last = -1, na = 0;
-    auto count = [&](double bound, double* sum) -> int {
-      double S = 0.0;
+    // one round of the column kernel: the entries above bound, their sum in
+    // its order, the least of them and the largest of the others
+    auto count = [&](double bound, double* sum, double* least, double* most) -> int {
+      double S = 0.0, lo = __builtin_huge_val(), hi = -__builtin_huge_val();
       int c = 0;
       for (int v = 0; v < nwave; ++v) {
         double y = 0.0;
         for (int k0 = 0; k0 < vpt; k0 += KW) {
           rows_of(v, k0);
 #pragma unroll
-          for (int i = 0; i < KW; ++i)
-            if (x[i] > bound) {
-              y += x[i];
-              ++c;
-            }
+          for (int i = 0; i < KW; ++i) {
+            const bool in = x[i] > bound;
+            y += in ? x[i] : 0.0;
+            c += in ? 1 : 0;
+            lo = fmin(lo, in ? x[i] : __builtin_huge_val());
+            hi = fmax(hi, in ? -__builtin_huge_val() : x[i]);
+          }
         }
         S += wave_reduce<OpSum>(y);
       }
       for (int o = 32; o; o >>= 1) c += __shfl_xor(c, o);
       *sum = S;
+      *least = wave_reduce<OpMin>(lo);
+      *most = wave_reduce<OpMax>(hi);
       return uniform_i(c);
     };
-    double S;
+    // its rounds, from the stored threshold (lset: the bound whose set, of na
+    // entries, gives lm).  A round depends on lm and the last count alone, so
+    // one that finds both as they were two rounds ago starts a cycle of two,
+    // and an even number of rounds can be left out.
+    double lm = uniform_d(lamv[jj]), lset = lm, lm1 = lm, lm2 = __builtin_nan(""), S, least, most;
+    int na = 0, last = -1, last1 = -1, last2 = -2;
     for (int it = 0; it < R + 4; ++it) {
-      na = count(lm, &S);
-      if (na == 0) break;
+      if (lm == lm2 && last == last2) it += (R + 3 - it) & ~1;
+      lm2 = lm1;
+      last2 = last1;
+      lm1 = lm;
+      last1 = last;
+      na = count(lm, &S, &least, &most);
+      if (na == 0) {
+        if (lm != lm) {
+          lm = most - tq;
+          last = 0x7fffffff;
+        } else if (last < 0) {
+          lm = __builtin_nan("");
+        } else {
+          break;
+        }
+        continue;
+      }
       lset = lm;
       lm = (S - tq) / (double)na;
-      if (na == last) break;
+      if (na == last || ((double)float_down(least) >= lm && (double)float_up(most) <= lm)) break;
       last = na;
     }
     double lo2 = lm;
     if (relaxed) {
-      lo2 = max_arith(lm, 0.0);
-      lset = lo2;
-      na = count(lset, &S);
+      lset = lo2 = max_arith(lm, 0.0);
+      na = count(lset, &S, &least, &most);
+    }
+    int brow = 0;  // nothing active: a row of the largest w stays as a witness
+    if (na == 0) {
+      double best = -__builtin_huge_val();
+      for (int v = 0; v < nwave; ++v)
+        for (int k0 = 0; k0 < vpt; k0 += KW) {
+          rows_of(v, k0);
+#pragma unroll
+          for (int i = 0; i < KW; ++i)
+            if (x[i] > best) {
+              best = x[i];
+              brow = rx[i];
+            }
+        }
+      const unsigned long long eq = __ballot(best == wave_reduce<OpMaxA>(best));
+      brow = __builtin_amdgcn_readlane(brow, eq ? __builtin_ctzll(eq) : 0);
     }
     // the new values; a row's w is formed before its value is stored
     int pos = 0;

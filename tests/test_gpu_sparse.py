@@ -189,3 +189,40 @@ def test_measures_over_several_workgroups(dtype, M):
     S = [int(x) for x in rng.integers(1, 3 * 5_400_000 // (130 * 4 * M) + 30, size=M)]
     p = inputs.tiny_problem(80 + M, R=130, S=S, dtype=dtype, rho=1.0, masses=list(rng.uniform(0.5, 1.5, M)), gamma=0.05)
     same(*both(p, 11))
+
+
+def dyadic_problem(K, M, S, levels, dtype="f64", rho=1024.0):
+    """M measures on S pixels each of a K x K grid, integer costs and weights
+    of a few binary digits: many entries of w lie exactly at a column's
+    threshold, or miss it by the rounding of one quotient."""
+    rng = np.random.default_rng(5)
+    R = K * K
+    pts = inputs.grid_points(K) * K
+    cols = np.concatenate([np.sort(rng.permutation(R)[:S]) for _ in range(M)])
+    q = np.concatenate([np.bincount(rng.integers(0, S, levels * S), minlength=S) for _ in range(M)]) / (512.0 * levels)
+    return inputs.Problem(name=f"dyadic_K{K}_M{M}_S{S}", R=R, S=[S] * M, cost=np.rint(inputs.sq_euclid(pts, pts)), q=q,
+                          dtype=dtype, iters=20, rho=rho, col_index=cols.astype(np.int32))
+
+
+@pytest.mark.parametrize("K,M,S,levels", [(26, 8, 512, 4), (26, 8, 512, 8), (24, 8, 576, 4), (32, 3, 1024, 16)])
+def test_entries_at_the_threshold(K, M, S, levels):
+    """Which of them a threshold is formed over decides its last bit, and on
+    such data the last bits decide where mass goes."""
+    for iters in (12, 40):
+        same(*both(dyadic_problem(K, M, S, levels), iters))
+
+
+def test_recorded_sets_at_the_threshold():
+    """A recorded set that takes in an entry at the threshold, or leaves it
+    out, changes the gradient by a whole part of it."""
+    p = dyadic_problem(26, 8, 512, 4)
+    g = torch.linspace(-1, 1, p.R, dtype=torch.float64, device="cuda") ** 2
+    grads = []
+    for ck in (0, 9, 1):
+        s = mam.solver_for(p)
+        s.init()
+        s.record(30, ck)
+        grads.append([x.cpu().numpy() for x in s.backward(g)])
+        s.close()
+    for other in grads[1:]:
+        same(grads[0], other)
