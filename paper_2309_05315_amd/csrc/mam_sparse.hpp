@@ -22,8 +22,9 @@
 //    V = the largest w outside C when the column was last looked at; since
 //    then each w of the measure rose by at most the sum of the iterations'
 //    largest rises of base (drift G_m, kept by the close kernel), so
-//    V + (G_now - G_then) bounds them all.  (Rounding enters only at the two
-//    ends; a margin of 2^-46 of the magnitudes covers it and the sums'.)
+//    V + (G_now - G_then) bounds them all.  (Every sum G is rounded up, so a
+//    call of any length keeps the bound; a margin of 2^-46 of the magnitudes
+//    covers the rounding at the two ends.)
 //    Base moves slowly, so few columns per iteration (1-3% after the first
 //    tens of iterations on the 64x64 workload) are looked at again.
 //  * In space, 16 lanes per open column, four columns per wave.  Over a block
@@ -128,6 +129,15 @@ using ConstPtr = const __attribute__((address_space(4))) U*;
 template <typename U>
 __device__ __forceinline__ ConstPtr<U> cptr(const U* p) {
   return (ConstPtr<U>)(uint64_t)p;
+}
+
+// A measure's rises so far plus the next one, no less than the exact sum: the
+// rise is a rounded difference, and the sum is rounded too (late in a run
+// rises are below half an ulp of G, and rounded to nearest they would all be
+// lost).  The kernels that form it use this one expression.
+__device__ __forceinline__ double drift_sum(double g, double rise) {
+  const double s = g + (rise + fabs(rise) * 0x1p-40);
+  return s + fabs(s) * 0x1p-52;
 }
 
 // Maxima of results of arithmetic: one instruction each (max_arith).
@@ -379,8 +389,7 @@ sparse_column_kernel(SpArgs<T> a) {
     }
   }
   delta = wave_reduce<OpMaxA>(delta);
-  delta += fabs(delta) * 0x1p-40;
-  const double G = G0 + delta;
+  const double G = drift_sum(G0, delta);
   // threshold of the patches alone
   double hi = max_arith(w[0], w[1]), mid = fmin(w[0], w[1]);
   const double lo2 = fmin(hi, w[2]);
@@ -996,8 +1005,7 @@ __device__ __forceinline__ void sparse_absorb(const ConstPtr<SpProb<T>> P, int m
   double d = lane < P->nblk ? dr[lane] : -__builtin_huge_val();
   if (lane + 64 < P->nblk) d = fmax(d, dr[lane + 64]);
   d = wave_reduce<OpMax>(d);
-  d += fabs(d) * 0x1p-40;
-  if (lane == 0) gptr(P->G)[m] = reset ? 0.0 : g + d;
+  if (lane == 0) gptr(P->G)[m] = reset ? 0.0 : drift_sum(g, d);
 }
 
 // How an iteration updated measure m: 0 not at all (bundles), 1 yes, 2 as

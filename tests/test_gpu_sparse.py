@@ -226,3 +226,36 @@ def test_recorded_sets_at_the_threshold():
         s.close()
     for other in grads[1:]:
         same(grads[0], other)
+
+
+def test_rises_below_the_rounding_of_their_sum():
+    """Two measures of 2048 columns.  In the first iteration 512 columns of
+    one put their weight on a row of theta0's choosing and never again: a rise
+    of 2^-14, and then only a column of weight 2^-56 in each, which the other
+    pulls towards its own row by 2^-68 an iteration, a quarter of what a sum
+    of 2^-14 rounds to.  After 2048 iterations their mass starts to move."""
+    R, S, tiny = 192, 2048, 2.0 ** -56
+    cost = np.ones((2 * S, R))
+    cost[:, 140] = 0.0
+    q = np.full(2 * S, 2.0 ** -11)
+    theta0 = np.repeat(q[:, None] / 256, R, 1)
+    theta0[100:612, 141] = 2.0
+    for j, (own, other) in ((5, (10, 75)), (S + 5, (75, 10))):
+        q[j] = tiny
+        theta0[j] = 0.0
+        cost[j] = 1.0
+        cost[j, own] = 0.0
+        cost[j, other] = tiny
+    res = []
+    for part in (7, 2600):  # calls of seven iterations are dense
+        say(f"case rises part={part}")
+        s = mam.Solver(R, [S, S], dtype=torch.float64, cost_mode=mam.COST_PER_COLUMN, cost_ncols=2 * S)
+        put = lambda x, ld: torch.nn.functional.pad(torch.from_numpy(x), (0, ld - R)).cuda()
+        s.bind(torch.zeros(2 * S, s.ld, dtype=torch.float64, device="cuda"), put(cost, s.cost_ld), torch.from_numpy(q).cuda())
+        s.init(put(theta0, s.ld))
+        for k in range(0, 2600, part):
+            s.iterate(min(part, 2600 - k))
+        res.append(state(s))
+        s.close()
+    assert res[0][2][5, 75] > res[0][2][6, 75]  # some of it has: more than the value of an inactive entry
+    same(*res)
