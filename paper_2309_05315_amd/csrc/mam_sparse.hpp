@@ -912,9 +912,10 @@ sparse_column_kernel(SpArgs<T> a) {
       last = na;
     }
     double lo2 = lm;
-    if (relaxed) {
-      lset = lo2 = max_arith(lm, 0.0);
-      na = count(lset, &S, &least, &most);
+    if (relaxed) {  // of the entries that the column kernel took, those above 0
+      lo2 = max_arith(lm, 0.0);
+      lset = max_arith(lset, lo2);
+      na = na != 0 ? count(lset, &S, &least, &most) : 0;
     }
     int brow = 0;  // nothing active: a row of the largest w stays as a witness
     if (na == 0) {

@@ -259,3 +259,18 @@ def test_rises_below_the_rounding_of_their_sum():
         s.close()
     assert res[0][2][5, 75] > res[0][2][6, 75]  # some of it has: more than the value of an inactive entry
     same(*res)
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_relaxed_entries_at_the_threshold(seed):
+    """Relaxed columns (and no damping step: gamma = 0): an entry that the
+    threshold's last round left out stays 0, though it may lie an ulp above
+    the threshold."""
+    rng = np.random.default_rng([11, seed])
+    R, S = 479, [100, 41, 94, 132, 96, 888, 120, 92, 233]
+    T = sum(S)
+    p = inputs.Problem(name=f"dyadic_relaxed_{seed}", R=R, S=S, cost=rng.integers(0, 400, (T, R)) - 3.0,
+                       q=rng.integers(0, 5, T) / 2048.0, dtype="f64", iters=8, rho=4096.0, gamma=0.0,
+                       col_index=np.arange(T, dtype=np.int32))
+    for iters in (8, 20):
+        same(*both(p, iters, relaxed=True))
