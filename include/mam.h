@@ -258,6 +258,13 @@ mam_status mam_init(mam_problem* p, const void* theta0, void* stream);
  * their active entries).  Errors: MAM_ESTATE before mam_init. */
 mam_status mam_iterate(mam_problem* p, int64_t iters, void* stream);
 
+/* Whether mam_iterate(p, iters, ...) would keep the plans in the workspace
+ * between its iterations (1), or take dense iterations (0; also before
+ * mam_init and on long columns, which have MAM_FLAG_SPARSE_STORE).  The
+ * results are the same bits either way; for callers that time or test one of
+ * the two. */
+int32_t mam_sparse_iterations(const mam_problem* p, int64_t iters);
+
 /* Grid of a MAM_COST_GRID problem (Theorem c: with measures on one grid and
  * alpha_m = 1/M the support Xi of a barycenter is itself a regular grid).
  * Row r is the grid point of index (i_0, ..., i_{dim-1}), last axis fastest
@@ -535,6 +542,9 @@ mam_status mam_batch_init(mam_batch* b, void* stream);
 
 /* 'iters' iterations of every problem; asynchronous. */
 mam_status mam_batch_iterate(mam_batch* b, int64_t iters, void* stream);
+
+/* mam_sparse_iterations for batches. */
+int32_t mam_batch_sparse_iterations(const mam_batch* b, int64_t iters);
 
 /* Graph replay for batches (rules of mam_graph). */
 mam_status mam_batch_graph(mam_batch* b, int64_t iters_per_launch);

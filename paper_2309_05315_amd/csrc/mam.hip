@@ -1916,6 +1916,11 @@ bool sparse_use(const Plan* pl, int64_t iters) {
   return !pl->lg.on && pl->sp.on && pl->sp.use && iters >= (pl->sp.plan_bytes >= ((int64_t)256 << 20) ? 4 : 8);
 }
 
+// The iterations of a call before the one, if any, that computes diagnostics.
+int64_t plain_iterations(const Plan* pl, int64_t iters) {
+  return iters - (!pl->batch && (pl->P[0].flags & MAM_FLAG_DIAG) && iters > 0 ? 1 : 0);
+}
+
 // Start of a call: the cost's block minima (the cost may have been rebuilt
 // in place since the last call).  Plans with sub-wave groups have no SPARSE
 // first iteration: their columns all start as stored dense.
@@ -2039,8 +2044,8 @@ mam_status plan_iterate(Plan* pl, int64_t iters, hipStream_t st) {
   if (iters < 0) return fail(MAM_EINVAL, "iters must be >= 0");
   if (!pl->inited) return fail(MAM_ESTATE, "mam_init has not run");
   // the last iteration computes the diagnostics, outside any graph
-  const bool diag = !pl->batch && (pl->P[0].flags & MAM_FLAG_DIAG) && iters > 0;
-  const int64_t plain = iters - (diag ? 1 : 0);
+  const int64_t plain = plain_iterations(pl, iters);
+  const bool diag = plain < iters;
   if (sparse_use(pl, plain)) {
     bool first = false;
     TRY(sparse_begin(pl, &first, st));
@@ -3041,6 +3046,10 @@ mam_status mam_set_grid(mam_problem* p, int32_t dim, const int64_t* n, const dou
   return MAM_OK;
 }
 
+int32_t mam_sparse_iterations(const mam_problem* p, int64_t iters) {
+  return p && p->plan.inited && sparse_use(&p->plan, plain_iterations(&p->plan, iters)) ? 1 : 0;
+}
+
 mam_status mam_iterate_until(mam_problem* p, int64_t max_iters, int32_t test, double tol, int64_t check_every,
                              mam_stop_result* out, void* stream) {
   if (!p) return fail(MAM_EINVAL, "NULL handle");
@@ -3328,6 +3337,10 @@ mam_status mam_batch_init(mam_batch* b, void* stream) {
 mam_status mam_batch_iterate(mam_batch* b, int64_t iters, void* stream) {
   if (!b) return fail(MAM_EINVAL, "NULL handle");
   return plan_iterate(&b->plan, iters, static_cast<hipStream_t>(stream));
+}
+
+int32_t mam_batch_sparse_iterations(const mam_batch* b, int64_t iters) {
+  return b && b->plan.inited && sparse_use(&b->plan, iters) ? 1 : 0;
 }
 
 mam_status mam_batch_graph(mam_batch* b, int64_t iters_per_launch) {

@@ -44,7 +44,7 @@ EXPORTED = ["mam_abi_version", "mam_last_error", "mam_create", "mam_set_schedule
             "mam_batch_destroy", "mam_adjoint_workspace_bytes", "mam_record", "mam_backward",
             "mam_bundle_workspace_bytes", "mam_set_bundles", "mam_iterate_bundles",
             "mam_iterate_until", "mam_set_grid", "mam_support_workspace_bytes", "mam_support_update",
-            "mam_solve_static", "mam_stream_copy"]
+            "mam_solve_static", "mam_stream_copy", "mam_sparse_iterations", "mam_batch_sparse_iterations"]
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libmam.so")
 
@@ -123,6 +123,8 @@ def lib() -> ctypes.CDLL:
                                                 ctypes.c_int32, ctypes.c_int32, _vp,
                                                 ctypes.c_int64, ctypes.c_int32, _vp, _vp]),
         "mam_graph": (ctypes.c_int32, [_vp, ctypes.c_int64]),
+        "mam_sparse_iterations": (ctypes.c_int32, [_vp, ctypes.c_int64]),
+        "mam_batch_sparse_iterations": (ctypes.c_int32, [_vp, ctypes.c_int64]),
         "mam_batch_create": (ctypes.c_int32, [ctypes.POINTER(_vp), ctypes.POINTER(Desc), ctypes.c_int32]),
         "mam_batch_groups": (ctypes.c_int32, [_vp]),
         "mam_batch_group_of": (ctypes.c_int32, [_vp, ctypes.c_int32]),
@@ -269,6 +271,11 @@ class Solver:
 
     def iterate(self, iters: int) -> None:
         _check(lib().mam_iterate(self._h, int(iters), _stream(self.device)), "mam_iterate")
+
+    def sparse_iterations(self, iters: int) -> bool:
+        """Whether iterate(iters) would keep the plans as -b plus their active
+        entries between its iterations (the same results, in another time)."""
+        return bool(lib().mam_sparse_iterations(self._h, int(iters)))
 
     def iterate_until(self, max_iters: int, test: str = "dtheta", tol: float = 1e-8,
                       check_every: int = 1) -> dict:
@@ -554,6 +561,9 @@ class Batch:
 
     def iterate(self, iters: int) -> None:
         _check(lib().mam_batch_iterate(self._h, int(iters), _stream(self.device)), "mam_batch_iterate")
+
+    def sparse_iterations(self, iters: int) -> bool:
+        return bool(lib().mam_batch_sparse_iterations(self._h, int(iters)))
 
     def graph(self, iters_per_launch: int) -> None:
         _check(lib().mam_batch_graph(self._h, int(iters_per_launch)), "mam_batch_graph")

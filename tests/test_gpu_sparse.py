@@ -7,9 +7,8 @@ between.  Both store the
 same values and add the same numbers in the same order, so plans, marginals
 and barycenters are compared bit for bit.  The dense kernels are held to the
 oracle in the other files; here the sizes are the edges of the sparse
-kernels: blocks of 64 rows, superblocks of 1024, partial vectors, columns
-with more active entries than a column lists, columns without weight or with
-a weight below the rounding of w, every cost layout.
+kernels: blocks of 64 rows, partial vectors, columns with more active entries than a column lists, columns without weight or with a weight
+below the rounding of w, every cost layout.
 """
 import dataclasses
 import sys
@@ -274,3 +273,39 @@ def test_relaxed_entries_at_the_threshold(seed):
                        col_index=np.arange(T, dtype=np.int32))
     for iters in (8, 20):
         same(*both(p, iters, relaxed=True))
+
+
+def long_columns(R, S, dtype, **kw):
+    """rho keeps the active sets small: the estimate at the start is 5 to 14 rows."""
+    return inputs.tiny_problem(R + len(S), R=R, S=S, dtype=dtype, rho=0.05, **kw)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("gamma", [np.inf, 0.05])
+@pytest.mark.parametrize("R,S", [(4096, [310, 313]), (4097, [340, 283]), (4099, [310, 313]), (8192, [184, 183])])
+def test_more_than_64_blocks(R, S, gamma, dtype):
+    """Block bounds, drifts and d^2 partials of a second 64 blocks; a first
+    iteration of 256 to 1024 threads."""
+    p = long_columns(R, S, dtype, gamma=gamma, zero_frac=0.1)
+    s = mam.solver_for(p)
+    s.init()
+    assert s.sparse_iterations(30) and not s.sparse_iterations(1)
+    s.close()
+    same(*both(p, 30))
+    same(*both(p, 30, threads_per_column=1024))
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_more_than_64_blocks_recorded(dtype):
+    p = long_columns(8000, [150, 133], dtype)
+    g = torch.linspace(-1, 1, p.R, dtype=torch.float64, device="cuda")
+    grads = []
+    for ck in (0, 1):
+        s = mam.solver_for(p)
+        s.init()
+        assert s.sparse_iterations(20) and not s.sparse_iterations(1)
+        s.record(20, ck)
+        grads.append([x.cpu().numpy() for x in s.backward(g)])
+        s.close()
+    assert np.abs(grads[0][1]).max() > 0.0
+    same(*grads)
