@@ -14,7 +14,6 @@ SparseFns<T> pick_sparse() {
   f.write = &sparse_write_kernel<T>;
   f.d2 = &sparse_d2_kernel<T>;
   f.cost_min = &cost_min_kernel<T>;
-  f.all_dense = &sparse_dense_kernel<T>;
   return f;
 }
 template SparseFns<float> pick_sparse<float>();

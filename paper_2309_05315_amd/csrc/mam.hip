@@ -1330,7 +1330,7 @@ mam_status launch_columns(Plan* pl, hipStream_t st, int diag, uint8_t* rec, int6
     const int kc = g.vec == 1 ? 1 : g.kc;
     if (g.nt < 64 && (diag || rec))
       return fail(MAM_EUNSUPPORTED, "diagnostics and the reverse mode need 64 or more threads per column");
-    mam::ColFn<T> fn = sparse ? mam::pick_column_sparse<T>(g.nt, g.vpt, g.vec)
+    mam::ColFn<T> fn = sparse ? mam::pick_first<T>(g.nt, g.vpt, g.vec)
                               : mam::pick_column<T>(g.nt, g.vpt, g.vec, kc, diag, g.stream);
     if (!fn) return fail(MAM_EUNSUPPORTED, "no column kernel for nt=%d vpt=%d vec=%d kc=%d", g.nt, g.vpt, g.vec, kc);
     const int wgsize = g.nt <= 64 ? 256 : g.nt;
@@ -1922,32 +1922,21 @@ int64_t plain_iterations(const Plan* pl, int64_t iters) {
 }
 
 // Start of a call: the cost's block minima (the cost may have been rebuilt
-// in place since the last call).  Plans with sub-wave groups have no SPARSE
-// first iteration: their columns all start as stored dense.
+// in place since the last call).
 template <typename T>
-mam_status sparse_begin_t(Plan* pl, bool* first, hipStream_t st) {
+mam_status sparse_begin_t(Plan* pl, hipStream_t st) {
   const SparsePlan& sp = pl->sp;
-  const mam::SparseFns<T> fn = mam::pick_sparse<T>();
-  const mam::SpProb<T>* probs = at<mam::SpProb<T>>(pl, sp.o_probs);
-  hipLaunchKernelGGL(fn.cost_min, dim3((unsigned)sp.costs.size()), dim3(256), 0, st, probs,
-                     at<mam::SpCost>(pl, sp.o_costs), pl->gate);
+  hipLaunchKernelGGL(mam::pick_sparse<T>().cost_min, dim3((unsigned)sp.costs.size()), dim3(256), 0, st,
+                     at<mam::SpProb<T>>(pl, sp.o_probs), at<mam::SpCost>(pl, sp.o_costs), pl->gate);
   LAUNCH_CHECK("cost_min_kernel");
-  *first = true;
-  for (const Group& g : pl->G) *first = *first && g.nt >= 64;
-  if (!*first) {
-    TRY(launch_sparse_close<T>(pl, 0, nullptr, mam::kSpNone, st));
-    hipLaunchKernelGGL(fn.all_dense, dim3((unsigned)((sp.tiles.size() + 3) / 4)), dim3(256), 0, st, probs,
-                       at<mam::SpTile>(pl, sp.o_tiles), (int)sp.tiles.size());
-    LAUNCH_CHECK("sparse_dense_kernel");
-  }
   return MAM_OK;
 }
 
-mam_status sparse_begin(Plan* pl, bool* first, hipStream_t st) {
-  return pl->dtype == MAM_F32 ? sparse_begin_t<float>(pl, first, st) : sparse_begin_t<double>(pl, first, st);
+mam_status sparse_begin(Plan* pl, hipStream_t st) {
+  return pl->dtype == MAM_F32 ? sparse_begin_t<float>(pl, st) : sparse_begin_t<double>(pl, st);
 }
 
-// One iteration; first: it reads the bound plans (SPARSE column kernel).
+// One iteration; first: the call's first, which reads the bound plans.
 template <typename T>
 mam_status sparse_iteration_t(Plan* pl, bool first, hipStream_t st, uint8_t* rec, int64_t rec_ld, int save_prev) {
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -2047,10 +2036,9 @@ mam_status plan_iterate(Plan* pl, int64_t iters, hipStream_t st) {
   const int64_t plain = plain_iterations(pl, iters);
   const bool diag = plain < iters;
   if (sparse_use(pl, plain)) {
-    bool first = false;
-    TRY(sparse_begin(pl, &first, st));
-    if (first) TRY(sparse_iteration(pl, true, st));
-    TRY(run_iterations(pl, first ? 1 : 0, plain, true, st));
+    TRY(sparse_begin(pl, st));
+    TRY(sparse_iteration(pl, true, st));
+    TRY(run_iterations(pl, 1, plain, true, st));
     TRY(sparse_end(pl, st));
   } else {
     TRY(long_begin(pl, iters, st));
@@ -2097,19 +2085,14 @@ enum UntilMode { kUntilDense, kUntilSparse, kUntilPeriod };
 
 mam_status until_period(Plan* pl, hipStream_t st, int test, int64_t every, UntilMode mode, bool start) {
   const Layout& L = pl->lay;
-  bool first = start;  // kUntilSparse: the run's first iteration reads the bound plans
   if (mode == kUntilSparse) {
-    for (int64_t k = 0; k < every; ++k) {
-      TRY(sparse_iteration(pl, first, st, nullptr, 0, k + 1 == every ? 1 : 0));
-      first = false;
-    }
+    // (the run's first iteration reads the bound plans)
+    for (int64_t k = 0; k < every; ++k)
+      TRY(sparse_iteration(pl, start && k == 0, st, nullptr, 0, k + 1 == every ? 1 : 0));
   } else {
     if (mode == kUntilPeriod) {
-      TRY(sparse_begin(pl, &first, st));
-      for (int64_t k = 0; k + 1 < every; ++k) {
-        TRY(sparse_iteration(pl, first, st));
-        first = false;
-      }
+      TRY(sparse_begin(pl, st));
+      for (int64_t k = 0; k + 1 < every; ++k) TRY(sparse_iteration(pl, k == 0, st));
       TRY(sparse_end(pl, st));
     } else {
       for (int64_t k = 0; k + 1 < every; ++k) TRY(one_iteration(pl, st, 0));
@@ -2166,8 +2149,8 @@ mam_status until_run(Plan* pl, int64_t max_iters, int test, double tol, int64_t 
   } else if (sparse_use(pl, every - 1)) {
     mode = kUntilPeriod;
   }
-  bool start = false;
-  if (mode == kUntilSparse) TRY(sparse_begin(pl, &start, st));
+  bool start = mode == kUntilSparse;
+  if (start) TRY(sparse_begin(pl, st));
   TRY(long_begin(pl, max_iters, st));
   if (graph && periods > (start ? 1 : 0) &&
       (!pl->uexec || pl->utest != test || pl->uevery != every || pl->umode != mode))
@@ -2330,8 +2313,7 @@ mam_status record_range(Plan* pl, int64_t k0, int64_t k1, int64_t rec_from, bool
   Adjoint& A = pl->adj;
   const Prob& p = pl->P[0];
   const bool sparse = sparse_use(pl, k1 - k0);
-  bool first = false;
-  if (sparse) TRY(sparse_begin(pl, &first, st));
+  if (sparse) TRY(sparse_begin(pl, st));
   for (int64_t k = k0; k < k1; ++k) {
     if (ckpt && k > 0 && k % A.C == 0) {
       if (sparse && k > k0) TRY(sparse_end(pl, st));
@@ -2357,9 +2339,8 @@ mam_status record_range(Plan* pl, int64_t k0, int64_t k1, int64_t rec_from, bool
                              hipMemcpyDeviceToDevice, st));
     }
     uint8_t* const rec = k >= rec_from ? mask_slot(pl, k) : nullptr;
-    if (sparse) TRY(sparse_iteration(pl, first, st, rec, A.mld));
+    if (sparse) TRY(sparse_iteration(pl, k == k0, st, rec, A.mld));
     else TRY(one_iteration(pl, st, 0, rec, A.mld));
-    first = false;
   }
   return sparse ? sparse_end(pl, st) : MAM_OK;
 }
@@ -2717,7 +2698,7 @@ mam_status launch_bundle_columns(Plan* pl, const BundleSched& bs, hipStream_t st
   a.xcd_remap = 0;
   a.kb = group_block(g);
   const int kc = g.vec == 1 ? 1 : g.kc;
-  mam::ColFn<T> fn = sparse ? mam::pick_column_sparse<T>(g.nt, g.vpt, g.vec)
+  mam::ColFn<T> fn = sparse ? mam::pick_first<T>(g.nt, g.vpt, g.vec)
                             : mam::pick_column<T>(g.nt, g.vpt, g.vec, kc, 0, g.stream);
   if (!fn) return fail(MAM_EUNSUPPORTED, "no column kernel for nt=%d vpt=%d vec=%d kc=%d", g.nt, g.vpt, g.vec, kc);
   const int wgsize = g.nt <= 64 ? 256 : g.nt;
@@ -2736,8 +2717,7 @@ mam_status launch_bundle_columns(Plan* pl, const BundleSched& bs, hipStream_t st
 // forms the next b and the rise of base for all of them.
 template <typename T>
 mam_status iterate_bundles_sparse(Plan* pl, int64_t iters, const int32_t* seq, hipStream_t st) {
-  bool first = false;
-  TRY(sparse_begin_t<T>(pl, &first, st));
+  TRY(sparse_begin_t<T>(pl, st));
   std::vector<char> seen(pl->bund.nb, 0);
   char* const bw = pl->bund.ws;
   for (int64_t k = 0; k < iters; ++k) {
@@ -2777,7 +2757,7 @@ mam_status plan_iterate_bundles(Plan* pl, int64_t iters, const int32_t* seq, hip
     if (seq[k] < 0 || seq[k] >= pl->bund.nb)
       return fail(MAM_EINVAL, "seq[%lld] = %d is not a bundle", (long long)k, seq[k]);
   const Layout& L = pl->lay;
-  // (sub-wave groups have no SPARSE first iteration)
+  // (plans with sub-wave groups stay dense)
   if (sparse_use(pl, iters / pl->bund.nb) && pl->G[0].nt >= 64) {
     TRY(pl->dtype == MAM_F32 ? iterate_bundles_sparse<float>(pl, iters, seq, st)
                              : iterate_bundles_sparse<double>(pl, iters, seq, st));

@@ -20,8 +20,7 @@ ColFn<T> pick_column_kc(int nt, int vpt, int vec, int stream);
 template <typename T>
 ColFn<T> pick_column_diag(int nt, int vpt, int vec);
 
-// First iteration of a sparse call (64 or more threads per column): theta
-// read, patches stored.
+// First iteration of a sparse call, 64 or more threads per column.
 template <typename T>
 ColFn<T> pick_column_sparse(int nt, int vpt, int vec);
 extern template ColFn<float> pick_column_sparse<float>(int, int, int);
@@ -41,7 +40,6 @@ struct SparseFns {
   void (*write)(const SpProb<T>*, const SpTile*, const int32_t*) = nullptr;
   void (*d2)(const SpProb<T>*, const int32_t*) = nullptr;
   void (*cost_min)(const SpProb<T>*, const SpCost*, const int32_t*) = nullptr;
-  void (*all_dense)(const SpProb<T>*, const SpTile*, int) = nullptr;
 };
 template <typename T>
 SparseFns<T> pick_sparse();
@@ -49,15 +47,22 @@ extern template SparseFns<float> pick_sparse<float>();
 extern template SparseFns<double> pick_sparse<double>();
 
 // Sub-wave instance (16 or 32 lanes per column, one column in flight, no
-// diagnostics) or nullptr.
+// diagnostics) or nullptr.  sparse: the first iteration of a sparse call.
 template <typename T>
-ColFn<T> pick_subwave(int nt, int vpt, int vec, int stream);
-extern template ColFn<float> pick_subwave<float>(int, int, int, int);
-extern template ColFn<double> pick_subwave<double>(int, int, int, int);
+ColFn<T> pick_subwave(int nt, int vpt, int vec, int stream, bool sparse);
+extern template ColFn<float> pick_subwave<float>(int, int, int, int, bool);
+extern template ColFn<double> pick_subwave<double>(int, int, int, int, bool);
+
+// The kernel of the first iteration of a sparse call: theta read, patches
+// stored (one column in flight, so a schedule's block of any size fits).
+template <typename T>
+inline ColFn<T> pick_first(int nt, int vpt, int vec) {
+  return nt < 64 ? pick_subwave<T>(nt, vpt, vec, 0, true) : pick_column_sparse<T>(nt, vpt, vec);
+}
 
 template <typename T>
 inline ColFn<T> pick_column(int nt, int vpt, int vec, int kc, int diag, int stream) {
-  if (nt < 64) return (diag || kc != 1) ? nullptr : pick_subwave<T>(nt, vpt, vec, stream);
+  if (nt < 64) return (diag || kc != 1) ? nullptr : pick_subwave<T>(nt, vpt, vec, stream, false);
   if (diag) return pick_column_diag<T>(nt, vpt, vec);
   switch (kc) {
     case 1: return pick_column_kc<T, 1>(nt, vpt, vec, stream);

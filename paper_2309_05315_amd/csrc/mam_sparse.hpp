@@ -1010,9 +1010,8 @@ __device__ __forceinline__ void sparse_absorb(const ConstPtr<SpProb<T>> P, int m
 }
 
 // How an iteration updated measure m: 0 not at all (bundles), 1 yes, 2 as
-// its first sparse iteration.  mode: kSpNone (no measure: the start of a call
-// without a SPARSE first iteration), kSpFirst, kSpNext.
-constexpr int kSpNone = 0, kSpFirst = 1, kSpNext = 2;
+// its first sparse iteration.  mode: the first iteration of a call, or one after it.
+constexpr int kSpFirst = 1, kSpNext = 2;
 
 // Steps 3 and 1 of a block of 64 rows, all measures: the new marginals from
 // the fixed-point sums, p, the partial sum of d^2, nbv = (T)(-b) of the
@@ -1051,7 +1050,7 @@ sparse_close_kernel(const SpProb<T>* __restrict__ probs, const SpRows* __restric
   const double t = balanced ? 1.0 : uniform_d(*gptr(P->t_out));
   const int rpar = mode == kSpNext ? uniform_i(gptr(P->par)[0]) : 0;
   const double pold = p[rr];
-  auto updated = [&](int m) -> int { return mode == kSpNone ? 0 : (upd != nullptr ? (int)upd[m] : 1); };
+  auto updated = [&](int m) -> int { return upd != nullptr ? (int)upd[m] : 1; };
   constexpr int U = 4;
   for (int m0 = wv; m0 < M; m0 += W * U) {
     double old[U], last[U];
@@ -1249,21 +1248,6 @@ sparse_write_kernel(const SpProb<T>* __restrict__ probs, const SpTile* __restric
         }
       }
     }
-  }
-}
-
-// Every column of the tiles stored dense in theta (the start of a call whose
-// first iteration has no SPARSE column kernel).
-template <typename T>
-__global__ void __launch_bounds__(256)
-sparse_dense_kernel(const SpProb<T>* __restrict__ probs, const SpTile* __restrict__ tiles, int ntiles) {
-  const int wid = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (wid >= ntiles) return;
-  const SpTile tk = tiles[wid];
-  const int n = tk.n & 0xffff, lane = threadIdx.x & 63;
-  if (lane < n) {
-    const int64_t j = (int64_t)tk.j0 + lane;
-    probs[tk.prob].cnt[j] = (double)probs[tk.prob].q[j] > 0.0 ? -1 : 0;
   }
 }
 

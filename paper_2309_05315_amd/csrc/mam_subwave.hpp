@@ -18,7 +18,8 @@
 // Segments and schedule tables are those of the column kernel with
 // NG = 256/NT groups per workgroup; a group takes blocks of kb columns.  No
 // diagnostics or active-set recording (the host takes the one-wave kernel
-// for those).
+// for those).  SPARSE instances store a column of at most kPatch active
+// entries as the list of them, as the column kernel's do.
 #pragma once
 
 #include "mam_kernels.hpp"
@@ -53,7 +54,7 @@ __device__ __forceinline__ int group_sum_i(int v) {
   return v;
 }
 
-template <typename T, int NT, int VPT, int VEC, bool STREAM>
+template <typename T, int NT, int VPT, int VEC, bool STREAM, bool SPARSE = false>
 __global__ void __launch_bounds__(256) subwave_kernel(ColArgs<T> a) {
   static_assert(NT == 16 || NT == 32, "sub-wave groups have 16 or 32 lanes");
   static_assert(VPT % VEC == 0, "VPT must be a multiple of VEC");
@@ -98,7 +99,12 @@ __global__ void __launch_bounds__(256) subwave_kernel(ColArgs<T> a) {
     const double* __restrict__ pv = gptr(P.p);
 
     const double t = damping_t(gptr(P.d2part), uniform_i(P.nb), uniform_d(P.rho), uniform_d(P.gamma), lane);
-    if (gtid == 0 && j0 == 0) gptr(P.t_out)[0] = t;
+    // (a sparse launch may leave out measure 0: every segment writes the same t)
+    if (gtid == 0 && (SPARSE || j0 == 0)) gptr(P.t_out)[0] = t;
+    if constexpr (SPARSE) {
+      const SpProb<T>& SP = a.sp[uniform_i(a.seg_p[si])];
+      if (gtid == 0) gptr(SP.par)[0] = gptr(SP.par)[1];
+    }
 
     // b^(m) at the group's rows (group 0 writes what every group reads); a
     // row past R gets b = -inf, so its w is -inf: never active
@@ -172,7 +178,7 @@ __global__ void __launch_bounds__(256) subwave_kernel(ColArgs<T> a) {
       bool act = valid && tau > 0.0;
       double lam = (act && warm) ? b.l : __builtin_nan("");
       if (!act) lam = __builtin_huge_val();
-      int mask = 0, nprev = -1;
+      int mask = 0, nprev = -1, nact = 0;  // nact: entries of mask (SPARSE)
       for (int it = 0; it < R + 4; ++it) {
         if (__ballot(act) == 0ull) break;
         const bool cold = lam != lam;
@@ -200,6 +206,7 @@ __global__ void __launch_bounds__(256) subwave_kernel(ColArgs<T> a) {
         if (__ballot(act && cold) != 0ull) wmx = group_reduce<NT, OpMax>(hi);
         if (act) {
           mask = bits;
+          if constexpr (SPARSE) nact = n;
           if (n == 0) {
             if (cold) {
               lam = wmx - tau;  // the exact lower bound w_max - tau
@@ -223,9 +230,21 @@ __global__ void __launch_bounds__(256) subwave_kernel(ColArgs<T> a) {
       T out[VPT];
 #pragma unroll
       for (int k = 0; k < VPT; ++k) out[k] = nb[k];
+      const bool listed = SPARSE && nact <= kPatch;
       if (__ballot(mask != 0) != 0ull) {
+        int at0 = 0;  // sparse: list entries of the slots before this one
 #pragma unroll
         for (int k = 0; k < VPT; ++k) {
+          if constexpr (SPARSE) {
+            const unsigned bits = (unsigned)(__ballot((mask >> k) & 1) >> (lane - tid)) & (unsigned)((1ull << NT) - 1ull);
+            if (listed && ((mask >> k) & 1)) {
+              const SpProb<T>& SP = a.sp[uniform_i(a.seg_p[si])];
+              const int64_t at = (int64_t)(at0 + __popc(bits & ((1u << tid) - 1u))) * SP.tcols + j;
+              gptr(SP.prow)[at] = ((k / VEC) * NT + tid) * VEC + (k % VEC);
+              gptr(SP.pval)[at] = (T)(fmax(w[k] - lout, 0.0) - lds_b[k * NT + tid]);
+            }
+            at0 += __popc(bits);
+          }
           if ((mask >> k) & 1) {
             const double ph = fmax(w[k] - lout, 0.0);
             out[k] = (T)(ph - lds_b[k * NT + tid]);
@@ -238,7 +257,7 @@ __global__ void __launch_bounds__(256) subwave_kernel(ColArgs<T> a) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
           const int r0 = (c * NT + tid) * VEC;
-          if (r0 < R) {
+          if (r0 < R && !listed) {
             T ov[VEC];
 #pragma unroll
             for (int v = 0; v < VEC; ++v) ov[v] = out[c * VEC + v];
@@ -253,6 +272,18 @@ __global__ void __launch_bounds__(256) subwave_kernel(ColArgs<T> a) {
           }
         }
         if (tid == 0) lamv[j] = lam;
+        if constexpr (SPARSE) {
+          if (tid == 0) {
+            const SpProb<T>& SP = a.sp[uniform_i(a.seg_p[si])];
+            const bool weight = tau > 0.0;
+            if (weight && nact == 0) {
+              gptr(SP.prow)[j] = 0;
+              gptr(SP.pval)[j] = nb[0];
+            }
+            gptr(SP.cnt)[j] = !listed ? -1 : (!weight ? 0 : (nact > 1 ? nact : 1));
+            gptr(SP.vg)[j] = __builtin_huge_val();  // nothing known about the other rows
+          }
+        }
       }
     };
 

@@ -309,3 +309,40 @@ def test_more_than_64_blocks_recorded(dtype):
         s.close()
     assert np.abs(grads[0][1]).max() > 0.0
     same(*grads)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("R,S,nt", [(70, [9000, 11003], 16), (130, [3001, 2999, 4100], 16), (256, [2600, 2700], 16),
+                                    (100, [7001, 7005], 32), (301, [1601, 1600, 1300], 32), (512, [1300, 1301], 32)])
+def test_sub_wave_first_iteration(R, S, nt, dtype):
+    """Groups of 16 and 32 lanes store patches from a call's first iteration
+    on: values per lane from 4 to 16, rows off the vector width, columns
+    without weight, lists of up to 16 entries and columns with more."""
+    for rho in (0.3, 12.0):
+        p = inputs.tiny_problem(R, R=R, S=S, dtype=dtype, rho=rho, zero_frac=0.1)
+        s = mam.solver_for(p, threads_per_column=nt)
+        s.init()
+        assert s.sparse_iterations(20)
+        s.close()
+        same(*both(p, 20, threads_per_column=nt))
+
+
+def test_sub_wave_calls_do_not_start_dense():
+    """A call of nine iterations on groups of 32 lanes, against one wave per
+    column: as long as its first iteration left every column to the whole-wave
+    path, the column kernels took 2.3 times as long on a batch."""
+    p = inputs.tiny_problem(3, R=250, S=[5003] * 8, dtype="f32")
+    ms = {}
+    for nt in (32, 64):
+        s = mam.solver_for(p, threads_per_column=nt)
+        times = []
+        for k in range(5):
+            s.init()
+            s.timing(k > 0)
+            s.iterate(9)
+            if k:
+                times.append(s.timing_read()[0])
+        ms[nt] = min(times)
+        s.close()
+    say(f"column kernels {ms}")
+    assert ms[32] <= 1.4 * ms[64]
