@@ -486,6 +486,15 @@ void build_long_schedule(Plan* pl);
 // per iteration over 200 iterations, dense against patches: 2.1 MB of plans
 // 11.6 / 13.5, 4.2 MB 16.8 / 16.4, 5.3 MB 18.4 / 13.3, 34 MB 26 / 12.4.
 //
+// Short columns stay dense too, for two reasons.  Every active entry is one
+// addition in memory to its row's sum, and with many columns to a row these
+// queue up (the dense kernels add a segment's in LDS first): measured with one
+// active entry a column, patches take 0.64 to 0.93 of the dense time at 256
+// columns to a row, 1.0 to 1.1 at 512, 1.3 to 2.5 at 2,000 and up to 6.9 at
+// 100,000 (16 to 256 rows, 1 to 12 measures, 6 to 96 MB of plans).  And the
+// slots of a column, 140 bytes in FP32 and 204 in FP64, must not exceed the
+// plans (35 and 26 rows where all columns are equally long).
+//
 // Limits: the close kernel holds 64 rows of every measure in LDS
 // (kSparseMaxM measures), tiles hold 32-bit column numbers, and
 // MAM_FLAG_COLD asks for cold threshold searches, which the dense kernels do.
@@ -497,6 +506,10 @@ void add_tiles(std::vector<mam::SpTile>& out, const Prob& p, int pi, int64_t m, 
 }
 
 constexpr int64_t kSparseMinBytes = (int64_t)5 << 20;
+constexpr int64_t kSparseMaxPerRow = 256;  // columns of a measure for each row
+
+// Workspace of a column's patches: slots, count and bound.
+int64_t patch_bytes(int dtype) { return mam::kPatch * (4 + (int64_t)elem_bytes(dtype)) + 4 + 8; }
 
 void build_sparse_tables(Plan* pl) {
   SparsePlan& sp = pl->sp;
@@ -509,9 +522,11 @@ void build_sparse_tables(Plan* pl) {
   sp.finite = false;
   sp.plan_bytes = 0;
   for (const Prob& p : pl->P) sp.plan_bytes += p.ld * p.T * (int64_t)elem_bytes(pl->dtype);
-  sp.on = !sp.off && sp.plan_bytes >= kSparseMinBytes;
+  for (const Prob& p : pl->P) T += p.T;
+  sp.on = !sp.off && sp.plan_bytes >= kSparseMinBytes && sp.plan_bytes >= T * patch_bytes(pl->dtype);
   for (const Prob& p : pl->P) {
-    T += p.T;
+    for (int64_t m = 0; m < p.M; ++m)
+      if (p.col_off[m + 1] - p.col_off[m] > kSparseMaxPerRow * p.R) sp.on = false;
     sp.finite = sp.finite || !std::isinf(p.gamma);
     sp.mmax = std::max<int>(sp.mmax, (int)p.M);
     if (p.R > kShortMaxR || p.M > mam::kSparseMaxM || (p.flags & MAM_FLAG_COLD) || p.T >= ((int64_t)1 << 30) ||

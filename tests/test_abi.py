@@ -301,3 +301,34 @@ def test_solve_static_rejects_before_touching_the_gpu():
     L.mam_destroy(hb)
     assert L.mam_solve_static(ctypes.byref(big), fake, fake, None, fake, None, 5, out, None) == -2
     assert b"static workspace" in L.mam_last_error()
+
+
+@pytest.mark.parametrize("dtype", [mam.F32, mam.F64])
+def test_patch_slots_stay_below_the_plans(dtype):
+    """The workspace of a sparse call's patches (none with MAM_FLAG_COLD, which
+    keeps calls dense): nothing for columns of a few rows, or with more than
+    256 columns to a row; elsewhere at most as much as the plans, plus what
+    depends on rows and cost columns."""
+    L = mam.lib()
+    eb = 4 if dtype == mam.F32 else 8
+
+    def grown(R, S):
+        sizes = []
+        for fl in (0, mam.FLAG_COLD):
+            rc, h = create(R=R, S=S, dtype=dtype, flags=fl, cost_mode=mam.COST_SHARED, cost_ncols=max(S))
+            assert rc == 0
+            sizes.append(L.mam_workspace_bytes(h))
+            L.mam_destroy(h)
+        return sizes[0] - sizes[1]
+
+    for R in (1, 5, 16, 24):
+        for S in ([200 * R] * 3, [1000000, 7], [3000] * 64):
+            assert grown(R, S) == 0
+    assert grown(300, [257 * 300, 10]) == 0
+    for R, S in ((36, [9000] * 20), (70, [9000] * 8), (300, [3000, 3001]), (300, [256 * 300, 10]), (4096, [400])):
+        T, M = sum(S), len(S)
+        more = grown(R, S)
+        assert T * 16 * (4 + eb) <= more
+        rows = (R + 63) // 64 * 64
+        tables = M * (rows * (16 + eb) + rows // 64 * 24 + 64) + max(S) * (rows // 64 + 4) * (eb + 1) + T * 8 + 20 * 1024
+        assert more <= T * R * eb + tables
