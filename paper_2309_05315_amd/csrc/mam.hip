@@ -203,7 +203,10 @@ struct LongPlan {
 struct SparsePlan {
   bool on = false;    // the kernels take this plan's shapes
   bool off = false;   // left out by the caller of the layout (no room for it)
-  bool use = false;   // decided by mam_init
+  // from the sampled candidates per column (mam_init): the iterations of a run
+  // that they ask for (sparse_need), and their share of the most that pay
+  // (sparse_most)
+  double need = 0.0, load = 0.0;
   int cols = 16;      // columns per wave
   int mmax = 0;
   bool finite = false;  // some problem has a finite gamma
@@ -211,8 +214,8 @@ struct SparsePlan {
   std::vector<mam::SpTile> tiles;
   std::vector<mam::SpRows> rows;
   std::vector<mam::SpCost> costs;
-  std::vector<mam::CandTask> cand;
-  size_t o_probs = 0, o_tiles = 0, o_rows = 0, o_costs = 0, o_cand = 0, o_stat = 0;
+  std::vector<mam::CandTask> samples;
+  size_t o_probs = 0, o_tiles = 0, o_rows = 0, o_costs = 0, o_samples = 0, o_stat = 0;
 };
 
 struct Plan {
@@ -511,12 +514,19 @@ constexpr int64_t kSparseMaxPerRow = 256;  // columns of a measure for each row
 // Workspace of a column's patches: slots, count and bound.
 int64_t patch_bytes(int dtype) { return mam::kPatch * (4 + (int64_t)elem_bytes(dtype)) + 4 + 8; }
 
+// Columns of a problem sampled for the estimate of its active sets.  (They
+// must not be evenly spaced: on K x K grids the spacing T/64 is a multiple of
+// K, and all of them lay on the images' edge, where there is hardly any mass.)
+int64_t candidate_samples(const Plan* pl, const Prob& p) {
+  return std::min(p.T, std::max<int64_t>(16, 64 / (int64_t)pl->P.size()));
+}
+
 void build_sparse_tables(Plan* pl) {
   SparsePlan& sp = pl->sp;
   sp.tiles.clear();
   sp.rows.clear();
   sp.costs.clear();
-  sp.cand.clear();
+  sp.samples.clear();
   int64_t T = 0;
   sp.mmax = 0;
   sp.finite = false;
@@ -535,7 +545,6 @@ void build_sparse_tables(Plan* pl) {
   }
   if (!sp.on) return;
   sp.cols = T <= (1 << 14) ? 4 : (T <= (1 << 15) ? 8 : (T <= (1 << 18) ? 16 : 32));
-  const int64_t ns = std::max<int64_t>(2, 64 / (int64_t)pl->P.size());
   for (size_t pi = 0; pi < pl->P.size(); ++pi) {
     const Prob& p = pl->P[pi];
     for (int64_t m = 0; m < p.M; ++m) add_tiles(sp.tiles, p, (int)pi, m, sp.cols, m == 0);
@@ -543,10 +552,12 @@ void build_sparse_tables(Plan* pl) {
     for (int b = 0; b < nblk; ++b) sp.rows.push_back({(int32_t)pi, b});
     for (int64_t c = 0; c < p.cost_ncols; c += 16)
       sp.costs.push_back({(int32_t)pi, (int32_t)c, (int32_t)std::min<int64_t>(16, p.cost_ncols - c), 0});
-    for (int64_t k = 0; k < std::min(ns, p.T); ++k) {
-      const int64_t j = (2 * k + 1) * p.T / (2 * std::min(ns, p.T));
+    const int64_t ns = candidate_samples(pl, p);
+    for (int64_t k = 0; k < ns; ++k) {
+      const double g = (double)(k + 1) * 0.6180339887498949;  // golden section
+      const int64_t j = std::min(p.T - 1, (int64_t)((g - std::floor(g)) * (double)p.T));
       const int64_t m = std::upper_bound(p.col_off.begin(), p.col_off.end(), j) - p.col_off.begin() - 1;
-      sp.cand.push_back({(int32_t)pi, (int32_t)m, j});
+      sp.samples.push_back({(int32_t)pi, (int32_t)m, j});
     }
   }
 }
@@ -888,7 +899,7 @@ void build_layout(Plan* pl) {
     sp.o_tiles = take(sp.tiles.size() * sizeof(mam::SpTile));
     sp.o_rows = take(sp.rows.size() * sizeof(mam::SpRows));
     sp.o_costs = take(sp.costs.size() * sizeof(mam::SpCost));
-    sp.o_cand = take(sp.cand.size() * sizeof(mam::CandTask));
+    sp.o_samples = take(sp.samples.size() * sizeof(mam::CandTask));
   }
   for (Prob& p : pl->P) {
     const size_t R = (size_t)p.R, M = (size_t)p.M;
@@ -925,10 +936,10 @@ void build_layout(Plan* pl) {
       p.o_fx = take(2 * M * 8);
     }
   }
-  // what init reads back, in one piece: every problem's masses and flags, and
-  // the sum of sampled candidates
-  size_t nchk = 1;
-  for (const Prob& p : pl->P) nchk += (size_t)p.M + 2;
+  // what init reads back, in one piece: every problem's masses and flags, then
+  // every problem's sum of sampled candidates
+  size_t nchk = 0;
+  for (const Prob& p : pl->P) nchk += (size_t)p.M + 3;
   L.nchk = nchk;
   L.chk = take(nchk * 8);
   size_t ochk = L.chk;
@@ -1281,7 +1292,7 @@ mam_status upload_tables(Plan* pl, hipStream_t st) {
     TRY(put(sp.o_tiles, sp.tiles.data(), sp.tiles.size() * sizeof(mam::SpTile)));
     TRY(put(sp.o_rows, sp.rows.data(), sp.rows.size() * sizeof(mam::SpRows)));
     TRY(put(sp.o_costs, sp.costs.data(), sp.costs.size() * sizeof(mam::SpCost)));
-    TRY(put(sp.o_cand, sp.cand.data(), sp.cand.size() * sizeof(mam::CandTask)));
+    TRY(put(sp.o_samples, sp.samples.data(), sp.samples.size() * sizeof(mam::CandTask)));
   }
   std::vector<mam::ProbDev<float>> pdf;
   std::vector<mam::ProbDev<double>> pdd;
@@ -1758,23 +1769,18 @@ mam_status resident_workgroups(Plan* pl, bool* changed) {
   return MAM_OK;
 }
 
-// Whether calls keep their plans as patches, from a sample of the columns:
-// the rows that a threshold w_max - q_s without corrections would leave
-// possibly active.  Small active sets are what the patches are for; where
-// most columns overflow their kPatch entries, the dense kernels are faster.
-// Measured on 32x32 and 64x64 grids, 8 measures, FP32, microseconds per
-// iteration over 20 iterations, dense against patches: rho = 4 (25-33
-// candidates) 40 against 35 and 230 against 173; rho = 16 (84-130) 41 against
-// 90 and 233 against 712, with the sets shrinking too slowly to make it good
-// (even after 100 iterations on the smaller grid).
-constexpr double kSparseMaxCandidates = 48.0;
+double sparse_need(const SparsePlan& sp, const Prob& p);
+double sparse_most(const SparsePlan& sp, const Prob& p);
 
+// Start-up estimate of the active sets, from a sample of the columns: the
+// rows that a threshold w_max - q_s without corrections would leave possibly
+// active (sparse_use).
 template <typename T>
 mam_status launch_candidates(Plan* pl, hipStream_t st) {
   SparsePlan& sp = pl->sp;
   if (pl->lg.on || !sp.on) return MAM_OK;
-  hipLaunchKernelGGL(mam::candidates_kernel<T>, dim3((unsigned)sp.cand.size()), dim3(256), 0, st,
-                     at<mam::ProbDev<T>>(pl, pl->lay.probdev), at<mam::CandTask>(pl, sp.o_cand),
+  hipLaunchKernelGGL(mam::candidates_kernel<T>, dim3((unsigned)sp.samples.size()), dim3(256), 0, st,
+                     at<mam::ProbDev<T>>(pl, pl->lay.probdev), at<mam::CandTask>(pl, sp.o_samples),
                      at<double>(pl, sp.o_stat));
   LAUNCH_CHECK("candidates_kernel");
   return MAM_OK;
@@ -1813,7 +1819,18 @@ mam_status plan_init(Plan* pl, const void* const* theta0, hipStream_t st) {
   std::vector<double> all(pl->lay.nchk);
   HIP_TRY(hipMemcpyAsync(all.data(), pl->ws + pl->lay.chk, all.size() * 8, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
-  pl->sp.use = !pl->lg.on && pl->sp.on && all.back() <= kSparseMaxCandidates * (double)pl->sp.cand.size();
+  pl->sp.need = pl->sp.load = 0.0;
+  if (!pl->lg.on && pl->sp.on) {
+    int64_t T = 0;
+    for (const Prob& p : pl->P) T += p.T;
+    const double* const sums = all.data() + (pl->sp.o_stat - pl->lay.chk) / 8;
+    for (size_t i = 0; i < pl->P.size(); ++i) {
+      const double c = sums[i] / (double)candidate_samples(pl, pl->P[i]);
+      const double part = (double)pl->P[i].T / (double)T;
+      pl->sp.need += part * c * sparse_need(pl->sp, pl->P[i]);
+      pl->sp.load += part * c / sparse_most(pl->sp, pl->P[i]);
+    }
+  }
   for (size_t i = 0; i < pl->P.size(); ++i) {
     Prob& p = pl->P[i];
     const double* const chk = all.data() + (p.o_check - pl->lay.chk) / 8;
@@ -1923,12 +1940,49 @@ mam_status launch_sparse_write(Plan* pl, const mam::SpTile* tiles, size_t ntiles
   return MAM_OK;
 }
 
-// Whether a run of 'iters' iterations keeps its plans as patches.  Its first
-// iterations cost more (the cost's block minima, a first look at every
-// column, the write-back): runs break even at 6-8 iterations on plans of
-// 10-80 MB and between 3 and 4 on 1.6 GB.
-bool sparse_use(const Plan* pl, int64_t iters) {
-  return !pl->lg.on && pl->sp.on && pl->sp.use && iters >= (pl->sp.plan_bytes >= ((int64_t)256 << 20) ? 4 : 8);
+// Whether a run of 'iters' iterations, the first of them the done-th since
+// mam_init, keeps its plans as patches.  The first iterations cost more than
+// the later ones: the cost's block minima, a first look at every column, the
+// write-back, and the whole-wave path for as long as the columns' active sets
+// exceed their kPatch entries.  How many iterations it takes to make that good
+// follows the estimate c of the sets at the start (the sampled candidates per
+// column).  Measured, iterations of a call from the start that take as long
+// either way (grids K x K, balanced, and random points):
+//   K = 32, M = 8, FP32, 34 MB    c = 11: < 8, 21: 10, 40: 17, 76: 40
+//   K = 24, M = 12, FP32, 16 MB   c = 9: < 8, 17: 13, 31: 30
+//   K = 32, M = 8, FP64, 67 MB    c = 18: < 8, 34: 9
+//   K = 64, M = 8, FP32, 537 MB   c = 19: < 8, 37: 8, 72: 16, 137: 27
+//   1003 rows, M = 6, FP32, 19 MB c = 52: < 8, 97: 12 (a cost column for every
+//   3000 rows, M = 4, FP32, 36 MB c = 46: 8, 87: 14    column: twice the reads)
+// A run that continues one has the first iterations behind it.
+//
+// With sets too wide at the start they stay too wide for hundreds of
+// iterations (sparse_most).  Microseconds per iteration over 300 iterations,
+// dense against patches, at the last c that pays and the next one measured:
+//   K = 16, M = 40, FP64, 21 MB   c = 16: 30.5 / 26.5   28: 30.4 / 32.3
+//   K = 24, M = 12, FP32, 16 MB   c = 31: 27.6 / 21.7   52: 28.0 / 33.6
+//   K = 32, M = 8, FP32, 34 MB    c = 76: 34.2 / 26.0   132: 35.3 / 54.0
+//   K = 32, M = 20, FP32, 84 MB   c = 228: 65.0 / 36.0
+//   K = 64, M = 8, FP32, 537 MB   c = 137: 248 / 76     255: 249 / 278
+//   3000 rows, M = 4, FP32, 36 MB c = 87: 40.7 / 34.9   165: 40.5 / 46.0
+// and the smallest plans, whose dense iterations take little more than their
+// launches (K = 16, M = 22, FP32, 5.8 MB): c = 9: 19.3 / 19.6, 18: 19.3 / 20.9.
+double sparse_need(const SparsePlan& sp, const Prob& p) {
+  if (p.cost_mode == MAM_COST_PER_COLUMN) return 0.2;
+  return sp.plan_bytes >= ((int64_t)256 << 20) ? 0.25 : (sp.plan_bytes >= ((int64_t)48 << 20) ? 0.4 : 0.6);
+}
+
+double sparse_most(const SparsePlan& sp, const Prob& p) {
+  const double mib = (double)sp.plan_bytes / (1 << 20);
+  const double c = std::min(144.0, (double)p.R / 13.0 * std::max(1.0, mib / 48.0));
+  return mib < 8.0 ? std::min(c, 10.0) : c;
+}
+
+bool sparse_use(const Plan* pl, int64_t iters, int64_t done) {
+  const SparsePlan& sp = pl->sp;
+  if (pl->lg.on || !sp.on) return false;
+  if (!(sp.load <= 1.0)) return false;
+  return iters >= (sp.plan_bytes >= ((int64_t)256 << 20) ? 4 : 8) && (double)iters + (double)done >= sp.need;
 }
 
 // The iterations of a call before the one, if any, that computes diagnostics.
@@ -2050,7 +2104,7 @@ mam_status plan_iterate(Plan* pl, int64_t iters, hipStream_t st) {
   // the last iteration computes the diagnostics, outside any graph
   const int64_t plain = plain_iterations(pl, iters);
   const bool diag = plain < iters;
-  if (sparse_use(pl, plain)) {
+  if (sparse_use(pl, plain, pl->iters_done)) {
     TRY(sparse_begin(pl, st));
     TRY(sparse_iteration(pl, true, st));
     TRY(run_iterations(pl, 1, plain, true, st));
@@ -2160,8 +2214,8 @@ mam_status until_run(Plan* pl, int64_t max_iters, int test, double tol, int64_t 
   const bool graph = pl->graph_iters > 0 && !pl->timing;
   UntilMode mode = kUntilDense;
   if (test != MAM_STOP_DTHETA) {
-    if (sparse_use(pl, max_iters)) mode = kUntilSparse;
-  } else if (sparse_use(pl, every - 1)) {
+    if (sparse_use(pl, max_iters, pl->iters_done)) mode = kUntilSparse;
+  } else if (sparse_use(pl, every - 1, pl->iters_done + max_iters / 4)) {  // (the later periods outweigh the first)
     mode = kUntilPeriod;
   }
   bool start = mode == kUntilSparse;
@@ -2327,7 +2381,7 @@ mam_status launch_copy(T* dst, const T* src, const Prob& p, hipStream_t st) {
 mam_status record_range(Plan* pl, int64_t k0, int64_t k1, int64_t rec_from, bool ckpt, hipStream_t st) {
   Adjoint& A = pl->adj;
   const Prob& p = pl->P[0];
-  const bool sparse = sparse_use(pl, k1 - k0);
+  const bool sparse = sparse_use(pl, k1 - k0, k0);
   if (sparse) TRY(sparse_begin(pl, st));
   for (int64_t k = k0; k < k1; ++k) {
     if (ckpt && k > 0 && k % A.C == 0) {
@@ -2773,7 +2827,7 @@ mam_status plan_iterate_bundles(Plan* pl, int64_t iters, const int32_t* seq, hip
       return fail(MAM_EINVAL, "seq[%lld] = %d is not a bundle", (long long)k, seq[k]);
   const Layout& L = pl->lay;
   // (plans with sub-wave groups stay dense)
-  if (sparse_use(pl, iters / pl->bund.nb) && pl->G[0].nt >= 64) {
+  if (sparse_use(pl, iters / pl->bund.nb, pl->iters_done / pl->bund.nb) && pl->G[0].nt >= 64) {
     TRY(pl->dtype == MAM_F32 ? iterate_bundles_sparse<float>(pl, iters, seq, st)
                              : iterate_bundles_sparse<double>(pl, iters, seq, st));
     pl->iters_done += iters;
@@ -3042,7 +3096,7 @@ mam_status mam_set_grid(mam_problem* p, int32_t dim, const int64_t* n, const dou
 }
 
 int32_t mam_sparse_iterations(const mam_problem* p, int64_t iters) {
-  return p && p->plan.inited && sparse_use(&p->plan, plain_iterations(&p->plan, iters)) ? 1 : 0;
+  return p && p->plan.inited && sparse_use(&p->plan, plain_iterations(&p->plan, iters), p->plan.iters_done) ? 1 : 0;
 }
 
 mam_status mam_iterate_until(mam_problem* p, int64_t max_iters, int32_t test, double tol, int64_t check_every,
@@ -3335,7 +3389,7 @@ mam_status mam_batch_iterate(mam_batch* b, int64_t iters, void* stream) {
 }
 
 int32_t mam_batch_sparse_iterations(const mam_batch* b, int64_t iters) {
-  return b && b->plan.inited && sparse_use(&b->plan, iters) ? 1 : 0;
+  return b && b->plan.inited && sparse_use(&b->plan, iters, b->plan.iters_done) ? 1 : 0;
 }
 
 mam_status mam_batch_graph(mam_batch* b, int64_t iters_per_launch) {

@@ -474,8 +474,8 @@ check_cost_kernel(const T* __restrict__ cost, int64_t cost_ld, int R, int64_t nc
 // Start-up estimate of the active sets (whether a call keeps its plans as
 // patches): over the sampled columns, the number of rows within rho q_s of
 // the column's least cost, i.e. those the threshold of a column without
-// corrections could make active (w_max - q_s < w).  Whole numbers, so the
-// sum does not depend on the order of the additions.
+// corrections could make active (w_max - q_s < w); one sum per problem.  Whole
+// numbers, so the sums do not depend on the order of the additions.
 struct CandTask {
   int32_t prob, m;
   int64_t j;
@@ -499,7 +499,7 @@ candidates_kernel(const ProbDev<T>* __restrict__ probs, const CandTask* __restri
   double n = 0.0;
   for (int r = threadIdx.x; r < P.R; r += 256) n += (double)col[r] - mn < width ? 1.0 : 0.0;
   n = wave_sum(n);
-  if ((threadIdx.x & 63) == 0) atomicAdd(sum, n);
+  if ((threadIdx.x & 63) == 0) atomicAdd(sum + tk.prob, n);
 }
 
 __global__ void __launch_bounds__(256)

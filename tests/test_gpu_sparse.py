@@ -313,7 +313,7 @@ def test_more_than_64_blocks_recorded(dtype):
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 @pytest.mark.parametrize("R,S,nt", [(70, [9000, 11003], 16), (130, [3001, 2999, 4100], 16), (256, [2600, 2700], 16),
-                                    (100, [7001, 7005], 32), (301, [1601, 1600, 1300], 32), (512, [1300, 1301], 32)])
+                                    (100, [7001, 7005], 32), (301, [4601, 4600, 4300], 32), (512, [4300, 4301], 32)])
 def test_sub_wave_first_iteration(R, S, nt, dtype):
     """Groups of 16 and 32 lanes store patches from a call's first iteration
     on: values per lane from 4 to 16, rows off the vector width, columns
@@ -346,3 +346,40 @@ def test_sub_wave_calls_do_not_start_dense():
         s.close()
     say(f"column kernels {ms}")
     assert ms[32] <= 1.4 * ms[64]
+
+
+def test_wide_sets_at_the_start_need_longer_calls():
+    """Estimates of 6 to 50 active rows per column at the start: the first
+    iterations of a sparse call cost more the wider the sets are, so a call
+    has to be longer to make that good, until the run has them behind it."""
+    p = inputs.balanced_plain(K=32, M=8, dtype="f32")
+    least = {}
+    for rho in (1.0, 4.0, 7.0):
+        s = mam.solver_for(dataclasses.replace(p, rho=rho))
+        s.init()
+        least[rho] = next(n for n in range(1, 60) if s.sparse_iterations(n))
+        s.iterate(60)
+        assert s.sparse_iterations(8) and not s.sparse_iterations(7)
+        s.close()
+    say(f"least iterations {least}")
+    assert least[1.0] == 8 < least[4.0] < least[7.0] <= 30
+
+
+def test_a_batch_weighs_its_problems_by_their_columns():
+    """Bits of a batch with one problem of very wide sets, which it can carry,
+    and with all of them like that, when it stays dense."""
+    probs = inputs.batched_problems(n=24, k_range=(20, 28), iters=10)
+    for wide, sparse in ((0, True), (1, True), (24, False)):
+        these = [dataclasses.replace(q, rho=200.0) if i < wide else q for i, q in enumerate(probs)]
+        b = mam.Batch(these)
+        b.init()
+        assert b.sparse_iterations(100) == sparse
+        b.iterate(30)
+        for i in (0, 1, 23):
+            one = mam.solver_for(these[i])
+            one.init()
+            for _ in range(30):
+                one.iterate(1)
+            assert np.array_equal(b.barycenter(i).cpu().numpy(), one.barycenter().cpu().numpy())
+            one.close()
+        b.close()
