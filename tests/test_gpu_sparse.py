@@ -383,3 +383,31 @@ def test_a_batch_weighs_its_problems_by_their_columns():
             assert np.array_equal(b.barycenter(i).cpu().numpy(), one.barycenter().cpu().numpy())
             one.close()
         b.close()
+
+
+@pytest.mark.parametrize("R,few", [(1024, 10), (1024, 3), (4000, 25)])
+def test_a_measure_of_few_columns(R, few):
+    """Its columns hold a part of the barycenter's rows each, more than they
+    list.  The same bits, and no more time than dense iterations (calls of
+    seven) take."""
+    p = inputs.tiny_problem(3, R=R, S=[1024] * 7 + [few], dtype="f32")
+    ms, res = {}, []
+    for part in (7, 140):
+        s = mam.solver_for(p)
+        times = []
+        for _ in range(3):
+            s.init()
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(140 // part):
+                s.iterate(part)
+            e[1].record()
+            torch.cuda.synchronize()
+            times.append(e[0].elapsed_time(e[1]))
+        assert s.sparse_iterations(part) == (part == 140)
+        ms[part] = min(times)
+        res.append(state(s))
+        s.close()
+    say(f"R={R} few={few}: {ms}")
+    same(*res)
+    assert ms[140] < 1.05 * ms[7]
