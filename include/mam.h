@@ -263,7 +263,7 @@ mam_status mam_iterate(mam_problem* p, int64_t iters, void* stream);
  * mam_init and on long columns, which have MAM_FLAG_SPARSE_STORE).  The
  * results are the same bits either way; for callers that time or test one of
  * the two. */
-int32_t mam_sparse_iterations(const mam_problem* p, int64_t iters);
+int32_t mam_sparse_iterations(mam_problem* p, int64_t iters);
 
 /* Grid of a MAM_COST_GRID problem (Theorem c: with measures on one grid and
  * alpha_m = 1/M the support Xi of a barycenter is itself a regular grid).
@@ -544,7 +544,7 @@ mam_status mam_batch_init(mam_batch* b, void* stream);
 mam_status mam_batch_iterate(mam_batch* b, int64_t iters, void* stream);
 
 /* mam_sparse_iterations for batches. */
-int32_t mam_batch_sparse_iterations(const mam_batch* b, int64_t iters);
+int32_t mam_batch_sparse_iterations(mam_batch* b, int64_t iters);
 
 /* Graph replay for batches (rules of mam_graph). */
 mam_status mam_batch_graph(mam_batch* b, int64_t iters_per_launch);

@@ -215,8 +215,60 @@ struct SparsePlan {
   std::vector<mam::SpRows> rows;
   std::vector<mam::SpCost> costs;
   std::vector<mam::CandTask> samples;
-  size_t o_probs = 0, o_tiles = 0, o_rows = 0, o_costs = 0, o_samples = 0, o_stat = 0;
+  size_t o_probs = 0, o_tiles = 0, o_rows = 0, o_costs = 0, o_samples = 0, o_stat = 0, o_wide = 0;
+  // what the last sparse call noted on its way out (sparse_look); no sparse
+  // calls before iteration 'hold'
+  bool notes = true;
+  int slot = -1;
+  uint32_t tag = 0;
+  int64_t hold = 0;
 };
+
+// Words of pinned host memory that kernels leave notes in: one page per
+// process, allocated with the first plan that wants one and kept (a kernel of
+// a plan that is gone may still write its note), dealt out to the plans.  A
+// note carries its plan's tag, so one that comes late is not mistaken for the
+// next owner's.  Without a free word a plan goes without notes.
+class Notes {
+ public:
+  void take(int* slot, uint32_t* tag) {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (!page_ && !failed_) {
+      void* h = nullptr;
+      if (hipHostMalloc(&h, kWords * 8, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();
+        failed_ = true;
+      } else {
+        std::memset(h, 0, kWords * 8);
+        for (int i = kWords - 1; i >= 0; --i) free_.push_back(i);
+        page_ = static_cast<uint64_t*>(h);
+      }
+    }
+    if (free_.empty()) return;
+    *slot = free_.back();
+    free_.pop_back();
+    *tag = ++serial_;
+    __atomic_store_n(page_ + *slot, (uint64_t)0, __ATOMIC_RELAXED);
+  }
+  void give(int slot) {
+    std::lock_guard<std::mutex> lock(mu_);
+    free_.push_back(slot);
+  }
+  uint64_t* word(int slot) const { return page_ + slot; }  // (page_ is set before any slot is out)
+
+ private:
+  static constexpr int kWords = 512;
+  std::mutex mu_;
+  uint64_t* page_ = nullptr;
+  bool failed_ = false;
+  uint32_t serial_ = 0;
+  std::vector<int> free_;
+};
+
+Notes& notes() {
+  static Notes* const n = new Notes;  // outlives every plan
+  return *n;
+}
 
 struct Plan {
   int dtype = MAM_F64;
@@ -271,6 +323,7 @@ struct Plan {
   std::vector<hipEvent_t> uev;
 
   ~Plan() {
+    if (sp.slot >= 0) notes().give(sp.slot);
     for (hipEvent_t e : uev) hipEventDestroy(e);
     if (uexec) hipGraphExecDestroy(uexec);
     if (host_flag) hipHostFree(host_flag);
@@ -906,6 +959,7 @@ void build_layout(Plan* pl) {
     sp.o_rows = take(sp.rows.size() * sizeof(mam::SpRows));
     sp.o_costs = take(sp.costs.size() * sizeof(mam::SpCost));
     sp.o_samples = take(sp.samples.size() * sizeof(mam::CandTask));
+    sp.o_wide = take(4);
   }
   for (Prob& p : pl->P) {
     const size_t R = (size_t)p.R, M = (size_t)p.M;
@@ -1227,6 +1281,7 @@ void fill_spprob(Plan* pl, std::vector<mam::SpProb<T>>& out) {
     d.prow = at<int32_t>(pl, p.o_prow);
     d.pval = at<T>(pl, p.o_pval);
     d.vg = at<double>(pl, p.o_vg);
+    d.wide = at<int32_t>(pl, pl->sp.o_wide);
   }
 }
 
@@ -1822,10 +1877,13 @@ mam_status plan_init(Plan* pl, const void* const* theta0, hipStream_t st) {
   TRY(upload_tables(pl, st));
   TRY(pl->dtype == MAM_F32 ? launch_checks<float>(pl, st) : launch_checks<double>(pl, st));
   TRY(pl->dtype == MAM_F32 ? launch_candidates<float>(pl, st) : launch_candidates<double>(pl, st));
+  if (!pl->lg.on && pl->sp.on && pl->sp.notes && pl->sp.slot < 0) notes().take(&pl->sp.slot, &pl->sp.tag);
   std::vector<double> all(pl->lay.nchk);
   HIP_TRY(hipMemcpyAsync(all.data(), pl->ws + pl->lay.chk, all.size() * 8, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   pl->sp.need = pl->sp.load = 0.0;
+  pl->sp.hold = 0;
+  if (pl->sp.slot >= 0) __atomic_store_n(notes().word(pl->sp.slot), (uint64_t)0, __ATOMIC_RELAXED);
   if (!pl->lg.on && pl->sp.on) {
     int64_t T = 0;
     for (const Prob& p : pl->P) T += p.T;
@@ -1940,8 +1998,10 @@ mam_status launch_sparse_d2(Plan* pl, hipStream_t st) {
 
 template <typename T>
 mam_status launch_sparse_write(Plan* pl, const mam::SpTile* tiles, size_t ntiles, hipStream_t st) {
+  const SparsePlan& sp = pl->sp;
   hipLaunchKernelGGL(mam::pick_sparse<T>().write, dim3((unsigned)ntiles), dim3(256), 0, st,
-                     at<mam::SpProb<T>>(pl, pl->sp.o_probs), tiles, pl->gate);
+                     at<mam::SpProb<T>>(pl, sp.o_probs), tiles, pl->gate,
+                     reinterpret_cast<unsigned long long*>(sp.slot >= 0 ? notes().word(sp.slot) : nullptr), sp.tag);
   LAUNCH_CHECK("sparse_write_kernel");
   return MAM_OK;
 }
@@ -1987,8 +2047,29 @@ double sparse_most(const SparsePlan& sp, const Prob& p) {
 bool sparse_use(const Plan* pl, int64_t iters, int64_t done) {
   const SparsePlan& sp = pl->sp;
   if (pl->lg.on || !sp.on) return false;
-  if (!(sp.load <= 1.0)) return false;
+  if (!(sp.load <= 1.0) || pl->iters_done < sp.hold) return false;
   return iters >= (sp.plan_bytes >= ((int64_t)256 << 20) ? 4 : 8) && (double)iters + (double)done >= sp.need;
+}
+
+// The estimate is of the start.  A cost or weights rebuilt in place since, or
+// sets that grow in another way, can leave so many columns stored dense that
+// an iteration waits longer for the wave that takes most of them than a dense
+// one takes.  The write-back of a sparse call notes its rows: with a note of
+// that kind (7.5 us for 1024 rows; dense iterations about 11 us and their
+// plans and costs at 4.4 TB/s) calls are dense until the run is twice as long.
+// The note is looked at and not waited for: a call that has not ended has none.
+// (32 x 32, 8 measures, FP32, the cost divided by 64 after mam_init: 86 us per
+// iteration against 35 dense, in every call and not in the first alone.)
+void sparse_look(Plan* pl) {
+  SparsePlan& sp = pl->sp;
+  if (sp.slot < 0) return;
+  const uint64_t note = __atomic_load_n(notes().word(sp.slot), __ATOMIC_RELAXED);
+  if (note == 0 || (uint32_t)(note >> 32) != sp.tag) return;
+  __atomic_store_n(notes().word(sp.slot), (uint64_t)0, __ATOMIC_RELAXED);
+  int64_t bytes = 0;
+  for (const Prob& p : pl->P)
+    bytes += p.T * p.R * (int64_t)elem_bytes(pl->dtype) * (p.cost_mode == MAM_COST_PER_COLUMN ? 3 : 2);
+  if ((double)(uint32_t)note * 7.5 / 1024.0 > 11.0 + (double)bytes / 4.4e6) sp.hold = 2 * pl->iters_done + 32;
 }
 
 // The iterations of a call before the one, if any, that computes diagnostics.
@@ -2110,6 +2191,7 @@ mam_status plan_iterate(Plan* pl, int64_t iters, hipStream_t st) {
   // the last iteration computes the diagnostics, outside any graph
   const int64_t plain = plain_iterations(pl, iters);
   const bool diag = plain < iters;
+  sparse_look(pl);
   if (sparse_use(pl, plain, pl->iters_done)) {
     TRY(sparse_begin(pl, st));
     TRY(sparse_iteration(pl, true, st));
@@ -2219,6 +2301,7 @@ mam_status until_run(Plan* pl, int64_t max_iters, int test, double tol, int64_t 
   const int64_t periods = max_iters / every, tail = max_iters % every;
   const bool graph = pl->graph_iters > 0 && !pl->timing;
   UntilMode mode = kUntilDense;
+  sparse_look(pl);
   if (test != MAM_STOP_DTHETA) {
     if (sparse_use(pl, max_iters, pl->iters_done)) mode = kUntilSparse;
   } else if (sparse_use(pl, every - 1, pl->iters_done + max_iters / 4)) {  // (the later periods outweigh the first)
@@ -2833,6 +2916,7 @@ mam_status plan_iterate_bundles(Plan* pl, int64_t iters, const int32_t* seq, hip
       return fail(MAM_EINVAL, "seq[%lld] = %d is not a bundle", (long long)k, seq[k]);
   const Layout& L = pl->lay;
   // (plans with sub-wave groups stay dense)
+  sparse_look(pl);
   if (sparse_use(pl, iters / pl->bund.nb, pl->iters_done / pl->bund.nb) && pl->G[0].nt >= 64) {
     TRY(pl->dtype == MAM_F32 ? iterate_bundles_sparse<float>(pl, iters, seq, st)
                              : iterate_bundles_sparse<double>(pl, iters, seq, st));
@@ -3101,7 +3185,8 @@ mam_status mam_set_grid(mam_problem* p, int32_t dim, const int64_t* n, const dou
   return MAM_OK;
 }
 
-int32_t mam_sparse_iterations(const mam_problem* p, int64_t iters) {
+int32_t mam_sparse_iterations(mam_problem* p, int64_t iters) {
+  if (p) sparse_look(&p->plan);
   return p && p->plan.inited && sparse_use(&p->plan, plain_iterations(&p->plan, iters), p->plan.iters_done) ? 1 : 0;
 }
 
@@ -3312,6 +3397,7 @@ mam_status mam_solve_static(const mam_desc* d, void* theta, const void* cost, co
   // the handle lives for this call only; the kernels queued on 'stream'
   // read only the caller's buffers and the static workspace, which outlive it
   std::unique_ptr<mam_problem, void (*)(mam_problem*)> h(raw, mam_destroy);
+  h->plan.sp.notes = false;  // no later call to read them
   size_t need = mam_workspace_bytes(h.get());
   const bool fits = !h->plan.lg.on || need - h->plan.lay.extra <= kStaticScratchBytes;
   if (fits && need > kStaticScratchBytes) {
@@ -3394,7 +3480,8 @@ mam_status mam_batch_iterate(mam_batch* b, int64_t iters, void* stream) {
   return plan_iterate(&b->plan, iters, static_cast<hipStream_t>(stream));
 }
 
-int32_t mam_batch_sparse_iterations(const mam_batch* b, int64_t iters) {
+int32_t mam_batch_sparse_iterations(mam_batch* b, int64_t iters) {
+  if (b) sparse_look(&b->plan);
   return b && b->plan.inited && sparse_use(&b->plan, iters, b->plan.iters_done) ? 1 : 0;
 }
 

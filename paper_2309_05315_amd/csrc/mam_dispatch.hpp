@@ -37,7 +37,7 @@ struct SparseFns {
   void (*column_rec)(SpArgs<T>) = nullptr;  // records the active sets
   void (*close)(const SpProb<T>*, const SpRows*, int, const uint8_t*, int, const int32_t*) = nullptr;
   void (*next)(const SpProb<T>*, const SpRows*, const uint8_t*, int, const int32_t*) = nullptr;
-  void (*write)(const SpProb<T>*, const SpTile*, const int32_t*) = nullptr;
+  void (*write)(const SpProb<T>*, const SpTile*, const int32_t*, unsigned long long*, unsigned) = nullptr;
   void (*d2)(const SpProb<T>*, const int32_t*) = nullptr;
   void (*cost_min)(const SpProb<T>*, const SpCost*, const int32_t*) = nullptr;
 };

@@ -97,6 +97,7 @@ struct SpProb {
   int32_t* prow;            // kPatch x tcols
   T* pval;                  // kPatch x tcols
   double* vg;               // largest w outside a column's patches, less the drift then (inf: not known)
+  int32_t* wide;            // one per plan: what the write-back of the call has noted (sparse_write_kernel)
 };
 
 struct SpTile {
@@ -206,6 +207,7 @@ cost_min_kernel(const SpProb<T>* __restrict__ probs, const SpCost* __restrict__ 
   if (stop != nullptr && *stop != 0) return;
   const SpCost tk = tasks[blockIdx.x];
   const ConstPtr<SpProb<T>> P = cptr(probs) + uniform_i(tk.prob);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *gptr(P->wide) = 0;
   const int lane = threadIdx.x & 63, l = lane & 15, g = lane >> 4;
   const int wv = uniform_i((int)(threadIdx.x >> 6));
   const int R = P->R, nblk = P->nblk;
@@ -1184,11 +1186,14 @@ sparse_d2_kernel(const SpProb<T>* __restrict__ probs, const int32_t* __restrict_
 
 // The plans back into theta: nbv with the patches in place (columns stored
 // dense are there already).  A workgroup takes one tile; a thread holds 16
-// bytes or two times 16 of nbv and walks the tile's columns.
+// bytes or two times 16 of nbv and walks the tile's columns.  note: null, or a
+// word of host memory for the most rows that a tile holds in columns stored
+// dense, under the plan's tag (the host looks at it before the next call and
+// never waits for it; a tile that meets another's note may leave the smaller).
 template <typename T>
 __global__ void __launch_bounds__(256)
 sparse_write_kernel(const SpProb<T>* __restrict__ probs, const SpTile* __restrict__ tiles,
-                    const int32_t* __restrict__ stop) {
+                    const int32_t* __restrict__ stop, unsigned long long* __restrict__ note, unsigned tag) {
   __shared__ int32_t s_n[64], s_r[64][kPatch];
   __shared__ T s_v[64][kPatch];
   if (stop != nullptr && *gptr(stop) != 0) return;
@@ -1207,6 +1212,11 @@ sparse_write_kernel(const SpProb<T>* __restrict__ probs, const SpTile* __restric
   }
   __syncthreads();
   const int R = P->R;
+  if (note != nullptr && threadIdx.x < 64) {
+    const int rows = __popcll(__ballot((int)threadIdx.x < n && s_n[threadIdx.x] < 0)) * R;
+    if (threadIdx.x == 0 && rows > 0 && atomicMax(gptr(P->wide), rows) < rows)
+      __hip_atomic_store(note, (unsigned long long)tag << 32 | (unsigned)rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
   const bool vec = P->vec_theta != 0;
   const T* const nbv = gptr(P->nbv) + (int64_t)m * P->Rp;
   T* const theta = gptr(P->theta);

@@ -411,3 +411,37 @@ def test_a_measure_of_few_columns(R, few):
     say(f"R={R} few={few}: {ms}")
     same(*res)
     assert ms[140] < 1.05 * ms[7]
+
+
+def test_a_cost_rebuilt_in_place_with_wider_sets():
+    """The choice of a route is by the costs at the start.  With the cost cut
+    to a 256th in place the sets are 256 times as wide: the next call, sparse
+    still, gives the same bits, and the ones after it are dense until the run
+    is twice as long."""
+    p = inputs.balanced_plain(K=32, M=8, dtype="f32")
+    res = []
+    for whole in (False, True):
+        s = mam.solver_for(p)
+        s.init()
+        s.iterate(40)
+        s.cost.mul_(1.0 / 256)
+        for part in (10, 70):
+            if whole:
+                assert s.sparse_iterations(part) == (part == 10)
+                s.iterate(part)
+                torch.cuda.synchronize()  # (the note of a call that runs is not waited for)
+            else:
+                for _ in range(part):
+                    s.iterate(1)
+        res.append(state(s))
+        if whole:
+            assert not s.sparse_iterations(100)
+            s.iterate(100)
+            assert s.sparse_iterations(100)
+            s.init()
+            assert not s.sparse_iterations(100)  # by the estimate of these costs
+            s.cost.mul_(256.0)
+            s.init()
+            assert s.sparse_iterations(100)
+        s.close()
+    same(*res)
