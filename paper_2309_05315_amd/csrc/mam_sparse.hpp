@@ -297,8 +297,7 @@ __device__ __forceinline__ double shfl_d(double v, int src) {
 // if the float bounds of the column kernel's certificate hold with equality.
 constexpr double kTie = 0x1p-46;
 template <bool REC>
-__device__ __forceinline__ bool is_tie(int near, double top, double lam, double tau) {
-  if (near > (top - lam <= (fabs(lam) + tau) * kTie ? 1 : 0)) return true;
+__device__ __forceinline__ bool top_unsure(double top, double lam) {
   return REC && top == lam && (double)(float)top == top;
 }
 
@@ -404,11 +403,9 @@ sparse_column_kernel(SpArgs<T> a) {
     if (lo > lam) lam = (sum3(w[0], row[0], w[1], row[1], w[2], row[2], ntl, vecl) - tau) / 3.0;
   }
   const double lout = relaxed ? max_arith(lam, 0.0) : lam;
-  int near = 0;  // entries that the threshold may or may not have met, by its rounding
-#pragma unroll
-  for (int k = 0; k < NL; ++k) near += fabs(w[k] - lam) <= (fabs(lam) + tau) * kTie ? 1 : 0;
-  const bool ok = lanes_take && !is_tie<REC>(near, hi, lam, tau) &&
-                  vg + G + (fabs(vg) + fabs(G) + fabs(lam) + tau) * kTie <= lout;
+  const double eps = (fabs(lam) + tau) * kTie;
+  const bool tie = fabs(mid - lam) <= eps || fabs(lo - lam) <= eps || top_unsure<REC>(hi, lam);
+  const bool ok = lanes_take && !tie && vg + G + ((fabs(vg) + fabs(G)) * kTie + eps) <= lout;
   unsigned long long open = __ballot(have && cnt != 0 && !ok);
   if (have && ok) {
     bool in[NL];
@@ -774,9 +771,12 @@ sparse_column_kernel(SpArgs<T> a) {
       const double S = lw[0];
       if (tree) lm = (S - tq) / (double)total;
     }
-    const double top = row16_reduce<OpMaxA>(cand ? ew : -__builtin_huge_val());
-    const unsigned near = group_bits(cand && fabs(ew - lm) <= (fabs(lm) + tq) * kTie);
-    const bool tie = live && is_tie<REC>(__popc(near), top, lm, tq);
+    // entries at the threshold, but for the largest (there is none larger)
+    const double gap = ew - lm, eps = (fabs(lm) + tq) * kTie;
+    const int near = __popc(group_bits(cand && fabs(gap) <= eps));
+    bool tie = live && near > (group_bits(cand && gap > eps) != 0u ? 0 : 1);
+    if constexpr (REC)
+      tie = tie || (live && group_bits(cand && gap > 0.0) == 0u && group_bits(cand && top_unsure<REC>(ew, lm)) != 0u);
     whole |= columns_where(mine, tie);
     if (live && !tie) {
       const double lo16 = relaxed ? max_arith(lm, 0.0) : lm;
@@ -791,6 +791,7 @@ sparse_column_kernel(SpArgs<T> a) {
       }
       if (bits == 0u) {
         // nothing active: the largest entry stays as a witness (pi_hat = 0)
+        const double top = row16_reduce<OpMaxA>(cand ? ew : -__builtin_huge_val());
         const unsigned eq = group_bits(cand && ew == top);
         bits = eq & (0u - eq);
         if (bits == 0u) bits = 1u;
@@ -890,52 +891,38 @@ sparse_column_kernel(SpArgs<T> a) {
     // and an even number of rounds can be left out.
     double lm = uniform_d(lamv[jj]), lset = lm, lm1 = lm, lm2 = __builtin_nan(""), S, least, most;
     int na = 0, last = -1, last1 = -1, last2 = -2;
-    for (int it = 0; it < R + 4; ++it) {
-      if (lm == lm2 && last == last2) it += (R + 3 - it) & ~1;
+    bool settled = false;
+    for (int it = 0;; ++it) {
+      if (lm == lm2 && last == last2 && it < R + 4) it += (R + 3 - it) & ~1;
       lm2 = lm1;
       last2 = last1;
       lm1 = lm;
       last1 = last;
-      na = count(lm, &S, &least, &most);
+      settled = settled || it >= R + 4;
+      if (settled) {
+        if (!relaxed || na == 0) break;
+        lset = max_arith(lset, max_arith(lm, 0.0));  // of the entries that it took, those above 0
+      }
+      na = count(settled ? lset : lm, &S, &least, &most);
+      if (settled) break;
       if (na == 0) {
+        settled = lm == lm && last >= 0;
         if (lm != lm) {
           lm = most - tq;
           last = 0x7fffffff;
-        } else if (last < 0) {
+        } else if (!settled) {
           lm = __builtin_nan("");
-        } else {
-          break;
         }
         continue;
       }
       lset = lm;
       lm = (S - tq) / (double)na;
-      if (na == last || ((double)float_down(least) >= lm && (double)float_up(most) <= lm)) break;
+      settled = na == last || ((double)float_down(least) >= lm && (double)float_up(most) <= lm);
       last = na;
     }
-    double lo2 = lm;
-    if (relaxed) {  // of the entries that the column kernel took, those above 0
-      lo2 = max_arith(lm, 0.0);
-      lset = max_arith(lset, lo2);
-      na = na != 0 ? count(lset, &S, &least, &most) : 0;
-    }
-    int brow = 0;  // nothing active: a row of the largest w stays as a witness
-    if (na == 0) {
-      double best = -__builtin_huge_val();
-      for (int v = 0; v < nwave; ++v)
-        for (int k0 = 0; k0 < vpt; k0 += KW) {
-          rows_of(v, k0);
-#pragma unroll
-          for (int i = 0; i < KW; ++i)
-            if (x[i] > best) {
-              best = x[i];
-              brow = rx[i];
-            }
-        }
-      const unsigned long long eq = __ballot(best == wave_reduce<OpMaxA>(best));
-      brow = __builtin_amdgcn_readlane(brow, eq ? __builtin_ctzll(eq) : 0);
-    }
+    const double lo2 = relaxed ? max_arith(lm, 0.0) : lm;
     // the new values; a row's w is formed before its value is stored
+    // (nothing active: a row of the largest w stays as a witness)
     int pos = 0;
     double vm = -__builtin_huge_val();
     const bool dense = na > kPatch;
@@ -956,7 +943,9 @@ sparse_column_kernel(SpArgs<T> a) {
           if (dense) {
             if (r >= 0) th[r] = nv;
           } else {
-            const bool keep = r >= 0 && (na ? in : r == brow);
+            const bool wit = na == 0 && pos == 0 && r >= 0 && x[i] == most;
+            const unsigned long long top = __ballot(wit);
+            const bool keep = in || (wit && lane == __builtin_ctzll(top));
             const unsigned long long bits = __ballot(keep);
             if (keep) {
               const int at = pos + __popcll(bits & ((1ull << lane) - 1ull));
