@@ -3,8 +3,9 @@
 A schedule (threads per column, columns in flight, workgroups, column order,
 XCD remap) changes only speed, never results beyond summation order.  The
 tuner times candidate schedules on the device with the library's own
-column-kernel timing (HIP events on the launch stream) and keeps the
-fastest.  Results are cached in a JSON file under a key of the problem's
+column-kernel timing (HIP events on the launch stream) over calls of one
+iteration and keeps the fastest: a call of several may keep its plans as
+patches, and its kernels after the first follow no schedule.  Results are cached in a JSON file under a key of the problem's
 shape: dtype, cost mode, R, M, the S^m list and the number of cost columns.
 
     sched = autotune.tune(problem)                  # kwargs for mam.solver_for
@@ -59,6 +60,11 @@ def _store(key: str, value: dict) -> None:
         pass  # a read-only home: tuning still works, it is just not remembered
 
 
+# Part of the cache keys: schedules that were stored under another one were
+# timed over calls of several iterations.
+_TIMED = "calls of one"
+
+
 def problem_key(p) -> str:
     mode = mam._cost_mode_of(p)
     s_hash = hashlib.sha1(",".join(str(int(s)) for s in p.S).encode()).hexdigest()[:12]
@@ -107,9 +113,11 @@ def _time_solver(p, sched: dict, iters: int, warm: int) -> Optional[float]:
         return None
     try:
         s.init()
-        s.iterate(warm)
+        for _ in range(warm):
+            s.iterate(1)
         s.timing(True)
-        s.iterate(iters)
+        for _ in range(iters):
+            s.iterate(1)
         ms, n = s.timing_read()
         return ms / max(n, 1)
     finally:
@@ -121,7 +129,7 @@ def _time_solver(p, sched: dict, iters: int, warm: int) -> Optional[float]:
 def tune(p, iters: int = 6, warm: int = 2, use_cache: bool = True, wide: bool = True,
          cands: Optional[Iterable[dict]] = None) -> dict:
     """Fastest schedule for one problem, as keyword arguments of mam.solver_for."""
-    key = "single|" + problem_key(p)
+    key = f"single|{_TIMED}|" + problem_key(p)
     if use_cache and cands is None:
         hit = _load().get(key)
         if hit:
@@ -146,9 +154,11 @@ def _time_batch(problems, group_sched: dict, iters: int, warm: int) -> Optional[
         return None
     try:
         b.init()
-        b.iterate(warm)
+        for _ in range(warm):
+            b.iterate(1)
         b.timing(True)
-        b.iterate(iters)
+        for _ in range(iters):
+            b.iterate(1)
         ms, n = b.timing_read()
         return ms / max(n, 1)
     finally:
@@ -171,7 +181,7 @@ def tune_batch(problems, iters: int = 6, warm: int = 2, use_cache: bool = True) 
     cache = _load() if use_cache else {}
     for g, idx in sorted(groups.items()):
         sub = [problems[i] for i in idx]
-        key = "batch|" + hashlib.sha1("|".join(problem_key(p) for p in sub).encode()).hexdigest()[:20]
+        key = f"batch|{_TIMED}|" + hashlib.sha1("|".join(problem_key(p) for p in sub).encode()).hexdigest()[:20]
         if key in cache:
             out[g] = dict(cache[key]["schedule"])
             continue

@@ -24,6 +24,45 @@ def test_cache_path_from_environment(monkeypatch, tmp_path):
     assert autotune.cache_path() == str(tmp_path / "c.json")
 
 
+class _Timed:
+    """Stands in for a Solver or Batch; keeps the lengths of its calls."""
+    calls = []
+
+    def __init__(self, *a, **kw):
+        self.on = False
+
+    def init(self):
+        pass
+
+    close = init
+
+    def iterate(self, n):
+        self.calls.append(n)
+
+    def timing(self, on):
+        self.on = on
+
+    def timing_read(self):
+        return 1.0, 1
+
+    def group_of(self, i):
+        return 0
+
+
+def test_schedules_are_timed_over_calls_of_one_iteration(monkeypatch, tmp_path):
+    """A longer call may run kernels that follow no schedule."""
+    monkeypatch.setenv("MAM_AUTOTUNE_CACHE", str(tmp_path / "c.json"))
+    monkeypatch.setattr(autotune.mam, "solver_for", _Timed)
+    monkeypatch.setattr(autotune.mam, "Batch", _Timed)
+    p = inputs.tiny_problem(1, R=300, S=[40, 17], dtype="f32")
+    for run, n in ((lambda: autotune.tune(p, iters=5, warm=3, cands=[{}, {}]), 16),
+                   (lambda: autotune.tune_batch([p, p], iters=5, warm=3), None)):
+        _Timed.calls.clear()
+        run()
+        assert set(_Timed.calls) == {1} and len(_Timed.calls) % 8 == 0
+        assert n is None or len(_Timed.calls) == n
+
+
 @pytest.mark.gpu
 def test_tuned_schedule_runs_and_matches_oracle(monkeypatch, tmp_path):
     import json
