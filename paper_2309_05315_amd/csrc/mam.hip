@@ -2174,13 +2174,18 @@ mam_status capture_graph(Plan* pl, bool sparse) {
   });
 }
 
+// Whether n iterations replay a graph, captured by then.  Called before a
+// call's first launch: a capture that fails leaves the plans as they were
+// (after the first iteration of a sparse call they would be in the workspace).
+mam_status ready_graph(Plan* pl, int64_t n, bool sparse, bool* use) {
+  *use = pl->graph_iters > 0 && !pl->timing && n >= pl->graph_iters;
+  return *use && !(sparse ? pl->sgexec : pl->gexec) ? capture_graph(pl, sparse) : MAM_OK;
+}
+
 // Iterations k .. end - 1 of a call, whole graphs of them first.
-mam_status run_iterations(Plan* pl, int64_t k, int64_t end, bool sparse, hipStream_t st) {
-  if (pl->graph_iters > 0 && !pl->timing && end - k >= pl->graph_iters) {
-    hipGraphExec_t* const g = sparse ? &pl->sgexec : &pl->gexec;
-    if (!*g) TRY(capture_graph(pl, sparse));
-    for (; end - k >= pl->graph_iters; k += pl->graph_iters) HIP_TRY(hipGraphLaunch(*g, st));
-  }
+mam_status run_iterations(Plan* pl, int64_t k, int64_t end, bool sparse, bool graph, hipStream_t st) {
+  for (; graph && end - k >= pl->graph_iters; k += pl->graph_iters)
+    HIP_TRY(hipGraphLaunch(sparse ? pl->sgexec : pl->gexec, st));
   for (; k < end; ++k) TRY(sparse ? sparse_iteration(pl, false, st) : one_iteration(pl, st, 0));
   return MAM_OK;
 }
@@ -2191,15 +2196,18 @@ mam_status plan_iterate(Plan* pl, int64_t iters, hipStream_t st) {
   // the last iteration computes the diagnostics, outside any graph
   const int64_t plain = plain_iterations(pl, iters);
   const bool diag = plain < iters;
+  bool graph = false;
   sparse_look(pl);
   if (sparse_use(pl, plain, pl->iters_done)) {
+    TRY(ready_graph(pl, plain - 1, true, &graph));
     TRY(sparse_begin(pl, st));
     TRY(sparse_iteration(pl, true, st));
-    TRY(run_iterations(pl, 1, plain, true, st));
+    TRY(run_iterations(pl, 1, plain, true, graph, st));
     TRY(sparse_end(pl, st));
   } else {
+    TRY(ready_graph(pl, plain, false, &graph));
     TRY(long_begin(pl, iters, st));
-    TRY(run_iterations(pl, 0, plain, false, st));
+    TRY(run_iterations(pl, 0, plain, false, graph, st));
   }
   if (diag) {
     TRY(one_iteration(pl, st, 1));
@@ -2308,8 +2316,7 @@ mam_status until_run(Plan* pl, int64_t max_iters, int test, double tol, int64_t 
     mode = kUntilPeriod;
   }
   bool start = mode == kUntilSparse;
-  if (start) TRY(sparse_begin(pl, st));
-  TRY(long_begin(pl, max_iters, st));
+  // (what can fail without a launch comes before the first one: ready_graph)
   if (graph && periods > (start ? 1 : 0) &&
       (!pl->uexec || pl->utest != test || pl->uevery != every || pl->umode != mode))
     TRY(capture_until(pl, test, every, mode));
@@ -2319,6 +2326,8 @@ mam_status until_run(Plan* pl, int64_t max_iters, int test, double tol, int64_t 
     HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     pl->uev.push_back(e);
   }
+  if (start) TRY(sparse_begin(pl, st));
+  TRY(long_begin(pl, max_iters, st));
   bool seen_stop = false;
   for (int64_t i = 0; i < periods; ++i) {
     if (i >= ahead) {
