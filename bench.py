@@ -678,6 +678,9 @@ def main():
         "metric": "plan-entry updates/s (FP32 plans, FP64 thresholds) + HBM GB/s fraction of the column kernel",
         "value": value,
         "unit": "plan-entry updates/s",
+        "value_counts": "every plan entry of every iteration, also those that a bound proves inactive and no kernel "
+                        "reads (the results are exact): an effective rate over one call of 'steps' iterations; "
+                        "'roofline' is of calls of one iteration, which move the plans whole",
         "n_gpus": 1,
         "steps": args.steps,
         "warmup": args.warmup,

@@ -114,7 +114,10 @@ typedef int32_t mam_status;
                                   mam_support_update returns.  Results are
                                   identical bit for bit; the workspace grows by
                                   the patch slots (about 8 bytes x candidate
-                                  slots per column and 1024 rows in FP32).
+                                  slots per column and 1024 rows in FP32).  The
+                                  tables of its scan (least costs, masks, work
+                                  list, two doubles per measure and row) are
+                                  part of every long plan's workspace.
                                   The write-back costs about one dense write
                                   pass, so the flag pays off for calls of
                                   more than one iteration. */
@@ -484,7 +487,9 @@ mam_status mam_stream_copy(void* dst, const void* src, size_t bytes, int32_t wor
  *   theta0: as for mam_init (NULL: theta^0 = q_s/R);
  *   iters:  >= 0 iterations of Alg. 1;
  *   p_out:  device, R doubles: the barycenter of theta^iters.
- * Results are those of the handle sequence above, bit for bit.  Every call
+ * Results are those of the handle sequence above, bit for bit (a problem
+ * that fits without the tables of the sparse iterations, or of the sparse
+ * store's scan, takes dense ones).  Every call
  * on one GPU uses the same array and leaves its contents behind (every
  * region a call reads is written by that call first): calls that overlap
  * on one GPU (other threads, or streams that run concurrently) race.
@@ -500,8 +505,9 @@ mam_status mam_solve_static(const mam_desc* d, void* theta, const void* cost, co
 /* Graph replay: capture 'iters_per_launch' iterations once as a HIP graph
  * (on a stream of the library's own) and let mam_iterate replay it on the
  * caller's stream, running any remainder (and a diagnostics iteration)
- * directly.  0 turns graphs off.  Rebinding or re-initialising drops the
- * captured graph.  No memset nodes are captured. */
+ * directly.  0 turns graphs off.  Rebinding drops the captured graph;
+ * re-initialising keeps it unless the schedule or an indexed cost is read
+ * anew.  No memset nodes are captured. */
 mam_status mam_graph(mam_problem* p, int64_t iters_per_launch);
 
 /* ---- batches -------------------------------------------------------------

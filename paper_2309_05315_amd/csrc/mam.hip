@@ -930,8 +930,10 @@ void build_layout(Plan* pl) {
       lg.o_nbv = take(2 * (size_t)pl->P[0].M * (size_t)pl->P[0].R * eb);
       lg.o_spar = take(12);
     }
-    // The scan's tables of the sparse store, a few per cent of the slots in
-    // use, are part of every long plan: the flag adds the patch slots alone.
+    // The scan's tables of the sparse store are part of every long plan: the
+    // flag adds the patch slots alone.  (0.09 of 9.9 GB on 349,281 rows and
+    // 36,000 columns; with few columns to a measure the two doubles per measure
+    // and row weigh more.)
     if (!pl->sp.off) {
       before = o;
       const size_t eb = elem_bytes(pl->dtype), M = (size_t)pl->P[0].M, nsub = (size_t)lg.nrb * 4;

@@ -1,14 +1,15 @@
 """Calls of several iterations against the same iterations one call at a time
 (MI355X only).
 
-A call of one iteration runs the dense column kernels; a call of eight or
-more on at least 5 MiB of plans keeps them as -b plus their active entries in
-between.  Both store the
-same values and add the same numbers in the same order, so plans, marginals
-and barycenters are compared bit for bit.  The dense kernels are held to the
-oracle in the other files; here the sizes are the edges of the sparse
-kernels: blocks of 64 rows, partial vectors, columns with more active entries than a column lists, columns without weight or with a weight
-below the rounding of w, every cost layout.
+A call of one iteration runs the dense column kernels; a longer one may keep
+the plans as -b plus their active entries in between (sparse_iterations says
+whether it does).  Both store the same values and add the same numbers in the
+same order, so plans, marginals and barycenters are compared bit for bit.  The
+dense kernels are held to the oracle in the other files; here the sizes are
+the edges of the sparse kernels: blocks of 64 rows, partial vectors, columns
+with more active entries than a column lists, with entries exactly at their
+threshold, without weight or with a weight below the rounding of w, every cost
+layout.
 """
 import dataclasses
 import sys
