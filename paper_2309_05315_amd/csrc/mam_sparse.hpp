@@ -460,15 +460,14 @@ sparse_column_kernel(SpArgs<T> a) {
   // ---- columns left open: 16 lanes each, four at a time ----
   const int l = lane & 15, g = lane >> 4, gs = g * 16;
   const bool vec = P->vec_cost != 0;
-  // the measure's block maxima: 64 blocks a round, four to a lane
+  // the measure's block maxima: 64 blocks a round, four to a lane (a second
+  // round's are read with every column: held, they spill the FP64 kernel's
+  // registers to memory that every column then waits for)
   const int nh = nblk > 64 ? 2 : 1;
-  double db[2][4];
+  double db[4];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) db[h][i] = -__builtin_huge_val();
-    if (h < nh && h * 64 + l * 4 < nblkp) load_row4<double>(dblk + h * 64 + l * 4, db[h]);
-  }
+  for (int i = 0; i < 4; ++i) db[i] = -__builtin_huge_val();
+  if (l * 4 < nblkp) load_row4<double>(dblk + l * 4, db);
   // the lanes' patches, for the groups
 #pragma unroll
   for (int k = 0; k < NL; ++k) {
@@ -554,10 +553,12 @@ sparse_column_kernel(SpArgs<T> a) {
       for (int i = 0; i < 4; ++i) ub[h][i] = -__builtin_huge_val();
       if (h < nh && h * 64 + l * 4 < nblkp) {
         T c4[4];
+        double d4[4];
         load_row4<T>(gptr(P->cmin) + c2 * nblkp + h * 64 + l * 4, c4);
+        if (h > 0) load_row4<double>(dblk + h * 64 + l * 4, d4);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (h * 64 + l * 4 + i < nblk) ub[h][i] = __builtin_fma(-(double)c4[i], inv_rho, db[h][i]);
+          if (h * 64 + l * 4 + i < nblk) ub[h][i] = __builtin_fma(-(double)c4[i], inv_rho, h > 0 ? d4[i] : db[i]);
       }
     }
     // its patches: entry l in lane l, the rows of the first three in every lane
@@ -775,11 +776,14 @@ sparse_column_kernel(SpArgs<T> a) {
     }
     // entries at the threshold, but for the largest (there is none larger)
     const double gap = ew - lm, eps = (fabs(lm) + tq) * kTie;
-    const int near = __popc(group_bits(cand && fabs(gap) <= eps));
-    bool tie = live && near > (group_bits(cand && gap > eps) != 0u ? 0 : 1);
-    if constexpr (REC)
-      tie = tie || (live && group_bits(cand && gap > 0.0) == 0u && group_bits(cand && top_unsure<REC>(ew, lm)) != 0u);
-    whole |= columns_where(mine, tie);
+    const bool near = cand && fabs(gap) <= eps;
+    bool tie = false;
+    if (__ballot(near) != 0ull) {
+      tie = live && __popc(group_bits(near)) > (group_bits(cand && gap > eps) != 0u ? 0 : 1);
+      if constexpr (REC)
+        tie = tie || (live && group_bits(cand && gap > 0.0) == 0u && group_bits(cand && top_unsure<REC>(ew, lm)) != 0u);
+      whole |= columns_where(mine, tie);
+    }
     if (live && !tie) {
       const double lo16 = relaxed ? max_arith(lm, 0.0) : lm;
       const bool in = cand && (relaxed ? ew > lo16 : ((set >> l) & 1u) != 0u);
