@@ -2056,12 +2056,15 @@ bool sparse_use(const Plan* pl, int64_t iters, int64_t done) {
 // The estimate is of the start.  A cost or weights rebuilt in place since, or
 // sets that grow in another way, can leave so many columns stored dense that
 // an iteration waits longer for the wave that takes most of them than a dense
-// one takes.  The write-back of a sparse call notes its rows: with a note of
-// that kind (7.5 us for 1024 rows; dense iterations about 11 us and their
-// plans and costs at 4.4 TB/s) calls are dense until the run is twice as long.
-// The note is looked at and not waited for: a call that has not ended has none.
-// (32 x 32, 8 measures, FP32, the cost divided by 64 after mam_init: 86 us per
-// iteration against 35 dense, in every call and not in the first alone.)
+// one takes.  (They are neighbours, the images' brightest pixels, and few in
+// all: below a 16th of the columns.)  The write-back of a sparse call notes
+// that wave's rows: with a note of that kind (12 us for 1024 rows; dense
+// iterations about 11 us and their plans and costs at 4.4 TB/s) calls are dense
+// until the run is twice as long.  The note is looked at and not waited for: a
+// call that has not ended has none.  Grids, M = 8, FP32, us per iteration and
+// rows noted after the cost was divided in place: 32 x 32 (dense 35) by 16: 33,
+// 1024, by 64: 92, 4096; 64 x 64 (dense 255) by 64: 168 to 303, 8192 to 24576,
+// by 256: 529, 32768.  Runs at rho from 1 to 16 note 512 rows at most.
 void sparse_look(Plan* pl) {
   SparsePlan& sp = pl->sp;
   if (sp.slot < 0) return;
@@ -2071,7 +2074,7 @@ void sparse_look(Plan* pl) {
   int64_t bytes = 0;
   for (const Prob& p : pl->P)
     bytes += p.T * p.R * (int64_t)elem_bytes(pl->dtype) * (p.cost_mode == MAM_COST_PER_COLUMN ? 3 : 2);
-  if ((double)(uint32_t)note * 7.5 / 1024.0 > 11.0 + (double)bytes / 4.4e6) sp.hold = 2 * pl->iters_done + 32;
+  if ((double)(uint32_t)note * 12.0 / 1024.0 > 11.0 + (double)bytes / 4.4e6) sp.hold = 2 * pl->iters_done + 32;
 }
 
 // The iterations of a call before the one, if any, that computes diagnostics.
